@@ -792,6 +792,201 @@ __global__ __launch_bounds__(512) void k_gemm_int8x(double* __restrict__ buf0, d
                               UPPER ? rmax + (size_t)(1 - st->cur) * ld : nullptr, kmode, kc0, kc1, cacc, 0);
 }
 
+// ---- 64 x 64 output tiles (dense upper-only products of small and middle N)
+//
+// With 128 x 128 tiles a product of N = 720 has 21 workgroups for 256 CUs, and
+// each walks its K loop and its epilogue alone.  Here one 256-thread workgroup
+// covers an upper 64 x 64 tile; wave w its 32 x 32 block (w >> 1, w & 1) with
+// NL accumulators of 16 int32, so two workgroups share a CU and one's epilogue
+// runs beside the other's products.  The digit sums are exact and the
+// epilogue's arithmetic per element is that of int8x_tile, so X_{n+1} and its
+// row maxima are the same bit for bit.  4 planes, 5 levels, per product (encode
+// included): N = 256 24 -> 11 us, 720 40 -> 17, 1024 48 -> 20, 1536 65 -> 37,
+// 2048 81 -> 74, 3072 232 -> 174.  What bounds it at N = 2048: alone, the loads
+// take 37 us (553 MB from L2 at 15 TB/s), the MFMAs 40 us (528 tiles on 256 CUs,
+// three on some) and the LDS reads and writes about 30 us of the same LDS; a
+// deeper ring or 32-k stages changed nothing.  Above N = 3400 the operand
+// traffic, twice that of 128 x 128 tiles, costs more than the balance gives.
+constexpr int QT = 64;
+
+template <int S> struct I8Stage64 {
+    static constexpr int KS = S <= 5 ? 2 : 1;    // 32-k blocks per stage
+    static constexpr int NST = S <= 5 ? 2 : 3;   // ring depth
+    static constexpr int NBLK = 2 * S * 2 * KS;    // 1 KiB blocks per stage
+    static constexpr int PER = NBLK / 4;           // blocks per wave
+};
+
+template <int S>
+struct I8Smem64 {
+    union {
+        int8_t buf[I8Stage64<S>::NST][I8Stage64<S>::NBLK][1024];   // [stage][((op S + plane) 2 + row block) KS + k block]
+        struct {
+            double ax[QT][QT + 1];                 // |X_{n+1}| of the tile, for its row and column maxima
+            double red[3][4];
+        } e;
+    };
+};
+
+template <int S, int NL>
+__device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
+                                             const State* __restrict__ st, const int8_t* __restrict__ digits,
+                                             const double* __restrict__ scale, double* __restrict__ part, int bi,
+                                             int bj, I8Smem64<S>& sm, unsigned long long* __restrict__ rmax_next) {
+    using G = I8Stage64<S>;
+    constexpr int KS = G::KS, NST = G::NST, PER = G::PER;
+    static_assert(NL == S || NL == S + 1, "levels: the triangle or one more");
+    static_assert(G::NBLK % 4 == 0, "stage must split evenly over 4 waves");
+    const int i0 = bi * QT, j0 = bj * QT;
+    const double* __restrict__ Xc = st->cur ? buf1 : buf0;
+    double* __restrict__ Xn = st->cur ? buf0 : buf1;
+    const size_t plane = (size_t)ld * ld;
+    const int nb = ld >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int wr = w >> 1, wc = w & 1;
+
+    v16i acc[NL];
+#pragma unroll
+    for (int L = 0; L < NL; ++L)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[L][r] = 0;
+    const int fr = lane & 31;
+    const int foff = fr * 32 + 16 * ((lane >> 5) ^ dswz(fr));
+
+    auto compute = [&](int stg) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+            v4i a[S], b[S];
+            b[0] = *reinterpret_cast<const v4i*>(&sm.buf[stg][(S * 2 + wc) * KS + kk][foff]);
+#pragma unroll
+            for (int tt = 0; tt < S; ++tt)
+                a[tt] = *reinterpret_cast<const v4i*>(&sm.buf[stg][(tt * 2 + wr) * KS + kk][foff]);
+#pragma unroll
+            for (int uu = 1; uu < S; ++uu)
+                b[uu] = *reinterpret_cast<const v4i*>(&sm.buf[stg][(S * 2 + uu * 2 + wc) * KS + kk][foff]);
+#pragma unroll
+            for (int uu = 0; uu < S; ++uu)
+#pragma unroll
+                for (int tt = 0; tt < S && tt < NL - uu; ++tt)
+                    acc[tt + uu] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[tt], b[uu], acc[tt + uu], 0, 0, 0);
+        }
+        constexpr int LA = 2;                                  // lookahead in reads
+        constexpr int R = 2 * S * KS, P = (S * (S + 1) / 2 + (NL - S) * (S - 1)) * KS;
+        constexpr int MID = R - 2 - LA < P ? R - 2 - LA : P;
+        __builtin_amdgcn_sched_group_barrier(0x100, 2 + LA, 0);
+#pragma unroll
+        for (int q = 0; q < MID; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        }
+        __builtin_amdgcn_sched_group_barrier(0x008, P - MID, 0);
+    };
+    auto issue = [&](int kb, int stg) {
+#pragma unroll
+        for (int m = 0; m < PER; ++m) {
+            const int blk = w + 4 * m;
+            const int kk = blk % KS, ob = blk / KS;
+            const int op = ob / (S * 2);
+            const int rem = ob - op * (S * 2);
+            const int sl = rem >> 1, rb = rem & 1;
+            const int grb = ((op ? j0 : i0) >> 5) + rb;
+            const int8_t* g = digits + sl * plane + ((size_t)grb * nb + kb * KS + kk) * 1024 + 16 * lane;
+            __builtin_amdgcn_global_load_lds((const void*)g,
+                                             (__attribute__((address_space(3))) void*)&sm.buf[stg][blk][0], 16, 0, 0);
+        }
+    };
+    const int nk = ld / (QK * KS);
+    for (int q = 0; q < NST - 1; ++q)
+        if (q < nk) issue(q, q);
+    for (int kt = 0; kt < nk; ++kt) {
+        // as in int8x_tile: this wave's blocks of stage kt have landed, the
+        // barrier covers the other waves'
+        if (NST >= 3 && kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F70 | PER);   // vmcnt(PER)
+        else __builtin_amdgcn_s_waitcnt(0x0F70);                                 // vmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        if (kt + NST - 1 < nk) issue(kt + NST - 1, (kt + NST - 1) % NST);
+        compute(kt % NST);
+    }
+
+    const int br = st->branch;
+    const bool mirror = bi != bj;
+    const int W = digit_bits(ld, S), E2 = 2 * digit_e0(W);
+    const int gj = j0 + wc * 32 + (lane & 31);
+    auto row_of = [&](int r) { return wr * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); };
+    // X_n of the wave's block and the row scales in one burst
+    double x[16], si[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        x[r] = Xc[(size_t)(i0 + row_of(r)) * ld + gj];
+        si[r] = scale[i0 + row_of(r)];
+    }
+    const double sj = scale[gj];
+    double tr = 0.0, fro = 0.0, idm = 0.0;
+    __syncthreads();   // every wave is past the ring, which ax overlays
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int gi = i0 + row_of(r);
+        double v = 0.0;
+#pragma unroll
+        for (int L = NL - 1; L >= 0; --L) v += ldexp((double)acc[L][r], -(E2 + W * L));
+        const double p = v * (si[r] * sj);
+        const double xn = br ? 2.0 * x[r] - p : p;
+        Xn[(size_t)gi * ld + gj] = xn;
+        if (gi == gj) tr += xn;
+        fro += xn * xn;
+        idm += (p - x[r]) * (p - x[r]);
+        sm.e.ax[row_of(r)][wc * 32 + (lane & 31)] = fabs(xn);
+    }
+    tr = wred_sum(tr);
+    fro = wred_sum(fro);
+    idm = wred_sum(idm);
+    if (lane == 0) {
+        sm.e.red[0][w] = tr;
+        sm.e.red[1][w] = fro;
+        sm.e.red[2][w] = idm;
+    }
+    __syncthreads();
+    // row maxima: four lanes per row, 16 columns each; column maxima the same
+    // way off the diagonal (a diagonal tile is symmetric)
+    {
+        const int q = tid & 3, l = tid >> 2;
+        double m = 0.0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) m = fmax(m, sm.e.ax[l][q + 4 * k]);
+        m = fmax(m, __shfl_xor(m, 1, 64));
+        m = fmax(m, __shfl_xor(m, 2, 64));
+        if (q == 0) atomicMax(rmax_next + i0 + l, (unsigned long long)__double_as_longlong(m));
+        if (mirror) {
+            double c = 0.0;
+            const int col = tid & 63, r0 = (tid >> 6) * 16;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) c = fmax(c, sm.e.ax[r0 + k][col]);
+            atomicMax(rmax_next + j0 + col, (unsigned long long)__double_as_longlong(c));
+        }
+    }
+    if (tid == 0) {
+        const int t = tri_index(bi, bj, ld / QT);
+        const double wgt = mirror ? 2.0 : 1.0;
+        part[3 * t + 0] = (sm.e.red[0][0] + sm.e.red[0][1]) + (sm.e.red[0][2] + sm.e.red[0][3]);
+        part[3 * t + 1] = wgt * ((sm.e.red[1][0] + sm.e.red[1][1]) + (sm.e.red[1][2] + sm.e.red[1][3]));
+        part[3 * t + 2] = wgt * ((sm.e.red[2][0] + sm.e.red[2][1]) + (sm.e.red[2][2] + sm.e.red[2][3]));
+    }
+}
+
+template <int S, int NL>
+__global__ __launch_bounds__(256, 2) void k_gemm_int8x_t64(double* __restrict__ buf0, double* __restrict__ buf1,
+                                                           int ld, const State* __restrict__ st,
+                                                           const int8_t* __restrict__ digits,
+                                                           const double* __restrict__ scale,
+                                                           double* __restrict__ part,
+                                                           unsigned long long* __restrict__ rmax, int tile_group) {
+    if (st->done || st->phase != 1) return;
+    extern __shared__ __align__(16) int8_t smem_raw[];
+    I8Smem64<S>& sm = *reinterpret_cast<I8Smem64<S>*>(smem_raw);
+    int bi, bj;
+    tile_of_block(blockIdx.x, ld / QT, tile_group, bi, bj);
+    int8x_tile64<S, NL>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, rmax + (size_t)(1 - st->cur) * ld);
+}
+
 // order_tile with one step per super-tile row instead of one per super-tile
 // (the list kernel maps every tile of the triangle): the same tile for
 // every position.
@@ -1074,6 +1269,38 @@ static hipError_t launch_list_kernel(SplitScratch& s, double* buf0, double* buf1
     return hipGetLastError();
 }
 
+// Dense products of which size run 64 x 64 tiles: those for which the model
+// below makes them faster, in us per product.  A round of 128 x 128 tiles over
+// the CUs takes 17 + 0.032 K (81 us at N = 2048, one round; 232 at 3072, two);
+// the 64 x 64 tiles share CUs and follow their number, 10 + 4.8e-5 T K (174 us
+// measured at N = 3072, 170 modelled; 113 against 101 at 2560, which stays on
+// 128).  From ld = 4096 on the 128 x 128 kernel splits its last round and is
+// never behind (N = 5600: 832 against 935 us).
+static bool use_tile64(int ld) {
+    if (ld >= 4096) return false;
+    const int n128 = ld / QB, n64 = ld / QT, cus = device_cus();
+    const int T128 = n128 * (n128 + 1) / 2, T64 = n64 * (n64 + 1) / 2;
+    const double t128 = ((T128 + cus - 1) / cus) * (17.0 + 0.032 * ld);
+    const double t64 = 10.0 + 4.8e-5 * (256.0 / cus) * T64 * ld;
+    return t64 < t128;
+}
+
+template <int S, int NL>
+static hipError_t launch_t64(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
+                             hipStream_t stream) {
+    const int nt = ld / QT, T = nt * (nt + 1) / 2;
+    const size_t lds = sizeof(I8Smem64<S>);
+    static std::atomic<unsigned long long> attr_done{0};
+    hipError_t e = once_per_device(attr_done, [&] {
+        return hipFuncSetAttribute((const void*)k_gemm_int8x_t64<S, NL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)lds);
+    });
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_gemm_int8x_t64<S, NL>), dim3(T), dim3(256), lds, stream, buf0, buf1, ld, st, s.digits,
+                       s.scale, part, s.rmax, 2 * s.tile_group);
+    return hipGetLastError();
+}
+
 template <int S, int NL>
 static hipError_t run_int8x(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                             hipStream_t stream, const int* env) {
@@ -1088,6 +1315,7 @@ static hipError_t run_int8x(SplitScratch& s, double* buf0, double* buf1, int ld,
         return e;
     }
     if (env) return launch_tile_kernel<S, NL, true, false>(s, buf0, buf1, ld, st, part, stream, env);
+    if (s.upper && use_tile64(ld)) return launch_t64<S, NL>(s, buf0, buf1, ld, st, part, stream);
     // dense products: the stage configuration chosen by the autotuner
     if constexpr (i8_cfg_ok(S, 2)) {
         if (s.stage_cfg == 2)
@@ -1191,7 +1419,7 @@ hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double
 
 hipError_t launch_int8x_gemm(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                              int* nslots, hipStream_t stream, const int* env) {
-    const int nt = ld / QB;
+    const int nt = ld / (s.upper && !env && use_tile64(ld) ? QT : QB);
     *nslots = nt * (nt + 1) / 2;
     const bool next = s.levels == s.slices + 1;
     if (!next && s.levels != s.slices) return hipErrorInvalidValue;

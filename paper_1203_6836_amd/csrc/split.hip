@@ -348,7 +348,7 @@ void split_free(SplitScratch& s) {
 }
 
 size_t split_part_slots(int ld) {
-    const int nt = ld / 128;
+    const int nt = ld / 64;   // 64 x 64 tiles at most
     return (size_t)nt * (nt + 1) / 2;
 }
 

@@ -346,3 +346,34 @@ def test_int8_mfma_rate_probe(ctx):
     r = ctx.sp2_int8_mfma_rate() / 1e12
     say(f"  int8 {r:.0f} TOP/s of 5000")
     assert 5000.0 / 3 < r <= 5000.0 * 1.05
+
+
+@pytest.mark.parametrize("n_atoms,recipe", [(27, {"slices": 4, "levels": 5}), (33, {"slices": 6}), (180, {"slices": 2}),
+                                            (384, {"slices": 5}), (560, {"slices": 4, "levels": 5}),
+                                            (768, {"slices": 4, "levels": 5})])
+def test_int8x_small_output_tile_equals_the_large_one(ctx, n_atoms, recipe):
+    """Direct solves of these sizes run 64 x 64 output tiles, the server's
+    128 x 128: the digit sums are exact and the update's arithmetic the same,
+    so D is the same bit for bit.  N = 108 (one padded tile), 132 and 720
+    (ragged), 1536, 2240 (17.5 padded tiles) and 3072 (several tiles per CU).
+    Two planes resolve no gap at N = 720: both ways end with the same status."""
+    import paper_1203_6836_amd as p
+    say(f"case int8x output tiles atoms={n_atoms} {recipe}")
+    pos = synth.lattice_positions(synth.cube_dims_for(n_atoms), seed=77, n_atoms=n_atoms)
+    H = otb.hamiltonian(pos, None, synth.STATIC_MODEL)
+    n_occ = 2 * n_atoms
+    srv = p.Server(ctx, max_slots=2, **recipe)
+    opts = p.options("int8x", **recipe)
+    try:
+        D_srv, _, st_srv = srv.sp2_server_wait(srv.sp2_server_submit(H, n_occ), H.shape[0])
+    except p.Sp2Error as e:
+        status, _ = ctx.sp2_density_matrix_status(to_dev(H), n_occ, opts)
+        say(f"  status {status} / {e.status}")
+        assert status == e.status == p.SP2_EGAP and recipe["slices"] == 2
+        return
+    finally:
+        srv.close()
+    D, st = ctx.sp2_density_matrix(to_dev(H), n_occ, opts)
+    say(f"  N={H.shape[0]} iterations {st['iterations']} / {st_srv['iterations']}")
+    assert st["branches"] == st_srv["branches"]
+    assert np.array_equal(D.cpu().numpy(), D_srv)
