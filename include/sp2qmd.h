@@ -232,10 +232,11 @@ sp2_status sp2_density_matrix_noalloc(sp2_ctx *ctx, int N, const double *H, int 
  * configuration of the LDS staging ring (stage_cfg 0: 64-byte K stages two
  * deep (32-byte three deep at six planes), 1: 32-byte stages three deep, 2:
  * 32-byte stages four deep, up to five planes), for FP64 the most chunks of a
- * tile split along K (8 or 16) and, up to a padded N of 2048, the output tile
- * shape (128 x 128 tiles of 4 waves, or 32 x 32 tiles whose 4 waves split K,
- * no tile order; without an entry pure FP64 solves take the 32 x 32 tile up
- * to a padded N of 1024) -- on a pseudo-random symmetric operand, and
+ * tile split along K (8 or 16) and, up to a padded N of 3968, the output tile
+ * shape (128 x 128 tiles of 4 waves, or 32 x 32 tiles whose waves split K,
+ * no tile order; without an entry pure FP64 solves take the 32 x 32 tile
+ * below a padded N of 4096 except where the 128 x 128 tiles nearly fill
+ * their last round over the CUs) -- on a pseudo-random symmetric operand, and
  * keeps the fastest (from a padded N of 4096 on, among 128 x 128 candidates
  * within 0.3 % of the fastest, the one whose tile order re-reads the fewest
  * operand panels: G = 8, then 16, 4, 32, row-major) for later solves of the

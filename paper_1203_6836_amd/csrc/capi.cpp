@@ -41,7 +41,7 @@ struct TuneChoice {
     int tile_group = 8;   // super-tile size of the tile order
     int stage_cfg = 0;    // INT8X: K-stage configuration of dense products
     int split_cap = 16;   // FP64: most chunks of a split tile
-    int tile = 0;         // FP64: output tile side, 128 or 32 (0 = 32 up to kSmallLd, else 128)
+    int tile = 0;         // FP64: output tile side, 128 or 32 (0 = as small_f64_tile)
     float ms = 0.f;       // measured ms per product
 };
 
@@ -451,7 +451,7 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     // tile, and does not keep the row maxima of the int8 encode)
     const TuneChoice f64c = tuned_choice(c, ld, SP2_PREC_FP64, 0, 0);
     const bool f64_small =
-        !(int8x || bf16x) && ((f64c.tile == 32 && ld <= kSmallMaxLd) || (f64c.tile == 0 && ld <= kSmallLd));
+        !(int8x || bf16x) && ((f64c.tile == 32 && ld <= kSmallMaxLd) || (f64c.tile == 0 && small_f64_tile(ld)));
 
     CtrlArgs a;
     a.n_occ = (double)n_occ;

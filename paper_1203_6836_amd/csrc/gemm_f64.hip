@@ -20,6 +20,7 @@
 #include <cmath>
 
 #include "gemm_internal.h"
+#include "small_f64.h"
 #include "sp2_internal.h"
 
 namespace sp2 {
@@ -244,11 +245,64 @@ hipError_t launch_tn(const GemmTN& g, int tile_group, double* chunk, size_t chun
     return hipGetLastError();
 }
 
+// Small products: one workgroup of NW waves per 32 x 32 tile, K split over its
+// waves, partial tiles added in LDS in wave order (no second launch that reads
+// chunks back).  Chosen as for the SP2 product (small_f64_tile); per symmetric
+// product N = 500 51 -> 11 us, 1020 82 -> 37, 2000 224 -> 164, 3072 779 -> 527.  With sym a tile on the diagonal writes its upper
+// triangle and mirrors it, as above.
+template <bool SYM, bool EDGE, bool VEC, int NW>
+__global__ __launch_bounds__(64 * NW) void k_gemm_tn_small(GemmTN g) {
+    constexpr int PER = kSmallTile * kSmallTile / (64 * NW);
+    __shared__ double red[NW][kSmallTile][kSmallTile + 1];
+    const int N = g.N, nt = (N + kSmallTile - 1) / kSmallTile;
+    int bi, bj;
+    tile_at<SYM>(xcd_deal(blockIdx.x, gridDim.x), nt, 16, bi, bj);
+    const int i0 = bi * kSmallTile, j0 = bj * kSmallTile;
+    const int w = threadIdx.x >> 6, nk = (N + 3) / 4;
+    const double* Cin = g.Cin;
+    double* C = g.C;
+    double cin[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = threadIdx.x + 64 * NW * q, gi = i0 + (e >> 5), gj = j0 + (e & 31);
+        cin[q] = Cin && (!EDGE || (gi < N && gj < N)) && (!SYM || gi <= gj) ? Cin[(size_t)gi * N + gj] : 0.0;
+    }
+    d4s acc[2][2];
+    small_mma<EDGE, VEC>(g.A, g.B, N, N, i0, j0, w * nk / NW, (w + 1) * nk / NW, acc);
+    small_store(red, acc);
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = threadIdx.x + 64 * NW * q, r = e >> 5, c = e & 31, gi = i0 + r, gj = j0 + c;
+        if ((EDGE && (gi >= N || gj >= N)) || (SYM && gi > gj)) continue;
+        double v = g.alpha * small_sum<NW>(red, r, c);
+        if (Cin) v += g.beta * cin[q];
+        if (gi == gj) v += g.gamma;
+        C[(size_t)gi * N + gj] = v;
+        if (SYM && gi != gj) C[(size_t)gj * N + gi] = v;
+    }
+}
+
+template <bool SYM, bool EDGE, bool VEC>
+hipError_t launch_tn_small(const GemmTN& g, hipStream_t s) {
+    const int nt = (g.N + kSmallTile - 1) / kSmallTile, T = SYM ? tri_tiles(nt) : nt * nt;
+    if (g.N <= kSmallWideLd) hipLaunchKernelGGL((k_gemm_tn_small<SYM, EDGE, VEC, 8>), dim3(T), dim3(512), 0, s, g);
+    else hipLaunchKernelGGL((k_gemm_tn_small<SYM, EDGE, VEC, 4>), dim3(T), dim3(256), 0, s, g);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_gemm_tn(const GemmTN& g, bool sym, int tile_group, double* chunk, size_t chunk_bytes,
                           hipStream_t s) {
     if (g.N < 1 || !g.A || !g.B || !g.C || (g.beta != 0.0 && !g.Cin)) return hipErrorInvalidValue;
+    if (small_f64_tile((g.N + TB - 1) / TB * TB)) {
+        const bool vec = g.N % 2 == 0 && (reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) % 16 == 0;
+        if (g.N % kSmallTile == 0 && vec)
+            return sym ? launch_tn_small<true, false, true>(g, s) : launch_tn_small<false, false, true>(g, s);
+        if (vec) return sym ? launch_tn_small<true, true, true>(g, s) : launch_tn_small<false, true, true>(g, s);
+        return sym ? launch_tn_small<true, true, false>(g, s) : launch_tn_small<false, true, false>(g, s);
+    }
     const bool edge = g.N % TB != 0;
     if (sym) return edge ? launch_tn<true, true>(g, tile_group, chunk, chunk_bytes, s)
                          : launch_tn<true, false>(g, tile_group, chunk, chunk_bytes, s);

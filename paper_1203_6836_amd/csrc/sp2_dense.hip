@@ -14,6 +14,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "small_f64.h"
 #include "sp2_internal.h"
 
 namespace sp2 {
@@ -40,6 +41,20 @@ __device__ double block_sum256(double v, double* sh) {
     if ((threadIdx.x & 63) == 0) sh[w] = v;
     __syncthreads();
     double r = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    __syncthreads();
+    return r;
+}
+
+// The same over NW waves (sums in wave order).
+template <int NW>
+__device__ __forceinline__ double block_sum(double v, double* sh) {
+    v = wave_sum(v);
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) sh[w] = v;
+    __syncthreads();
+    double r = sh[0];
+#pragma unroll
+    for (int k = 1; k < NW; ++k) r += sh[k];
     __syncthreads();
     return r;
 }
@@ -361,7 +376,6 @@ __global__ __launch_bounds__(256) void k_ctrl_step_grouped(const GroupDesc* __re
 // the other buffer; per-tile partials Tr X_{n+1}, ||X_{n+1}||_F^2,
 // ||P - X_n||_F^2 (off-diagonal tiles count twice) into part[3 * tile].
 constexpr int GB = 128;   // tile
-constexpr int SB = 32;    // tile of the small-product kernel
 constexpr int GK = 16;    // k per stage
 constexpr int GS = GB;      // LDS row stride (doubles)
 constexpr int F64_NST = 2;  // LDS stages (double buffer: 2 stages x 2 operands x 16 KiB)
@@ -586,81 +600,67 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f64(double* __restrict__ buf0,
     f64_tile<THR>(buf0, buf1, ld, st, part, env, bi, bj, kmode, kc0, kc1, cacc, 0);
 }
 
-// Small products (ld <= kSmallMaxLd; at ld <= 1024 X is at most 8 MiB and
-// stays in L2): the 128 x 128 tiles would occupy a handful of CUs, each
-// walking its K loop alone, and splitting them along K adds a second launch
-// that reads the chunks back.  Instead one workgroup per 32 x 32 upper tile (T = nt(nt+1)/2,
-// nt = ld / 32): each of its four waves multiplies a quarter of the K range
-// with operands loaded straight into registers (lane l of a 4-deep k step
-// reads row k + l / 16 of X, 16 consecutive columns per 16 lanes), the four
-// partial tiles are added in LDS in wave order, and the fused update and the
-// partials follow as in the large kernel (one slot per 32 x 32 tile).
-__global__ __launch_bounds__(256) void k_gemm_f64_small(double* __restrict__ buf0, double* __restrict__ buf1,
-                                                        int ld, const State* __restrict__ st,
-                                                        double* __restrict__ part) {
+// Small products (ld <= kSmallMaxLd): the 128 x 128 tiles occupy a part of the
+// CUs, or leave a round nearly empty, and splitting them along K adds a second
+// launch that reads the chunks back.  Instead one workgroup of NW waves per 32 x 32
+// upper tile (T = nt(nt+1)/2, nt = ld / 32): each wave multiplies its share of
+// the K range with operands loaded straight into registers, the partial tiles
+// are added in LDS in wave order, and the fused update and the partials
+// follow as in the large kernel (one slot per 32 x 32 tile).  With the
+// pipelined K loop of small_f64.h and the tile of X_n loaded beside it a
+// product takes 6.6 us at N = 256 (9.1 before), 9.5 at 512 (14.7), 33.7 at
+// 1024 (48.4), 75 at 1536 (149; 100 on 128 x 128 tiles), 169 at 2048 (282;
+// 200).  At N = 1024 and above the matrix cores are busy 45-70 % of it; 64 x 32
+// tiles (a quarter less L2 traffic, half the waves) took 175 us at 2048.
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_gemm_f64_small(double* __restrict__ buf0, double* __restrict__ buf1,
+                                                            int ld, const State* __restrict__ st,
+                                                            double* __restrict__ part) {
+    constexpr int PER = kSmallTile * kSmallTile / (64 * NW);
+    __shared__ double red[NW][kSmallTile][kSmallTile + 1];
+    __shared__ double sh[NW];
     if (st->done || st->phase != 0) return;
-    const int nts = ld / SB;
-    int t = blockIdx.x, bi = 0;
-    while (t >= nts - bi) {
-        t -= nts - bi;
-        ++bi;
-    }
-    const int bj = bi + t;
     const double* __restrict__ Xc = st->cur ? buf1 : buf0;
     double* __restrict__ Xn = st->cur ? buf0 : buf1;
-    const int i0 = bi * SB, j0 = bj * SB;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int ci = lane & 15, kr = lane >> 4;
-    const int kq = ld / 4, k0 = w * kq;    // ld is a multiple of 128: kq of 4
-    d4 acc[2][2];
+    const int nts = ld / kSmallTile;
+    int bi, bj;
+    tile_of_block(blockIdx.x, nts, 16, bi, bj);
+    const int t = tri_index(bi, bj, nts), i0 = bi * kSmallTile, j0 = bj * kSmallTile;
+    const int tid = threadIdx.x, w = tid >> 6;
+    double x[PER];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n) acc[m][n] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 4
-    for (int k = k0; k < k0 + kq; k += 4) {
-        const double* __restrict__ row = Xc + (size_t)(k + kr) * ld;
-        const double a0 = row[i0 + ci], a1 = row[i0 + 16 + ci];
-        const double b0 = row[j0 + ci], b1 = row[j0 + 16 + ci];
-        acc[0][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b0, acc[0][0], 0, 0, 0);
-        acc[0][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0, b1, acc[0][1], 0, 0, 0);
-        acc[1][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b0, acc[1][0], 0, 0, 0);
-        acc[1][1] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1, b1, acc[1][1], 0, 0, 0);
+    for (int q = 0; q < PER; ++q) {
+        const int e = tid + 64 * NW * q;
+        x[q] = Xc[(size_t)(i0 + (e >> 5)) * ld + j0 + (e & 31)];
     }
-    __shared__ double red[4][SB][SB + 1];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)   // lane l, element r: row l / 16 + 4 r, column l % 16
-                red[w][m * 16 + kr + 4 * r][n * 16 + ci] = acc[m][n][r];
+    const int nk = ld / 4;
+    d4s acc[2][2];
+    small_mma<false, true>(Xc, Xc, ld, ld, i0, j0, w * nk / NW, (w + 1) * nk / NW, acc);
+    small_store(red, acc);
     __syncthreads();
     const int br = st->branch;
-    const bool mirror = bi != bj;
     double tr = 0.0, fro = 0.0, idm = 0.0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int e = tid + 256 * q, r = e >> 5, c = e & 31;
-        const double p = ((red[0][r][c] + red[1][r][c]) + red[2][r][c]) + red[3][r][c];
+    for (int q = 0; q < PER; ++q) {
+        const int e = tid + 64 * NW * q, r = e >> 5, c = e & 31;
         const int gi = i0 + r, gj = j0 + c;
-        const double x = Xc[(size_t)gi * ld + gj];
-        const double xn = br ? 2.0 * x - p : p;
+        if (gi > gj) continue;
+        const double p = small_sum<NW>(red, r, c);
+        const double xn = br ? 2.0 * x[q] - p : p;
+        const double wgt = gi == gj ? 1.0 : 2.0;   // the mirrored element's share
         Xn[(size_t)gi * ld + gj] = xn;
-        if (mirror) Xn[(size_t)gj * ld + gi] = xn;
+        if (gi != gj) Xn[(size_t)gj * ld + gi] = xn;
         tr += gi == gj ? xn : 0.0;
-        fro += xn * xn;
-        idm += (p - x) * (p - x);
+        fro += wgt * xn * xn;
+        idm += wgt * (p - x[q]) * (p - x[q]);
     }
-    const double wgt = mirror ? 2.0 : 1.0;
-    __shared__ double sh[4];
-    const double btr = block_sum256(tr, sh);
-    const double bfr = block_sum256(fro, sh);
-    const double bid = block_sum256(idm, sh);
+    const double btr = block_sum<NW>(tr, sh);
+    const double bfr = block_sum<NW>(fro, sh);
+    const double bid = block_sum<NW>(idm, sh);
     if (tid == 0) {
-        part[3 * blockIdx.x + 0] = btr;
-        part[3 * blockIdx.x + 1] = wgt * bfr;
-        part[3 * blockIdx.x + 2] = wgt * bid;
+        part[3 * t + 0] = btr;
+        part[3 * t + 1] = bfr;
+        part[3 * t + 2] = bid;
     }
 }
 
@@ -822,13 +822,21 @@ hipError_t launch_ctrl_step_grouped(const GroupDesc* g, hipStream_t s) {
     hipLaunchKernelGGL(k_ctrl_step_grouped, dim3(kMaxGroup), dim3(256), 0, s, g);
     return hipGetLastError();
 }
+bool small_f64_tile(int ld) {
+    if (ld >= 4096) return false;
+    const int cus = device_cus(), rounds = (tri_tiles(ld / GB) + cus - 1) / cus;
+    return 1.82e-8 * (256.0 / cus) * ld * ld < 0.13 * rounds;
+}
 hipError_t launch_gemm_f64(double* buf0, double* buf1, int ld, State* st, double* part,
                            int* nslots, hipStream_t s, const int* env, int tile_group, double* tail_buf,
                            size_t tail_bytes, int split_cap, bool small_ok) {
     if (small_ok && !env && ld <= kSmallMaxLd) {
-        const int T = tri_tiles(ld / SB);
+        const int T = tri_tiles(ld / kSmallTile);
         *nslots = T;
-        hipLaunchKernelGGL(k_gemm_f64_small, dim3(T), dim3(256), 0, s, buf0, buf1, ld, st, part);
+        if (ld <= kSmallWideLd)
+            hipLaunchKernelGGL(k_gemm_f64_small<8>, dim3(T), dim3(512), 0, s, buf0, buf1, ld, st, part);
+        else
+            hipLaunchKernelGGL(k_gemm_f64_small<4>, dim3(T), dim3(256), 0, s, buf0, buf1, ld, st, part);
         return hipGetLastError();
     }
     const int nt = ld / GB;

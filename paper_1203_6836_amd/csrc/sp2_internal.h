@@ -246,10 +246,17 @@ constexpr size_t kF64Chunk = 16 * 4 * 256;
 // small_ok: a product with ld <= kSmallMaxLd and no threshold runs the
 // small-product kernel (32 x 32 tiles), whose partial slots are one per
 // 32 x 32 tile (only when no product of another kernel shares the solve's
-// slots).  Untuned solves use it up to kSmallLd; the autotuner times it
-// against the 128 x 128 kernel up to kSmallMaxLd.
-constexpr int kSmallLd = 1024;
-constexpr int kSmallMaxLd = 2048;
+// slots).  Untuned solves use it where small_f64_tile says so; the autotuner
+// times it against the 128 x 128 kernel up to kSmallMaxLd.
+constexpr int kSmallMaxLd = 3968;
+// Whether an FP64 product of padded size ld runs 32 x 32 tiles: they follow
+// the work, 1.82e-8 us N^3 per product (2048: 169 us, 3072: 527, 3584: 813),
+// the 128 x 128 tiles the rounds they make over the CUs, 0.13 us N each (2816,
+// one round of 253 tiles on 256 CUs: 389; 3072, two: 779; 3584: 912).  So the
+// large tile is ahead only where its last round is nearly full (2688-2816,
+// 3840-3968 on 256 CUs), and from 4096 on, where it splits its last round
+// (1165 against 1235 us).
+bool small_f64_tile(int ld);
 hipError_t launch_gemm_f64(double* buf0, double* buf1, int ld, State* st, double* part,
                            int* nslots, hipStream_t s, const int* env = nullptr, int tile_group = 8,
                            double* tail_buf = nullptr, size_t tail_bytes = 0, int split_cap = 16,

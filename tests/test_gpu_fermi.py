@@ -289,3 +289,40 @@ def test_finite_temperature_xlbomd_2048_orbitals_newton_passes(ctx):
     say(f"  SCF {it} iterations (res {res:.1e}); Newton passes per step {passes}, "
         f"max|q-n| {max(r['max_q_minus_n'] for r in rec):.1e}")
     assert max(passes[1:]) <= 8
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 101, 130, 545, 1055, 2050])
+def test_product_tiles_at_ragged_sizes(ctx, n):
+    """The FP64 products of the transforms at sizes around their tiles (odd
+    leading dimensions, one row past a tile, both K splits): the full and
+    symmetric products of a non-orthogonal FP64 solve and the recursion's, on
+    random symmetric matrices, against numpy.  Bars: FP64 rounding of N-term
+    sums through a 7-step factor and an 8-step recursion, far below 1e-10."""
+    import paper_1203_6836_amd as p
+    say(f"case ragged FP64 products N={n}")
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n))
+    H = 0.5 * (A + A.T) / np.sqrt(max(n, 2))
+    e, v = np.linalg.eigh(H)
+    mu, kT, steps = 0.1, 0.3, 8
+    y = (e - mu) / kT / 2.0 ** (steps + 2)
+    f = 1.0 / (1.0 + ((0.5 + y) / (0.5 - y)) ** (2.0 ** steps))
+    D, _, _ = ctx.sp2_fermi_density_matrix(to_dev(H), 1.0, kT, steps, mu=mu, max_newton=0)
+    D = D.cpu().numpy()
+    err = float(np.abs(D - (v * f) @ v.T).max())
+    say(f"  recursion max|dD| {err:.1e}")
+    assert np.array_equal(D, D.T) and err < 1e-10
+    if n < 2 or n > 1100:
+        return
+    B = rng.standard_normal((n, n))
+    S = np.eye(n) + 0.1 * (B + B.T) / np.sqrt(n)
+    n_occ = n // 2
+    w, u = np.linalg.eigh(S)
+    Z = (u / np.sqrt(w)) @ u.T
+    Hp = Z @ H @ Z
+    _, vp = np.linalg.eigh(0.5 * (Hp + Hp.T))
+    ref = Z @ (vp[:, :n_occ] @ vp[:, :n_occ].T) @ Z
+    R, _, _ = ctx.sp2_density_matrix_nonorth(to_dev(H), to_dev(S), n_occ, p.options("fp64"))
+    err = float(np.abs(R.cpu().numpy() - ref).max())
+    say(f"  non-orthogonal max|dD| {err:.1e}")
+    assert err < 1e-10
