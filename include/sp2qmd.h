@@ -359,9 +359,10 @@ sp2_status sp2_fermi_density_matrix(sp2_ctx *ctx, int N, const double *H, double
  * / kT) + 1)^(-1) over the eigenvalues e_i of H (the occupations of the
  * Fermi operator at mu; the factor 2 counts spin).  Computed without
  * eigenvalues as Tr s((H - mu I) / kT) by a Chebyshev expansion over H's
- * Gershgorin interval: coefficients on the host (8192 Chebyshev-Gauss nodes,
- * kept while above 1e-13), moments Tr T_k from about half as many N x N
- * symmetric FP64 MFMA products as coefficients.  H: N x N device, finite and
+ * Gershgorin interval: coefficients on the host (up to 8192 Chebyshev-Gauss nodes,
+ * kept while above 1e-13), moments Tr T_k from about 2 sqrt(coefficients) N x N
+ * symmetric FP64 MFMA products (sqrt(coefficients) <= 32 stored matrices, at
+ * most 32 GiB of work matrices or five of them).  H: N x N device, finite and
  * symmetric (EINVAL otherwise); mu finite; kT > 0 in the units of H; EINVAL
  * when more than about 4000 coefficients would be needed (the count grows as
  * the Gershgorin width over kT: about 1000 at kT = 0.5 and 2200 at 0.25 on

@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/sp2qmd.h"
+#include "cheb_internal.h"
 #include "f32_internal.h"
 #include "fermi_internal.h"
 #include "gemm_internal.h"
@@ -157,6 +158,7 @@ static sp2_status grow(sp2_ctx* c, void** p, size_t* cap, size_t need_bytes) {
     *cap = 0;
     if (hipMalloc(p, need_bytes) != hipSuccess) {
         *p = nullptr;
+        (void)hipGetLastError();   // the failure is reported here, not by the next launch
         return fail(c, SP2_ENOMEM, "device allocation of " + std::to_string(need_bytes) + " bytes failed");
     }
     *cap = need_bytes;
@@ -1168,15 +1170,122 @@ extern "C" sp2_status sp2_fermi_density_matrix(sp2_ctx* c, int N, const double* 
     return SP2_OK;
 }
 
+// ---- Chebyshev moments
+// Tr T_k(Ht), k < m, of Ht = (H - ctr I) / w, from the stored T_1 .. T_s and
+// the multiples T_s, T_2s, .. (s - 1 + Q - 1 products): Tr T_qs directly and
+// Tr T_(qs+j) = 2 <T_qs, T_j> - Tr T_|qs-j|.  s is about sqrt(m), which makes
+// the products fewest while the elements read for the dots stay m N^2 / 2.
+// The matrices (s + 2 of N x N) lie in nobuf: at most 32 GiB of them, but
+// always the five of the recursion; an allocation that fails is tried again
+// with fewer.
+struct ChebBasis {
+    int s = 0;            // stored polynomials, T_j at T + (j - 1) N^2
+    double* T = nullptr;
+    double* buf[2] = {nullptr, nullptr};   // two more N x N matrices
+    std::vector<double> mom;               // Tr T_k, k < m
+};
+
+static int cheb_stored(int N, int m) {
+    const double cap = std::max(5.0, std::floor(32.0 * 1073741824.0 / (8.0 * N * N)));
+    return std::max(1, std::min({(int)std::lround(std::sqrt((double)m)), kChebMaxS, (int)cap - 2}));
+}
+static int cheb_multiples(int m, int s) { return std::max((m + s - 1) / s - 1, 0); }
+
+static sp2_status cheb_moments(sp2_ctx* c, int N, const double* H, double ctr, double w, int m, ChebBasis* b) {
+    const size_t n2 = (size_t)N * N;
+    const int nblk = cheb_dot_blocks(N);
+    sp2_status s = SP2_ENOMEM;
+    for (b->s = cheb_stored(N, m); b->s >= 1; b->s = b->s == 1 ? 0 : (b->s + 1) / 2) {
+        const size_t slots = (size_t)cheb_multiples(m, b->s) * b->s;
+        size_t nb = c->nocap;
+        s = grow(c, (void**)&c->nobuf, &nb,
+                 ((b->s + 2) * n2 + slots * (nblk + 1) + kChebMaxS) * sizeof(double));
+        c->nocap = nb;
+        if (s != SP2_ENOMEM) break;
+    }
+    if (s != SP2_OK) return s;
+    const int S = b->s, Q = cheb_multiples(m, S);
+    const int nslots = Q * S;
+    double* T = b->T = c->nobuf;
+    b->buf[0] = T + S * n2;
+    b->buf[1] = b->buf[0] + n2;
+    double* part = b->buf[1] + n2;
+    double* out = part + (size_t)nslots * nblk;   // S traces, then the Q x S sums
+    hipStream_t st = c->stream;
+    HIPCHK(c, launch_cheb_scale(H, N, ctr, 1.0 / w, T, st));
+    for (int j = 2; j <= S; ++j) {   // T_j = 2 Ht T_(j-1) - T_(j-2)
+        double* Tj = T + (size_t)(j - 1) * n2;
+        const double* prev = j > 2 ? T + (size_t)(j - 3) * n2 : nullptr;
+        if ((s = prod(c, N, T, Tj - n2, Tj, true, 2.0, prev ? 0.0 : -1.0, prev ? -1.0 : 0.0, prev)) != SP2_OK)
+            return s;
+    }
+    HIPCHK(c, launch_cheb_traces(T, N, S, out, st));
+    const double* Ts = T + (size_t)(S - 1) * n2;
+    const double* G = Ts;      // T_qs
+    const double* Gp = nullptr;   // T_(q-1)s (null: I)
+    for (int q = 1; q <= Q; ++q) {
+        HIPCHK(c, launch_cheb_dots(G, T, N, S, part + (size_t)(q - 1) * S * nblk, st));
+        if (q == Q) break;
+        // T_(q+1)s = 2 T_s T_qs - T_(q-1)s, over T_(q-1)s once that is in a buffer
+        double* out_m = q % 2 ? b->buf[0] : b->buf[1];
+        if ((s = prod(c, N, Ts, G, out_m, true, 2.0, Gp ? 0.0 : -1.0, Gp ? -1.0 : 0.0, Gp)) != SP2_OK) return s;
+        Gp = G;
+        G = out_m;
+    }
+    HIPCHK(c, launch_cheb_sums(part, nblk, nslots, out + S, st));
+    std::vector<double> h(S + nslots);
+    HIPCHK(c, hipMemcpyAsync(h.data(), out, h.size() * sizeof(double), hipMemcpyDeviceToHost, st));
+    HIPCHK(c, hipStreamSynchronize(st));
+    b->mom.assign(std::max((Q + 1) * S, S + 1), 0.0);
+    b->mom[0] = N;
+    for (int j = 1; j <= S; ++j) b->mom[j] = h[j - 1];
+    for (int q = 1; q <= Q; ++q) {
+        const double* d = &h[S + (size_t)(q - 1) * S];
+        b->mom[q * S] = d[0];
+        for (int j = 1; j < S; ++j) b->mom[q * S + j] = 2.0 * d[j] - b->mom[q * S - j];
+    }
+    return SP2_OK;
+}
+
+// Coefficients of g over [-1, 1] (g(x) at the nodes x) and the number m of
+// them up to the last above tol, by Chebyshev-Gauss quadrature on M nodes
+// with m + 72 <= M / 2, M doubled up to kChebNodes (m + 8 >= M / 2 there: not
+// resolved, returned as m = 0).  m_guess: where to start.
+constexpr int kChebNodes = 8192;
+template <typename F>
+static int cheb_expand(F g, double tol, int m_guess, std::vector<double>* x, std::vector<double>* a) {
+    int M = 256;
+    while (M < kChebNodes && 2 * (m_guess + 72) > M) M *= 2;
+    for (;; M *= 2) {
+        *x = cheb_nodes(M);
+        std::vector<double> v(M);
+        for (int j = 0; j < M; ++j) v[j] = g((*x)[j]);
+        cheb_coefficients(v, *a);
+        int m = 0;
+        for (int k = 0; k < M / 2 && k < m + 64; ++k)   // stop after 64 coefficients below the tolerance
+            if (std::fabs((*a)[k]) > tol) m = k + 1;
+        if (M < kChebNodes ? m + 72 <= M / 2 : m + 8 < M / 2) return std::max(m, 2);
+        if (M >= kChebNodes) return 0;
+    }
+}
+
+// A first guess of the number of coefficients above tol of a function with
+// poles at i pi kT from an interval of half width w: the coefficients fall by
+// rho = a + sqrt(1 + a^2) each, a = pi kT / w.
+static int cheb_guess(double kT, double w, double tol) {
+    const double a = 3.14159265358979323846 * kT / w;
+    const double m = -std::log(tol) / std::log(a + std::sqrt(1.0 + a * a));
+    return (int)std::min(std::max(m, 2.0), (double)kChebNodes);
+}
+
 // Electronic entropy S / k_B = -2 sum_i [f_i ln f_i + (1 - f_i) ln(1 - f_i)]
 // (Eq. Entropy) of the Fermi occupations f_i = (exp(beta (e_i - mu)) + 1)^(-1)
 // of H's eigenvalues, as Tr s(beta (H - mu I)) expanded in Chebyshev
 // polynomials of Ht = (H - c I) / w over the Gershgorin interval [c - w, c + w].
 // s(x) = ln(1 + e^-|x|) + |x| / (1 + e^|x|) is analytic within pi / beta of the
-// real axis, so the coefficients fall geometrically.  The moments Tr T_k(Ht)
-// come from T_0 .. T_K alone: Tr T_2k = 2 <T_k, T_k> - N and
-// Tr T_(2k+1) = 2 <T_(k+1), T_k> - Tr T_1, one product per k.
-constexpr int kEntropyNodes = 8192;   // Chebyshev-Gauss nodes of the coefficients
+// real axis, so the coefficients fall geometrically.  About 1090 moments at
+// kT = 0.5 eV on the sp lattices: 64 products instead of the 545 of one per
+// pair of moments, N = 500 56 -> 2.6 ms, 2048 140 -> 18, 4096 757 -> 105.
 constexpr double kEntropyCoefTol = 1e-13;
 
 static double fermi_entropy_term(double x) {   // s(x) per state, spin not counted
@@ -1194,14 +1303,9 @@ extern "C" sp2_status sp2_fermi_entropy(sp2_ctx* c, int N, const double* H, doub
     if (!(kT > 0.0) || !std::isfinite(kT) || !std::isfinite(mu)) return fail(c, SP2_EINVAL, "need finite mu and kT > 0");
     HIPCHK(c, hipSetDevice(c->device));
     sp2_status s;
-    const size_t n2 = (size_t)N * N;
-    const int kmax = kEntropyNodes / 2;
-    size_t nb = c->nocap;
-    if ((s = grow(c, (void**)&c->nobuf, &nb, (3 * n2 + kmax + 8) * sizeof(double))) != SP2_OK) return s;
-    c->nocap = nb;
     size_t pbytes = c->partcap * sizeof(double);
-    if ((s = grow(c, (void**)&c->part, &pbytes,
-                  std::max<size_t>({(size_t)(N + 3) / 4 * 2, (size_t)kDotBlocks, 1024}) * sizeof(double))) != SP2_OK)
+    if ((s = grow(c, (void**)&c->part, &pbytes, std::max<size_t>((size_t)(N + 3) / 4 * 2, 1024) * sizeof(double))) !=
+        SP2_OK)
         return s;
     c->partcap = pbytes / sizeof(double);
     hipStream_t st = c->stream;
@@ -1215,66 +1319,15 @@ extern "C" sp2_status sp2_fermi_entropy(sp2_ctx* c, int N, const double* H, doub
     const double beta = 1.0 / kT;
     const double ctr = 0.5 * (c->st_host->eps_min + c->st_host->eps_max);
     const double w = std::max(0.5 * (c->st_host->eps_max - c->st_host->eps_min) * (1.0 + 1e-12), 1e-300);
-    // coefficients a_k = (2 / M) sum_j s(beta (w t_j + ctr - mu)) cos(k theta_j), t_j = cos theta_j
-    std::vector<double> g(kEntropyNodes), a(kmax);
-    const double pi = 3.14159265358979323846;
-    for (int j = 0; j < kEntropyNodes; ++j)
-        g[j] = fermi_entropy_term(beta * (w * std::cos(pi * (j + 0.5) / kEntropyNodes) + ctr - mu));
-    // cos(k theta_j) by rotating (cos, sin)(k theta_j) by theta_j, recomputed
-    // exactly every 32 orders (rounding stays near 32 ulp)
-    std::vector<double> ck(kEntropyNodes), sk(kEntropyNodes), c1(kEntropyNodes), s1(kEntropyNodes);
-    for (int j = 0; j < kEntropyNodes; ++j) {
-        c1[j] = std::cos(pi * (j + 0.5) / kEntropyNodes);
-        s1[j] = std::sin(pi * (j + 0.5) / kEntropyNodes);
-    }
-    int m = 0;
-    for (int k = 0; k < kmax && k < m + 64; ++k) {   // stop after 64 coefficients below the tolerance
-        double acc = 0.0;
-        if (k % 32 == 0) {
-            for (int j = 0; j < kEntropyNodes; ++j) {   // k theta_j reduced mod 2 pi in integers
-                const long long r = ((long long)k * (2 * j + 1)) % (4LL * kEntropyNodes);
-                ck[j] = std::cos(pi * (double)r / (2.0 * kEntropyNodes));
-                sk[j] = std::sin(pi * (double)r / (2.0 * kEntropyNodes));
-            }
-        } else {
-            for (int j = 0; j < kEntropyNodes; ++j) {
-                const double cn = ck[j] * c1[j] - sk[j] * s1[j];
-                sk[j] = sk[j] * c1[j] + ck[j] * s1[j];
-                ck[j] = cn;
-            }
-        }
-        for (int j = 0; j < kEntropyNodes; ++j) acc += g[j] * ck[j];
-        a[k] = 2.0 * acc / kEntropyNodes;
-        if (std::fabs(a[k]) > kEntropyCoefTol) m = k + 1;
-    }
-    if (m + 8 >= kmax)
+    std::vector<double> x, a;
+    const int m = cheb_expand([&](double t) { return fermi_entropy_term(beta * (w * t + ctr - mu)); },
+                              kEntropyCoefTol, cheb_guess(kT, w, kEntropyCoefTol), &x, &a);
+    if (m == 0)
         return fail(c, SP2_EINVAL, "kT too small against the spectral width for the entropy's Chebyshev expansion");
-    m = std::max(m, 2);
-    const int K = (m + 1) / 2;   // T_0 .. T_K give the moments 0 .. 2K
-    double* Ht = c->nobuf;
-    double* Tp = Ht + n2;   // T_(k-1)
-    double* Tc = Tp + n2;   // T_k
-    double* mom = Tc + n2;  // <T_k, T_k>, <T_(k+1), T_k> pairs
-    HIPCHK(c, launch_cheb_init(H, N, ctr, 1.0 / w, Ht, Tp, st));   // Tp = T_0 = I
-    HIPCHK(c, hipMemcpyAsync(Tc, Ht, n2 * sizeof(double), hipMemcpyDeviceToDevice, st));   // T_1
-    HIPCHK(c, launch_dot(Tp, Tc, n2, c->part, &ns, mom, st));   // Tr T_1
-    for (int k = 1; k <= K; ++k) {
-        // <T_k, T_k> (moment 2k); then T_(k+1) = 2 Ht T_k - T_(k-1) over T_(k-1)
-        HIPCHK(c, launch_dot(Tc, Tc, n2, c->part, &ns, mom + 2 * k, st));
-        if (k == K) break;
-        if ((s = prod(c, N, Ht, Tc, Tp, true, 2.0, 0.0, -1.0, Tp)) != SP2_OK) return s;
-        std::swap(Tp, Tc);
-        HIPCHK(c, launch_dot(Tc, Tp, n2, c->part, &ns, mom + 2 * k + 1, st));   // <T_(k+1), T_k>
-    }
-    std::vector<double> h(2 * K + 1);
-    HIPCHK(c, hipMemcpyAsync(h.data(), mom, (2 * K + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
-    HIPCHK(c, hipStreamSynchronize(st));
-    // moments: mu_0 = N, mu_1 = Tr T_1, mu_2k = 2 <T_k, T_k> - N, mu_(2k+1) = 2 <T_(k+1), T_k> - mu_1
+    ChebBasis b;
+    if ((s = cheb_moments(c, N, H, ctr, w, m, &b)) != SP2_OK) return s;
     double S = 0.5 * a[0] * N;
-    for (int k = 1; k < std::min(m, 2 * K + 1); ++k) {
-        const double mk = k == 1 ? h[0] : (k % 2 == 0 ? 2.0 * h[k] - N : 2.0 * h[k] - h[0]);
-        S += a[k] * mk;
-    }
+    for (int k = 1; k < m; ++k) S += a[k] * b.mom[k];
     if (!std::isfinite(S)) return fail(c, SP2_EDEVICE, "non-finite entropy");
     *S_out = 2.0 * S;
     if (moments) *moments = m;

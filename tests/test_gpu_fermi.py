@@ -326,3 +326,30 @@ def test_product_tiles_at_ragged_sizes(ctx, n):
     err = float(np.abs(R.cpu().numpy() - ref).max())
     say(f"  non-orthogonal max|dD| {err:.1e}")
     assert err < 1e-10
+
+
+@pytest.mark.parametrize("n,kT", [(1, 0.5), (2, 0.3), (33, 40.0), (101, 2.0), (130, 0.6), (530, 0.2), (530, 4.0), (1056, 0.1)])
+def test_entropy_moments_at_ragged_sizes(ctx, n, kT):
+    """The entropy's moments for every number of stored polynomials the
+    coefficient count selects (from 2 to the most, 32) and sizes around the
+    dot kernel's tiles, on random symmetric matrices against the eigenvalues:
+    the moments are FP64 sums, so the bar of the lattice test applies.  The
+    coefficients fall by a + sqrt(1 + a^2), a = pi kT / w over the Gershgorin half
+    width w; where more than 4000 of them stay above 1e-13 the call is refused."""
+    import paper_1203_6836_amd as p
+    say(f"case entropy moments N={n} kT={kT}")
+    rng = np.random.default_rng(100 + n)
+    A = rng.standard_normal((n, n))
+    H = 0.5 * (A + A.T)
+    e = np.linalg.eigvalsh(H)
+    mu = 0.2
+    S_ref = fermi.entropy(fermi.fermi_occupations(e, mu, 1.0 / kT))
+    lo, hi = osp2.gershgorin(H)
+    if hi > lo and -np.log(1e-13) / np.arcsinh(2.0 * np.pi * kT / (hi - lo)) > 4200:
+        with pytest.raises(p.Sp2Error) as ei:
+            ctx.sp2_fermi_entropy(to_dev(H), mu, kT)
+        assert ei.value.status == p.SP2_EINVAL
+        return
+    S, m = ctx.sp2_fermi_entropy(to_dev(H), mu, kT)
+    say(f"  S {S:.12f} (eigenvalues {S_ref:.12f}), {m} coefficients")
+    assert abs(S - S_ref) < 1e-10 * max(S_ref, 1.0)
