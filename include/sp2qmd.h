@@ -323,7 +323,9 @@ sp2_status sp2_mulliken_overlap(sp2_ctx *ctx, int n_atoms, const double *D, cons
  * Fermi-operator expansion: X_0 = I/2 - beta (H - mu I) / 2^(n_steps + 2),
  * then n_steps times X <- X^2 (X^2 + (I - X)^2)^(-1) (every product is of
  * polynomials in H, formed as a symmetric FP64 MFMA product of upper tiles,
- * so each X is exactly symmetric; the inverse by Newton-Schulz).  Its
+ * so each X is exactly symmetric; the inverse by Newton-Schulz), or, where
+ * that takes fewer products, by the Chebyshev expansion of the same function
+ * of H (mu then comes from moments, at most 32 GiB of work matrices).  Its
  * exponent carries a relative error of about (beta |e - mu| / 2^n_steps)^2
  * / 12 per eigenvalue e; FP64 rounding sets a floor near 1e-11 for
  * n_steps >= 16.
@@ -345,10 +347,11 @@ sp2_status sp2_mulliken_overlap(sp2_ctx *ctx, int n_atoms, const double *D, cons
  * *mu then hold the last pass).
  *
  * D_out: N x N device, may not alias H.  newton_iterations (may be NULL):
- * passes made.  products (may be NULL): N x N FP64 matrix products made over
- * all passes (2 per step plus 2 per Newton-Schulz update; the updates per
- * inverse follow from a bound on X's spectrum, fewer in the first steps,
- * where X is near I/2).  N <= 32768 (five N x N FP64 work matrices).  Blocks
+ * passes made.  products (may be NULL): the N x N FP64 matrix products of the
+ * recursion over all passes (2 per step plus 2 per Newton-Schulz update; the
+ * updates per inverse follow from a bound on X's spectrum, fewer in the first
+ * steps, where X is near I/2); the expansion forms fewer for the same
+ * result.  N <= 32768 (five N x N FP64 work matrices at least).  Blocks
  * the host until D_out is written. */
 sp2_status sp2_fermi_density_matrix(sp2_ctx *ctx, int N, const double *H, double n_occ, double kT,
                                     int n_steps, int max_newton, double tol, double *mu,

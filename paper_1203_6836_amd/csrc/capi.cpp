@@ -1036,140 +1036,6 @@ extern "C" sp2_status sp2_density_matrix_nonorth(sp2_ctx* c, int N, const double
 }
 
 // ---------------------------------------------- finite electronic temperature
-// One pass of the recursive Fermi-operator expansion at chemical potential mu:
-// X_0 = I/2 - beta (H - mu I) / 2^(n+2), then n steps
-// X_{k+1} = X_k^2 (X_k^2 + (I - X_k)^2)^(-1), each made exactly symmetric.
-// delta0 bounds |x - 1/2| over the spectrum of X_0 (from the Gershgorin
-// interval); under the step, a bound d becomes 2 d / (1 + 4 d^2), which sets
-// the Newton-Schulz start and update count of each inverse.
-// buf holds five N x N matrices; returns the one holding X_n.
-static sp2_status fermi_pass(sp2_ctx* c, int N, const double* H, double mu, double beta, int n_steps, double delta0,
-                             double* buf, double** Xn, long long* products) {
-    const size_t n2 = (size_t)N * N;
-    double* X = buf;
-    double* X2 = buf + n2;
-    double* A = buf + 2 * n2;
-    double* Y = buf + 3 * n2;
-    double* R = buf + 4 * n2;
-    hipStream_t st = c->stream;
-    sp2_status s;
-    HIPCHK(c, launch_fermi_init(H, N, mu, beta / std::ldexp(1.0, n_steps + 2), X, st));
-    double delta = delta0;
-    for (int k = 0; k < n_steps; ++k) {
-        const double db = std::min(0.5, delta * 1.01 + 1e-9);   // margin for rounding
-        const double rho = 2.0 * db * db / (1.0 + 2.0 * db * db);
-        int updates = 0;   // error rho^2 after Y_1, squared by each update
-        for (double err = rho * rho; err > kFermiInvErr && updates < kFermiInvUpdates; err *= err) ++updates;
-        // every factor is a polynomial in H: the products are symmetric
-        if ((s = prod(c, N, X, X, X2, true)) != SP2_OK) return s;
-        HIPCHK(c, launch_fermi_a(X2, X, N, 2.0 / (1.0 + 2.0 * db * db), A, Y, st));   // A, Y_1
-        double* W = X;                                        // X is free until X_{k+1}
-        for (int j = 0; j < updates; ++j) {
-            if ((s = prod(c, N, A, Y, R, true, -1.0, 2.0)) != SP2_OK) return s;   // R = 2 I - A Y
-            if ((s = prod(c, N, Y, R, W, true)) != SP2_OK) return s;               // Y <- Y (2 I - A Y)
-            std::swap(Y, W);
-        }
-        if ((s = prod(c, N, X2, Y, W, true)) != SP2_OK) return s;      // X_{k+1} = X_k^2 A^(-1)
-        X = W;
-        *products += 2 + 2 * updates;
-        delta = std::min(0.5, 2.0 * delta / (1.0 + 4.0 * delta * delta));
-    }
-    *Xn = X;
-    return SP2_OK;
-}
-
-extern "C" sp2_status sp2_fermi_density_matrix(sp2_ctx* c, int N, const double* H, double n_occ, double kT,
-                                                int n_steps, int max_newton, double tol, double* mu,
-                                                double* D_out, int* newton_iterations, long long* products) {
-    CTX_ENTER(c);
-    if (!c) return SP2_EINVAL;
-    if (newton_iterations) *newton_iterations = 0;
-    if (products) *products = 0;
-    long long nprod = 0;
-    if (N < 1 || N > 32768 || !H || !D_out || !mu) return fail(c, SP2_EINVAL, "bad Fermi-operator arguments");
-    if (!(kT > 0.0) || !std::isfinite(kT)) return fail(c, SP2_EINVAL, "need a finite kT > 0");
-    if (n_steps < 1 || n_steps > 60) return fail(c, SP2_EINVAL, "need 1 <= n_steps <= 60");
-    if (max_newton < 0 || max_newton > 1000) return fail(c, SP2_EINVAL, "need 0 <= max_newton <= 1000");
-    if (max_newton > 0 && (!(n_occ > 0.0) || !(n_occ < N) || !(tol > 0.0)))
-        return fail(c, SP2_EINVAL, "need 0 < n_occ < N and tol > 0");
-    if (max_newton == 0 && !std::isfinite(*mu)) return fail(c, SP2_EINVAL, "a fixed mu must be finite");
-    HIPCHK(c, hipSetDevice(c->device));
-    sp2_status s;
-    const size_t n2 = (size_t)N * N;
-    size_t nb = c->nocap;
-    if ((s = grow(c, (void**)&c->nobuf, &nb, (5 * n2 + 2 * kFermiBlocks + 8) * sizeof(double))) != SP2_OK) return s;
-    c->nocap = nb;
-    double* part = c->nobuf + 5 * n2;
-    double* res = part + 2 * kFermiBlocks;
-    // the Gershgorin pass writes a (min, max) pair per 4 rows into c->part
-    size_t pbytes = c->partcap * sizeof(double);
-    if ((s = grow(c, (void**)&c->part, &pbytes, std::max<size_t>((size_t)(N + 3) / 4 * 2, 1024) * sizeof(double))) !=
-        SP2_OK)
-        return s;
-    c->partcap = pbytes / sizeof(double);
-    hipStream_t st = c->stream;
-    // validity of H and its Gershgorin interval
-    int ns = 0, nchk = 0;
-    HIPCHK(c, launch_check_h(H, N, c->chk, &nchk, st));
-    HIPCHK(c, launch_gershgorin(H, N, c->part, &ns, st));
-    HIPCHK(c, launch_bounds(c->part, ns, c->chk, nchk, c->st, st));
-    HIPCHK(c, hipMemcpyAsync(c->st_host, c->st, sizeof(State), hipMemcpyDeviceToHost, st));
-    HIPCHK(c, hipStreamSynchronize(st));
-    if (c->st_host->done == 5) return fail(c, SP2_EINVAL, "H is not finite and symmetric");
-    const double e_lo = c->st_host->eps_min, e_hi = c->st_host->eps_max;
-    const double beta = 1.0 / kT;
-    // the root stays bracketed: below e_lo - 40 kT every Fermi factor is under
-    // e^-40 (Tr < n_occ), above e_hi + 40 kT over 1 - e^-40 (Tr > n_occ)
-    double lo = e_lo - 40.0 * kT, hi = e_hi + 40.0 * kT;
-    double m = max_newton == 0 ? *mu : (std::isfinite(*mu) && *mu > lo && *mu < hi) ? *mu : 0.5 * (e_lo + e_hi);
-    // X_0 has its spectrum in [0, 1] (and A in [1/2, 1]) when
-    // beta |e - mu| <= 2^(n+1) over the Gershgorin interval
-    const double reach = std::ldexp(1.0, n_steps + 1) / beta;
-    if (!(std::max(e_hi - m, m - e_lo) <= reach) || (max_newton > 0 && !(hi - lo <= reach)))
-        return fail(c, SP2_EINVAL, "beta |e - mu| can exceed 2^(n_steps + 1): more steps needed");
-    const int evals = max_newton == 0 ? 1 : max_newton;
-    for (int it = 0; it < evals; ++it) {
-        double* X = nullptr;
-        const double delta0 = beta * std::max(e_hi - m, m - e_lo) / std::ldexp(1.0, n_steps + 2);
-        if ((s = fermi_pass(c, N, H, m, beta, n_steps, delta0, c->nobuf, &X, &nprod)) != SP2_OK) return s;
-        if (newton_iterations) *newton_iterations = it + 1;
-        if (products) *products = nprod;
-        if (max_newton == 0) {
-            HIPCHK(c, hipMemcpyAsync(D_out, X, n2 * sizeof(double), hipMemcpyDeviceToDevice, st));
-            HIPCHK(c, hipStreamSynchronize(st));
-            return SP2_OK;
-        }
-        HIPCHK(c, launch_trace_fro(X, N, part, st));
-        HIPCHK(c, launch_sum_pairs(part, kFermiBlocks, res, st));
-        HIPCHK(c, hipMemcpyAsync(c->scal_host, res, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
-        HIPCHK(c, hipStreamSynchronize(st));
-        const double t = c->scal_host[0], fr = c->scal_host[1];
-        if (!std::isfinite(t) || !std::isfinite(fr)) return fail(c, SP2_EDEVICE, "non-finite Fermi-operator trace");
-        if (std::fabs(t - n_occ) < tol || it + 1 == evals) {
-            HIPCHK(c, hipMemcpyAsync(D_out, X, n2 * sizeof(double), hipMemcpyDeviceToDevice, st));
-            HIPCHK(c, hipStreamSynchronize(st));
-            *mu = m;
-            if (std::fabs(t - n_occ) < tol) return SP2_OK;
-            return fail(c, SP2_ENOCONV, "Newton on mu did not reach Tr D = n_occ");
-        }
-        // Newton with dTr X / dmu ~ beta Tr[X (I - X)] (the Fermi function's
-        // derivative); a step out of the bracket bisects it instead
-        if (t < n_occ) lo = m;
-        else hi = m;
-        const double d = beta * (t - fr);
-        const double nm = d > 0.0 ? m - (t - n_occ) / d : NAN;
-        const double next = (nm > lo && nm < hi) ? nm : 0.5 * (lo + hi);
-        if (next == m) {   // X_0 cannot resolve a finer mu
-            HIPCHK(c, hipMemcpyAsync(D_out, X, n2 * sizeof(double), hipMemcpyDeviceToDevice, st));
-            HIPCHK(c, hipStreamSynchronize(st));
-            *mu = m;
-            return fail(c, SP2_ENOCONV, "tol is below the resolution of Tr D in mu");
-        }
-        m = next;
-    }
-    return SP2_OK;
-}
-
 // ---- Chebyshev moments
 // Tr T_k(Ht), k < m, of Ht = (H - ctr I) / w, from the stored T_1 .. T_s and
 // the multiples T_s, T_2s, .. (s - 1 + Q - 1 products): Tr T_qs directly and
@@ -1187,15 +1053,17 @@ struct ChebBasis {
 
 static int cheb_stored(int N, int m) {
     const double cap = std::max(5.0, std::floor(32.0 * 1073741824.0 / (8.0 * N * N)));
-    return std::max(1, std::min({(int)std::lround(std::sqrt((double)m)), kChebMaxS, (int)cap - 2}));
+    return cheb_round(std::min((int)std::ceil(std::sqrt((double)m)), (int)cap - 2));
 }
 static int cheb_multiples(int m, int s) { return std::max((m + s - 1) / s - 1, 0); }
 
-static sp2_status cheb_moments(sp2_ctx* c, int N, const double* H, double ctr, double w, int m, ChebBasis* b) {
+// min_s: fewest stored polynomials to try; moments: whether b->mom is formed.
+static sp2_status cheb_moments(sp2_ctx* c, int N, const double* H, double ctr, double w, int m, int min_s, bool moments,
+                               ChebBasis* b) {
     const size_t n2 = (size_t)N * N;
     const int nblk = cheb_dot_blocks(N);
     sp2_status s = SP2_ENOMEM;
-    for (b->s = cheb_stored(N, m); b->s >= 1; b->s = b->s == 1 ? 0 : (b->s + 1) / 2) {
+    for (b->s = cheb_stored(N, m); b->s >= min_s; b->s = b->s == 1 ? 0 : cheb_round(b->s / 2)) {
         const size_t slots = (size_t)cheb_multiples(m, b->s) * b->s;
         size_t nb = c->nocap;
         s = grow(c, (void**)&c->nobuf, &nb,
@@ -1219,18 +1087,23 @@ static sp2_status cheb_moments(sp2_ctx* c, int N, const double* H, double ctr, d
         if ((s = prod(c, N, T, Tj - n2, Tj, true, 2.0, prev ? 0.0 : -1.0, prev ? -1.0 : 0.0, prev)) != SP2_OK)
             return s;
     }
+    if (!moments) return SP2_OK;
     HIPCHK(c, launch_cheb_traces(T, N, S, out, st));
     const double* Ts = T + (size_t)(S - 1) * n2;
-    const double* G = Ts;      // T_qs
-    const double* Gp = nullptr;   // T_(q-1)s (null: I)
+    // Multiple q is T_s itself or lies in buf[q % 2]; two at a time for the dots
+    auto mult = [&](int q) { return q == 1 ? Ts : (const double*)b->buf[q % 2]; };
     for (int q = 1; q <= Q; ++q) {
-        HIPCHK(c, launch_cheb_dots(G, T, N, S, part + (size_t)(q - 1) * S * nblk, st));
-        if (q == Q) break;
-        // T_(q+1)s = 2 T_s T_qs - T_(q-1)s, over T_(q-1)s once that is in a buffer
-        double* out_m = q % 2 ? b->buf[0] : b->buf[1];
-        if ((s = prod(c, N, Ts, G, out_m, true, 2.0, Gp ? 0.0 : -1.0, Gp ? -1.0 : 0.0, Gp)) != SP2_OK) return s;
-        Gp = G;
-        G = out_m;
+        if (q > 1) {   // T_qs = 2 T_s T_(q-1)s - T_(q-2)s, over T_(q-2)s
+            const double* Gp = q > 2 ? mult(q - 2) : nullptr;
+            if ((s = prod(c, N, Ts, mult(q - 1), b->buf[q % 2], true, 2.0, Gp ? 0.0 : -1.0, Gp ? -1.0 : 0.0, Gp)) !=
+                SP2_OK)
+                return s;
+        }
+        if (q % 2 == 0 || q == Q) {
+            const int q0 = q % 2 ? q : q - 1;
+            HIPCHK(c, launch_cheb_dots(mult(q0), q0 < q ? mult(q) : nullptr, T, N, S,
+                                       part + (size_t)(q0 - 1) * S * nblk, st));
+        }
     }
     HIPCHK(c, launch_cheb_sums(part, nblk, nslots, out + S, st));
     std::vector<double> h(S + nslots);
@@ -1278,6 +1151,292 @@ static int cheb_guess(double kT, double w, double tol) {
     return (int)std::min(std::max(m, 2.0), (double)kChebNodes);
 }
 
+// One pass of the recursive Fermi-operator expansion at chemical potential mu:
+// X_0 = I/2 - beta (H - mu I) / 2^(n+2), then n steps
+// X_{k+1} = X_k^2 (X_k^2 + (I - X_k)^2)^(-1), each made exactly symmetric.
+// delta0 bounds |x - 1/2| over the spectrum of X_0 (from the Gershgorin
+// interval); under the step, a bound d becomes 2 d / (1 + 4 d^2), which sets
+// the Newton-Schulz start and update count of each inverse.
+// buf holds five N x N matrices; returns the one holding X_n.
+static double fermi_margin(double delta) { return std::min(0.5, delta * 1.01 + 1e-9); }   // for rounding
+static double fermi_next(double delta) { return std::min(0.5, 2.0 * delta / (1.0 + 4.0 * delta * delta)); }
+static int fermi_updates(double delta) {   // error rho^2 after Y_1, squared by each update
+    const double db = fermi_margin(delta), rho = 2.0 * db * db / (1.0 + 2.0 * db * db);
+    int updates = 0;
+    for (double err = rho * rho; err > kFermiInvErr && updates < kFermiInvUpdates; err *= err) ++updates;
+    return updates;
+}
+// Products of one pass.
+static long long fermi_products(double delta, int n_steps) {
+    long long p = 0;
+    for (int k = 0; k < n_steps; ++k, delta = fermi_next(delta)) p += 2 + 2 * fermi_updates(delta);
+    return p;
+}
+static sp2_status fermi_pass(sp2_ctx* c, int N, const double* H, double mu, double beta, int n_steps, double delta0,
+                             double* buf, double** Xn) {
+    const size_t n2 = (size_t)N * N;
+    double* X = buf;
+    double* X2 = buf + n2;
+    double* A = buf + 2 * n2;
+    double* Y = buf + 3 * n2;
+    double* R = buf + 4 * n2;
+    hipStream_t st = c->stream;
+    sp2_status s;
+    HIPCHK(c, launch_fermi_init(H, N, mu, beta / std::ldexp(1.0, n_steps + 2), X, st));
+    double delta = delta0;
+    for (int k = 0; k < n_steps; ++k) {
+        const double db = fermi_margin(delta);
+        const int updates = fermi_updates(delta);
+        // every factor is a polynomial in H: the products are symmetric
+        if ((s = prod(c, N, X, X, X2, true)) != SP2_OK) return s;
+        HIPCHK(c, launch_fermi_a(X2, X, N, 2.0 / (1.0 + 2.0 * db * db), A, Y, st));   // A, Y_1
+        double* W = X;                                        // X is free until X_{k+1}
+        for (int j = 0; j < updates; ++j) {
+            if ((s = prod(c, N, A, Y, R, true, -1.0, 2.0)) != SP2_OK) return s;   // R = 2 I - A Y
+            if ((s = prod(c, N, Y, R, W, true)) != SP2_OK) return s;               // Y <- Y (2 I - A Y)
+            std::swap(Y, W);
+        }
+        if ((s = prod(c, N, X2, Y, W, true)) != SP2_OK) return s;      // X_{k+1} = X_k^2 A^(-1)
+        X = W;
+        delta = fermi_next(delta);
+    }
+    *Xn = X;
+    return SP2_OK;
+}
+
+static double fermi_entropy_term(double x) {   // s(x) per state, spin not counted
+    const double a = std::fabs(x);
+    const double e = std::exp(-a);
+    return std::log1p(e) + a * e / (1.0 + e);
+}
+
+// ---- the recursion's function as one Chebyshev expansion
+// X_n is a function of H: with t = beta (e - mu) / 2^(n+1) an eigenvalue e of H becomes
+// f(e) = ((1 - t)^(2^n)) / ((1 - t)^(2^n) + (1 + t)^(2^n)) = 1 / (1 + exp(2^(n+1) atanh t)).
+// Its Chebyshev expansion over the Gershgorin interval has about 36 w / (pi kT)
+// coefficients above 1e-15 (1250 at kT = 0.5 eV on the sp lattices).  T_k does not
+// depend on mu: the moments Tr T_k give Tr f and Tr f^2 at every mu on the
+// host, so the whole Newton solve costs the products of the moments once, and
+// D = sum_k c_k T_k at the final mu as many again (cheb_evaluate).  That is
+// about 100 products where the recursion makes 114 per pass and 5 passes, and
+// none of them amplifies rounding errors: kT = 0.5 eV, N = 500 6.5 -> 3.1 ms, 2048
+// 97 -> 26, 4096 672 -> 165; max|D - f(H)| at the same mu 5e-12 -> 4e-15.
+static double fermi_occupation(double e, double mu, double beta, int n_steps) {
+    const double t = std::max(-1.0, std::min(1.0, beta * (e - mu) / std::ldexp(1.0, n_steps + 1)));
+    return 1.0 / (1.0 + std::exp(std::ldexp(std::atanh(t), n_steps + 1)));
+}
+constexpr double kFermiCoefTol = 1e-15;
+// Tr D of the expansion and the moments' own sums agree to about 1e-13 N: a
+// tighter tol is left to the recursion.
+constexpr double kFermiTolPerN = 4e-13;
+
+// D = sum_k c_k T_k(Ht) from the stored polynomials: sum_q B_q(Ht) T_q(T_s(Ht)) with
+// B_q = sum_j b_qj T_j, by Clenshaw's recurrence in T_s (one product and one
+// pass over the stored matrices per q).
+static sp2_status cheb_evaluate(sp2_ctx* c, int N, const ChebBasis& B, std::vector<double> coef, double* D_out) {
+    int d = 1;
+    for (int k = 0; k < (int)coef.size() / 2; ++k)
+        if (std::fabs(coef[k]) > kFermiCoefTol) d = k + 1;
+    coef.resize(d);
+    coef[0] *= 0.5;
+    const int S = B.s, Q = (d - 1) / S;
+    std::vector<std::vector<double>> b;
+    cheb_blocks(coef, S, Q, b);
+    const size_t n2 = (size_t)N * N;
+    const double* Ts = B.T + (size_t)(S - 1) * n2;
+    auto combine = [&](int q, const double* V, double* C, bool full) -> sp2_status {
+        ChebCoef cc{};
+        std::copy(b[q].begin(), b[q].end(), cc.b);
+        HIPCHK(c, launch_cheb_combine(B.T, N, S, cc, V, C, full, c->stream));
+        return SP2_OK;
+    };
+    if (Q == 0) return combine(0, nullptr, D_out, true);
+    // V_q = B_q + 2 T_s V_(q+1) - V_(q+2), V_q over V_(q+2)
+    sp2_status s;
+    double *V1 = B.buf[0], *V2 = B.buf[1];   // V_(q+1), V_(q+2)
+    if ((s = combine(Q, nullptr, V1, true)) != SP2_OK) return s;
+    for (int q = Q - 1; q >= 1; --q) {
+        if ((s = combine(q, q == Q - 1 ? nullptr : V2, V2, false)) != SP2_OK) return s;
+        if ((s = prod(c, N, Ts, V1, V2, true, 2.0, 0.0, 1.0, V2)) != SP2_OK) return s;
+        std::swap(V1, V2);
+    }
+    if ((s = combine(0, Q == 1 ? nullptr : V2, V2, false)) != SP2_OK) return s;
+    return prod(c, N, Ts, V1, D_out, true, 1.0, 0.0, 1.0, V2);   // D = B_0 + T_s V_1 - V_2
+}
+
+// sp2_fermi_density_matrix; entropy (may be null): S / k_B at the final mu, from
+// the same moments where the expansion is used.
+static sp2_status fermi_solve(sp2_ctx* c, int N, const double* H, double n_occ, double kT, int n_steps,
+                              int max_newton, double tol, double* mu, double* D_out, int* newton_iterations,
+                              long long* products, double* entropy) {
+    if (newton_iterations) *newton_iterations = 0;
+    if (products) *products = 0;
+    long long nprod = 0;
+    if (N < 1 || N > 32768 || !H || !D_out || !mu) return fail(c, SP2_EINVAL, "bad Fermi-operator arguments");
+    if (!(kT > 0.0) || !std::isfinite(kT)) return fail(c, SP2_EINVAL, "need a finite kT > 0");
+    if (n_steps < 1 || n_steps > 60) return fail(c, SP2_EINVAL, "need 1 <= n_steps <= 60");
+    if (max_newton < 0 || max_newton > 1000) return fail(c, SP2_EINVAL, "need 0 <= max_newton <= 1000");
+    if (max_newton > 0 && (!(n_occ > 0.0) || !(n_occ < N) || !(tol > 0.0)))
+        return fail(c, SP2_EINVAL, "need 0 < n_occ < N and tol > 0");
+    if (max_newton == 0 && !std::isfinite(*mu)) return fail(c, SP2_EINVAL, "a fixed mu must be finite");
+    HIPCHK(c, hipSetDevice(c->device));
+    sp2_status s;
+    const size_t n2 = (size_t)N * N;
+    // the Gershgorin pass writes a (min, max) pair per 4 rows into c->part
+    size_t pbytes = c->partcap * sizeof(double);
+    if ((s = grow(c, (void**)&c->part, &pbytes, std::max<size_t>((size_t)(N + 3) / 4 * 2, 1024) * sizeof(double))) !=
+        SP2_OK)
+        return s;
+    c->partcap = pbytes / sizeof(double);
+    hipStream_t st = c->stream;
+    // validity of H and its Gershgorin interval
+    int ns = 0, nchk = 0;
+    HIPCHK(c, launch_check_h(H, N, c->chk, &nchk, st));
+    HIPCHK(c, launch_gershgorin(H, N, c->part, &ns, st));
+    HIPCHK(c, launch_bounds(c->part, ns, c->chk, nchk, c->st, st));
+    HIPCHK(c, hipMemcpyAsync(c->st_host, c->st, sizeof(State), hipMemcpyDeviceToHost, st));
+    HIPCHK(c, hipStreamSynchronize(st));
+    if (c->st_host->done == 5) return fail(c, SP2_EINVAL, "H is not finite and symmetric");
+    const double e_lo = c->st_host->eps_min, e_hi = c->st_host->eps_max;
+    const double beta = 1.0 / kT;
+    // the root stays bracketed: below e_lo - 40 kT every Fermi factor is under
+    // e^-40 (Tr < n_occ), above e_hi + 40 kT over 1 - e^-40 (Tr > n_occ)
+    double lo = e_lo - 40.0 * kT, hi = e_hi + 40.0 * kT;
+    double m = max_newton == 0 ? *mu : (std::isfinite(*mu) && *mu > lo && *mu < hi) ? *mu : 0.5 * (e_lo + e_hi);
+    // X_0 has its spectrum in [0, 1] (and A in [1/2, 1]) when
+    // beta |e - mu| <= 2^(n+1) over the Gershgorin interval
+    const double reach = std::ldexp(1.0, n_steps + 1) / beta;
+    if (!(std::max(e_hi - m, m - e_lo) <= reach) || (max_newton > 0 && !(hi - lo <= reach)))
+        return fail(c, SP2_EINVAL, "beta |e - mu| can exceed 2^(n_steps + 1): more steps needed");
+    const int evals = max_newton == 0 ? 1 : max_newton;
+    auto delta_of = [&](double at) { return beta * std::max(e_hi - at, at - e_lo) / std::ldexp(1.0, n_steps + 2); };
+    // The expansion, where it costs less than the recursion's products.  Each
+    // multiple and each Clenshaw step is a product and a pass over the stored
+    // matrices, together 2 products up to N = 1024 (10 + 10 us at N = 500) and
+    // 1.6 above (174 + 109 and 61 us at 2048).  A cold mu solve takes 4 passes
+    // or more, one from a nearby mu 2 (kT = 0.25 eV, N = 500, where m = 2400:
+    // cold 5.9 ms against 6.8, two passes or a fixed mu stay on the recursion).
+    bool expand = false;
+    ChebBasis B;
+    std::vector<double> x, coef, W;
+    const double ctr = 0.5 * (e_lo + e_hi), w = std::max(0.5 * (e_hi - e_lo) * (1.0 + 1e-12), 1e-300);
+    if (max_newton == 0 || tol >= kFermiTolPerN * N) {
+        // mu at the centre needs the most coefficients: the poles lie nearest there
+        const int mc = cheb_expand([&](double t) { return fermi_occupation(ctr + w * t, ctr, beta, n_steps); },
+                                   kFermiCoefTol, cheb_guess(kT, w, kFermiCoefTol), &x, &coef);
+        if (mc > 0) {
+            const bool moments = max_newton > 0 || entropy;
+            const int S = cheb_stored(N, mc), Q = cheb_multiples(mc, S);
+            const int passes = std::min(evals, max_newton > 0 && m == *mu ? 2 : 4);
+            const double step = N <= 1024 ? 2.0 : 1.6, cost = (S - 1) + (moments ? 2 : 1) * Q * step;
+            const double entropy_cost = entropy ? (S - 1) + Q * step : 0.0;   // its own moments beside the recursion
+            if (cost <= (double)passes * fermi_products(delta_of(m), n_steps) + entropy_cost) {
+                s = cheb_moments(c, N, H, ctr, w, mc, S, moments, &B);
+                if (s != SP2_OK && s != SP2_ENOMEM) return s;
+                expand = s == SP2_OK;   // no room for the stored matrices: the recursion
+            }
+        }
+    }
+    double *part = nullptr, *res = nullptr;
+    if (expand) {
+        if (!B.mom.empty()) cheb_weights(B.mom, (int)x.size(), W);
+    } else {
+        size_t nb = c->nocap;
+        if ((s = grow(c, (void**)&c->nobuf, &nb, (5 * n2 + 2 * kFermiBlocks + 8) * sizeof(double))) != SP2_OK) return s;
+        c->nocap = nb;
+        part = c->nobuf + 5 * n2;
+        res = part + 2 * kFermiBlocks;
+    }
+    // D_out at the chemical potential `at`; X: the recursion's result there
+    auto finish = [&](double at, const double* X) -> sp2_status {
+        if (expand) {
+            std::vector<double> f(x.size());
+            for (size_t j = 0; j < x.size(); ++j) f[j] = fermi_occupation(ctr + w * x[j], at, beta, n_steps);
+            cheb_coefficients(f, coef);
+            sp2_status e = cheb_evaluate(c, N, B, coef, D_out);
+            if (e != SP2_OK) return e;
+        } else {
+            HIPCHK(c, hipMemcpyAsync(D_out, X, n2 * sizeof(double), hipMemcpyDeviceToDevice, st));
+        }
+        HIPCHK(c, hipStreamSynchronize(st));
+        if (max_newton > 0) *mu = at;
+        if (entropy && expand) {
+            double S = 0.0;
+            for (size_t j = 0; j < x.size(); ++j) S += W[j] * fermi_entropy_term(beta * (ctr + w * x[j] - at));
+            if (!std::isfinite(S)) return fail(c, SP2_EDEVICE, "non-finite entropy");
+            *entropy = 2.0 * S;
+        }
+        return SP2_OK;
+    };
+    // Tr f and Tr f^2 at the chemical potential `at` from the moments
+    auto traces = [&](double at, double* t, double* fr) {
+        *t = *fr = 0.0;
+        for (size_t j = 0; j < x.size(); ++j) {
+            const double f = fermi_occupation(ctr + w * x[j], at, beta, n_steps);
+            *t += W[j] * f;
+            *fr += W[j] * f * f;
+        }
+    };
+    for (int it = 0; it < evals; ++it) {
+        double* X = nullptr;
+        const double delta0 = delta_of(m);
+        double t = 0.0, fr = 0.0;
+        if (!expand && (s = fermi_pass(c, N, H, m, beta, n_steps, delta0, c->nobuf, &X)) != SP2_OK) return s;
+        nprod += fermi_products(delta0, n_steps);
+        if (newton_iterations) *newton_iterations = it + 1;
+        if (products) *products = nprod;
+        if (max_newton == 0) {
+            if ((s = finish(m, X)) != SP2_OK) return s;
+            break;
+        }
+        if (expand) {
+            traces(m, &t, &fr);
+        } else {
+            HIPCHK(c, launch_trace_fro(X, N, part, st));
+            HIPCHK(c, launch_sum_pairs(part, kFermiBlocks, res, st));
+            HIPCHK(c, hipMemcpyAsync(c->scal_host, res, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
+            HIPCHK(c, hipStreamSynchronize(st));
+            t = c->scal_host[0];
+            fr = c->scal_host[1];
+        }
+        if (!std::isfinite(t) || !std::isfinite(fr)) return fail(c, SP2_EDEVICE, "non-finite Fermi-operator trace");
+        if (std::fabs(t - n_occ) < tol || it + 1 == evals) {
+            if (expand && std::fabs(t - n_occ) < tol && t > fr) {
+                // another step costs no product here: kept if it comes closer
+                const double nm = m - (t - n_occ) / (beta * (t - fr));
+                double t2, fr2;
+                traces(nm, &t2, &fr2);
+                if (nm > lo && nm < hi && std::fabs(t2 - n_occ) < std::fabs(t - n_occ)) m = nm;
+            }
+            if ((s = finish(m, X)) != SP2_OK) return s;
+            if (std::fabs(t - n_occ) < tol) break;
+            return fail(c, SP2_ENOCONV, "Newton on mu did not reach Tr D = n_occ");
+        }
+        // Newton with dTr X / dmu ~ beta Tr[X (I - X)] (the Fermi function's
+        // derivative); a step out of the bracket bisects it instead
+        if (t < n_occ) lo = m;
+        else hi = m;
+        const double d = beta * (t - fr);
+        const double nm = d > 0.0 ? m - (t - n_occ) / d : NAN;
+        const double next = (nm > lo && nm < hi) ? nm : 0.5 * (lo + hi);
+        if (next == m) {   // X_0 cannot resolve a finer mu
+            if ((s = finish(m, X)) != SP2_OK) return s;
+            return fail(c, SP2_ENOCONV, "tol is below the resolution of Tr D in mu");
+        }
+        m = next;
+    }
+    if (entropy && !expand) return sp2_fermi_entropy(c, N, H, m, kT, entropy, nullptr);
+    return SP2_OK;
+}
+
+extern "C" sp2_status sp2_fermi_density_matrix(sp2_ctx* c, int N, const double* H, double n_occ, double kT,
+                                                int n_steps, int max_newton, double tol, double* mu,
+                                                double* D_out, int* newton_iterations, long long* products) {
+    CTX_ENTER(c);
+    if (!c) return SP2_EINVAL;
+    return fermi_solve(c, N, H, n_occ, kT, n_steps, max_newton, tol, mu, D_out, newton_iterations, products, nullptr);
+}
+
 // Electronic entropy S / k_B = -2 sum_i [f_i ln f_i + (1 - f_i) ln(1 - f_i)]
 // (Eq. Entropy) of the Fermi occupations f_i = (exp(beta (e_i - mu)) + 1)^(-1)
 // of H's eigenvalues, as Tr s(beta (H - mu I)) expanded in Chebyshev
@@ -1287,12 +1446,6 @@ static int cheb_guess(double kT, double w, double tol) {
 // kT = 0.5 eV on the sp lattices: 64 products instead of the 545 of one per
 // pair of moments, N = 500 56 -> 2.6 ms, 2048 140 -> 18, 4096 757 -> 105.
 constexpr double kEntropyCoefTol = 1e-13;
-
-static double fermi_entropy_term(double x) {   // s(x) per state, spin not counted
-    const double a = std::fabs(x);
-    const double e = std::exp(-a);
-    return std::log1p(e) + a * e / (1.0 + e);
-}
 
 extern "C" sp2_status sp2_fermi_entropy(sp2_ctx* c, int N, const double* H, double mu, double kT, double* S_out,
                                          int* moments) {
@@ -1325,7 +1478,7 @@ extern "C" sp2_status sp2_fermi_entropy(sp2_ctx* c, int N, const double* H, doub
     if (m == 0)
         return fail(c, SP2_EINVAL, "kT too small against the spectral width for the entropy's Chebyshev expansion");
     ChebBasis b;
-    if ((s = cheb_moments(c, N, H, ctr, w, m, &b)) != SP2_OK) return s;
+    if ((s = cheb_moments(c, N, H, ctr, w, m, 1, true, &b)) != SP2_OK) return s;
     double S = 0.5 * a[0] * N;
     for (int k = 1; k < m; ++k) S += a[k] * b.mom[k];
     if (!std::isfinite(S)) return fail(c, SP2_EDEVICE, "non-finite entropy");
@@ -1365,11 +1518,10 @@ extern "C" sp2_status sp2_fermi_density_matrix_nonorth(sp2_ctx* c, int N, const 
     HIPCHK(c, hipMemcpyAsync(Zf, Zm, n2 * sizeof(double), hipMemcpyDeviceToDevice, st));
     if ((s = prod(c, N, H, Zf, F1, false)) != SP2_OK) return s;
     if ((s = prod(c, N, F1, Zf, Hp, true)) != SP2_OK) return s;
-    if ((s = sp2_fermi_density_matrix(c, N, Hp, n_occ, kT, n_steps, max_newton, tol, mu, Dp, newton_iterations,
-                                      nullptr)) != SP2_OK)
+    if ((s = fermi_solve(c, N, Hp, n_occ, kT, n_steps, max_newton, tol, mu, Dp, newton_iterations, nullptr,
+                         entropy_out)) != SP2_OK)
         return s;
-    if (entropy_out && (s = sp2_fermi_entropy(c, N, Hp, *mu, kT, entropy_out, nullptr)) != SP2_OK) return s;
-    double* tmp = c->nobuf;   // at least 3 N x N after the calls above
+    double* tmp = c->nobuf;   // at least one N x N matrix after the call above
     // rho = Z D_perp Z^T
     if ((s = prod(c, N, Dp, Zf, tmp, false)) != SP2_OK) return s;
     if ((s = prod(c, N, tmp, Zf, D_out, true)) != SP2_OK) return s;
@@ -1750,12 +1902,10 @@ static sp2_status md_evaluate(xlbomd* m, int* iters, bool with_forces = true, fl
         // finite electronic temperature: the Fermi operator at the canonical mu
         // (from the previous step's), its entropy, charges and forces
         int passes = 0;
-        if ((s = sp2_fermi_density_matrix(c, N, m->H, (double)m->n_occ, m->o.kT, m->o.fermi_steps,
-                                          m->o.fermi_max_newton, m->o.fermi_tol, &m->mu, m->D, &passes, nullptr)) !=
-            SP2_OK)
-            return s;
         double S = 0.0;
-        if ((s = sp2_fermi_entropy(c, N, m->H, m->mu, m->o.kT, &S, nullptr)) != SP2_OK) return s;
+        if ((s = fermi_solve(c, N, m->H, (double)m->n_occ, m->o.kT, m->o.fermi_steps, m->o.fermi_max_newton,
+                             m->o.fermi_tol, &m->mu, m->D, &passes, nullptr, &S)) != SP2_OK)
+            return s;
         m->ts = m->o.kT * S;
         m->dm_count += 1;
         if (iters) *iters = passes;

@@ -9,6 +9,7 @@
 // of its sums.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "cheb_internal.h"
 #include "sp2_internal.h"
@@ -44,45 +45,88 @@ __global__ __launch_bounds__(256) void k_cheb_traces(const double* __restrict__ 
 
 // Workgroups stride over the 32 x 32 tiles of the upper triangle (off-diagonal
 // ones count twice: half the reads of a pass over the whole matrices); each
-// thread keeps the s sums in registers.  HBM (or last-level cache) bound:
-// (s + 1) N^2 / 2 doubles read.  SM: s rounded up to 8, 16 or 32.
-template <int SM>
-__global__ __launch_bounds__(256) void k_cheb_dots(const double* __restrict__ G, const double* __restrict__ T, int N,
-                                                   int s, double* __restrict__ part) {
+// thread keeps the sums of NG multiples in registers, so two multiples share
+// one read of the S - 1 matrices.  HBM (or last-level cache) bound:
+// (S - 1 + NG) N^2 / 2 doubles read.  S is a template argument: with a run-time
+// bound on j the loads waited for one another (S = 32, N = 500: 46 us for one
+// multiple, 24 for two now; N = 2048: 204, and 122 for two, 4.7 TB/s).
+template <int S, int NG>
+__global__ __launch_bounds__(256) void k_cheb_dots(const double* __restrict__ G0, const double* __restrict__ G1,
+                                                   const double* __restrict__ T, int N, double* __restrict__ part) {
     const int nt = (N + CT - 1) / CT, ntiles = nt * (nt + 1) / 2;
     const size_t n2 = (size_t)N * N;
     const int c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
-    double acc[SM];
+    double acc[NG][S];
 #pragma unroll
-    for (int j = 0; j < SM; ++j) acc[j] = 0.0;
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+        for (int j = 0; j < S; ++j) acc[g][j] = 0.0;
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
         int bi, bj;
         order_tile(t, nt, 0, bi, bj);
         const double wgt = bi == bj ? 1.0 : 2.0;
         const int gj = bj * CT + c;
-#pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int gi = bi * CT + r0 + 8 * q;
             if (gi >= N || gj >= N) continue;
             const size_t e = (size_t)gi * N + gj;
-            const double g = wgt * G[e];
-            if (gi == gj) acc[0] += g;
+            double v[S], g[NG];
 #pragma unroll
-            for (int j = 1; j < SM; ++j)
-                if (j < s) acc[j] += g * T[(size_t)(j - 1) * n2 + e];
+            for (int j = 1; j < S; ++j) v[j] = T[(size_t)(j - 1) * n2 + e];
+            g[0] = wgt * G0[e];
+            if (NG > 1) g[NG - 1] = wgt * G1[e];
+#pragma unroll
+            for (int k = 0; k < NG; ++k) {
+                if (gi == gj) acc[k][0] += g[k];
+#pragma unroll
+                for (int j = 1; j < S; ++j) acc[k][j] += g[k] * v[j];
+            }
         }
     }
-    __shared__ double sw[4][SM];
+    __shared__ double sw[4][NG * S];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
 #pragma unroll
-    for (int j = 0; j < SM; ++j) {
-        const double v = wsum_c(acc[j]);
-        if (lane == 0) sw[w][j] = v;
-    }
+    for (int k = 0; k < NG; ++k)
+#pragma unroll
+        for (int j = 0; j < S; ++j) {
+            const double v = wsum_c(acc[k][j]);
+            if (lane == 0) sw[w][k * S + j] = v;
+        }
     __syncthreads();
-    if (threadIdx.x < s)
+    if (threadIdx.x < NG * S)
         part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] =
             (sw[0][threadIdx.x] + sw[1][threadIdx.x]) + (sw[2][threadIdx.x] + sw[3][threadIdx.x]);
+}
+
+// HBM (or last-level cache) bound: (S + 1) N^2 / 2 doubles read and written
+// (S = 32, N = 2048: 109 us, 5.1 TB/s).
+template <int S>
+__global__ __launch_bounds__(256) void k_cheb_combine(const double* __restrict__ T, int N, ChebCoef b,
+                                                      const double* V, double* C, int full) {
+    const int nt = (N + CT - 1) / CT;
+    const size_t n2 = (size_t)N * N;
+    const int t = blockIdx.x, c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    int bi, bj;
+    if (full) {
+        bi = t / nt;
+        bj = t % nt;
+    } else {
+        order_tile(t, nt, 0, bi, bj);
+    }
+    const int gj = bj * CT + c;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int gi = bi * CT + r0 + 8 * q;
+        if (gi >= N || gj >= N) continue;
+        const size_t e = (size_t)gi * N + gj;
+        double x[S], v = gi == gj ? b.b[0] : 0.0;
+#pragma unroll
+        for (int j = 1; j < S; ++j) x[j] = T[(size_t)(j - 1) * n2 + e];
+        if (V) v -= V[e];
+#pragma unroll
+        for (int j = 1; j < S; ++j) v += b.b[j] * x[j];
+        C[e] = v;
+    }
 }
 
 __global__ __launch_bounds__(256) void k_cheb_sums(const double* __restrict__ part, int nblk,
@@ -149,6 +193,39 @@ void cheb_coefficients(const std::vector<double>& g, std::vector<double>& a) {
     }
 }
 
+// Re sum_k (c_k e^(i pi k / 2M)) e^(2 pi i k j / 2M), c_0 halved: the conjugate of
+// an FFT of the conjugates, padded to 2 M.
+void cheb_weights(const std::vector<double>& mu, int M, std::vector<double>& W) {
+    std::vector<double> re(2 * (size_t)M, 0.0), im(2 * (size_t)M, 0.0);
+    for (size_t k = 0; k < mu.size() && k < (size_t)M; ++k) {
+        const double t = M_PI * (double)k / (2.0 * M), c = (k == 0 ? 0.5 : 1.0) * mu[k];
+        re[k] = c * std::cos(t);
+        im[k] = -c * std::sin(t);
+    }
+    fft(re, im);
+    W.resize(M);
+    for (int j = 0; j < M; ++j) W[j] = re[j] * 2.0 / M;
+}
+
+// From the highest block down, T_(qs+j) = 2 T_qs T_j - T_(qs-j).
+void cheb_blocks(const std::vector<double>& c, int s, int Q, std::vector<std::vector<double>>& b) {
+    std::vector<double> a(c);
+    a.resize((size_t)(Q + 1) * s, 0.0);
+    b.assign(Q + 1, std::vector<double>(s, 0.0));
+    for (int q = Q; q >= 0; --q) {
+        b[q][0] = a[(size_t)q * s];
+        for (int j = 1; j < s; ++j) {
+            const double v = a[(size_t)q * s + j];
+            if (q == 0) {
+                b[0][j] = v;
+            } else {
+                b[q][j] = 2.0 * v;
+                a[(size_t)q * s - j] -= v;
+            }
+        }
+    }
+}
+
 static int grid_elem(int N) {
     const size_t g = ((size_t)N * N + 255) / 256;
     return (int)(g < 4096 ? g : 4096);
@@ -166,13 +243,44 @@ int cheb_dot_blocks(int N) {
     const int nt = (N + CT - 1) / CT;
     return std::min(tri_tiles(nt), kChebBlocks);
 }
-hipError_t launch_cheb_dots(const double* G, const double* T, int N, int s, double* part, hipStream_t st) {
-    if (s < 1 || s > kChebMaxS) return hipErrorInvalidValue;
-    const int nblk = cheb_dot_blocks(N);
-    if (s <= 8) hipLaunchKernelGGL(k_cheb_dots<8>, dim3(nblk), dim3(256), 0, st, G, T, N, s, part);
-    else if (s <= 16) hipLaunchKernelGGL(k_cheb_dots<16>, dim3(nblk), dim3(256), 0, st, G, T, N, s, part);
-    else hipLaunchKernelGGL(k_cheb_dots<32>, dim3(nblk), dim3(256), 0, st, G, T, N, s, part);
-    return hipGetLastError();
+// f with the template argument S = s for the counts that cheb_round makes.
+template <typename F>
+static hipError_t with_stored(int s, F f) {
+    switch (s) {
+        case 1: return f(std::integral_constant<int, 1>{});
+        case 2: return f(std::integral_constant<int, 2>{});
+        case 4: return f(std::integral_constant<int, 4>{});
+        case 8: return f(std::integral_constant<int, 8>{});
+        case 12: return f(std::integral_constant<int, 12>{});
+        case 16: return f(std::integral_constant<int, 16>{});
+        case 20: return f(std::integral_constant<int, 20>{});
+        case 24: return f(std::integral_constant<int, 24>{});
+        case 28: return f(std::integral_constant<int, 28>{});
+        case 32: return f(std::integral_constant<int, 32>{});
+        default: return hipErrorInvalidValue;
+    }
+}
+int cheb_round(int s) { return s <= 1 ? 1 : s <= 3 ? 2 : s <= 7 ? 4 : std::min(s / 4 * 4, kChebMaxS); }
+
+hipError_t launch_cheb_dots(const double* G0, const double* G1, const double* T, int N, int s, double* part,
+                            hipStream_t st) {
+    const dim3 grid(cheb_dot_blocks(N));
+    return with_stored(s, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        if (G1) hipLaunchKernelGGL((k_cheb_dots<S, 2>), grid, dim3(256), 0, st, G0, G1, T, N, part);
+        else hipLaunchKernelGGL((k_cheb_dots<S, 1>), grid, dim3(256), 0, st, G0, G1, T, N, part);
+        return hipGetLastError();
+    });
+}
+hipError_t launch_cheb_combine(const double* T, int N, int s, const ChebCoef& b, const double* V, double* C, bool full,
+                               hipStream_t st) {
+    const int nt = (N + CT - 1) / CT, f = full ? 1 : 0;
+    const dim3 grid(full ? nt * nt : tri_tiles(nt));
+    return with_stored(s, [&](auto sc) {
+        constexpr int S = decltype(sc)::value;
+        hipLaunchKernelGGL(k_cheb_combine<S>, grid, dim3(256), 0, st, T, N, b, V, C, f);
+        return hipGetLastError();
+    });
 }
 hipError_t launch_cheb_sums(const double* part, int nblk, int nslots, double* out, hipStream_t st) {
     if (nslots < 1) return hipSuccess;

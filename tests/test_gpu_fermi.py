@@ -353,3 +353,40 @@ def test_entropy_moments_at_ragged_sizes(ctx, n, kT):
     S, m = ctx.sp2_fermi_entropy(to_dev(H), mu, kT)
     say(f"  S {S:.12f} (eigenvalues {S_ref:.12f}), {m} coefficients")
     assert abs(S - S_ref) < 1e-10 * max(S_ref, 1.0)
+
+
+@pytest.mark.parametrize("n,kT,steps,max_newton", [(1, 0.5, 12, 0), (33, 30.0, 6, 50), (101, 6.0, 8, 0),
+                                                   (101, 6.0, 8, 50), (130, 3.0, 3, 50), (530, 12.0, 16, 50),
+                                                   (1056, 9.0, 16, 50), (530, 1.0, 16, 50)])
+def test_expansion_is_the_recursions_function(ctx, n, kT, steps, max_newton):
+    """D on random symmetric matrices against the recursion's own function of
+    the eigenvalues, X_n(e) = (1 - t)^(2^n) / ((1 - t)^(2^n) + (1 + t)^(2^n)) at the
+    mu returned (few steps: far from the Fermi function), at a fixed and at
+    the canonical mu, for coefficient counts from a handful to those where the
+    recursion is used instead.  Bars: the recursion's rounding floor, 1e-10, and
+    the requested trace.  A canonical solve whose bracket, the Gershgorin
+    interval and 40 kT on each side, is wider than 2^(n + 1) kT is refused."""
+    import paper_1203_6836_amd as p
+    say(f"case fermi expansion N={n} kT={kT} steps={steps} newton={max_newton}")
+    rng = np.random.default_rng(200 + n)
+    A = rng.standard_normal((n, n))
+    H = 0.5 * (A + A.T)
+    e, v = np.linalg.eigh(H)
+    n_occ, tol = max(0.37 * n, 0.3), 1e-8
+    lo, hi = osp2.gershgorin(H)
+    if max_newton and hi - lo + 80.0 * kT > 2.0 ** (steps + 1) * kT:
+        with pytest.raises(p.Sp2Error) as ei:
+            ctx.sp2_fermi_density_matrix(to_dev(H), n_occ, kT, steps, max_newton=max_newton, tol=tol)
+        assert ei.value.status == p.SP2_EINVAL
+        return
+    D, mu, passes = ctx.sp2_fermi_density_matrix(to_dev(H), n_occ, kT, steps, mu=0.1 if max_newton == 0 else None,
+                                                 max_newton=max_newton, tol=tol)
+    D = D.cpu().numpy()
+    t = (e - mu) / kT / 2.0 ** (steps + 1)
+    f = 1.0 / (1.0 + np.exp(2.0 ** (steps + 1) * np.arctanh(t)))
+    err = float(np.abs(D - (v * f) @ v.T).max())
+    say(f"  mu {mu:.10f}, passes {passes}, recursion products {ctx.last_fermi_products}, max|dD| {err:.1e}")
+    assert np.array_equal(D, D.T) and err < 1e-10
+    assert passes * 2 * steps <= ctx.last_fermi_products <= passes * 10 * steps
+    if max_newton:
+        assert abs(np.trace(D) - n_occ) < 1.01 * tol
