@@ -932,16 +932,21 @@ extern "C" sp2_status sp2_tune_load(sp2_ctx* c, const char* path) {
 // when A B is symmetric (A and B symmetric and commuting, or a congruence
 // M^T B M): then only the upper tiles are formed and mirrored, and C is
 // exactly symmetric.  The K split of sparse last waves uses the context's
-// FP64 chunk buffer.
+// FP64 chunk buffer.  prod_keep: rounded alike by every product kernel.
 static sp2_status prod(sp2_ctx* c, int N, const double* A, const double* B, double* C, bool sym,
-                       double alpha = 1.0, double gamma = 0.0, double beta = 0.0, const double* Cin = nullptr) {
+                       double alpha = 1.0, double gamma = 0.0, double beta = 0.0, const double* Cin = nullptr,
+                       bool keep_split = false) {
     double* chunk = nullptr;
     size_t chunk_bytes = 0;
     sp2_status s = f64_tail_buffer(c, 0, -1, &chunk, &chunk_bytes);
     if (s != SP2_OK) return s;
-    GemmTN g{A, B, Cin, C, N, alpha, beta, gamma};
+    GemmTN g{A, B, Cin, C, N, alpha, beta, gamma, keep_split};
     HIPCHK(c, launch_gemm_tn(g, sym, 8, chunk, chunk_bytes, c->stream));
     return SP2_OK;
+}
+
+static sp2_status prod_keep(sp2_ctx* c, int N, const double* A, const double* B, double* C, bool sym) {
+    return prod(c, N, A, B, C, sym, 1.0, 0.0, 0.0, nullptr, true);
 }
 
 constexpr int kNsMaxIter = 40;
@@ -967,14 +972,15 @@ static sp2_status loewdin_factor(sp2_ctx* c, int N, const double* S, double** Zo
     hipStream_t st = c->stream;
     HIPCHK(c, launch_zero_word(mx, st));
     HIPCHK(c, launch_row_abs_max(S, N, mx, st));
-    HIPCHK(c, launch_ns_init(S, N, mx, Y, Zm, st));
+    HIPCHK(c, launch_ns_init(S, N, mx, Y, st));
     const double tol = 1e-11 * N;   // ||Z_k Y_k - I||_F: about 1e-11 per element
     double prev = 1e300;
     int it = 0;
     bool converged = false;
     for (; it < kNsMaxIter; ++it) {
-        if ((s = prod(c, N, Zm, Y, T, true)) != SP2_OK) return s;        // T = Z_k Y_k (polynomials in S)
-        HIPCHK(c, launch_ns_step(T, N, part, st));                      // residual; T = (3 I - T) / 2
+        // T = Z_k Y_k (polynomials in S); Z_0 = I needs no product
+        if (it > 0 && (s = prod_keep(c, N, Zm, Y, T, true)) != SP2_OK) return s;
+        HIPCHK(c, launch_ns_step(it > 0 ? T : Y, it == 0, T, N, part, st));   // residual; T = (3 I - T) / 2
         HIPCHK(c, launch_sum_sqrt(part, kNsBlocks, res, st));
         HIPCHK(c, hipMemcpyAsync(c->scal_host, res, sizeof(double), hipMemcpyDeviceToHost, st));
         HIPCHK(c, hipStreamSynchronize(st));
@@ -982,13 +988,31 @@ static sp2_status loewdin_factor(sp2_ctx* c, int N, const double* S, double** Zo
         if (!(r == r)) return fail(c, SP2_EINVAL, "overlap matrix gives a non-finite inverse factor");
         if (r < tol || (it >= 4 && r >= prev && r < 1e-6 * N)) {   // converged, or at its rounding floor
             converged = true;
+            if (it == 0) HIPCHK(c, launch_identity(Zm, N, st));
             break;
         }
         prev = r;
-        if ((s = prod(c, N, Y, T, W, true)) != SP2_OK) return s;         // Y_{k+1} = Y_k T_k
-        std::swap(Y, W);
-        if ((s = prod(c, N, T, Zm, W, true)) != SP2_OK) return s;        // Z_{k+1} = T_k Z_k
-        std::swap(Zm, W);
+        // R_(k+1) = 3/4 R_k^2 + 1/4 R_k^3 for the residual matrix: once that is
+        // surely below tol, Z_(k+1) is the factor (and the next iteration the
+        // last), and neither Y_(k+1) nor its residual is needed.  Within 10
+        // iterations S / c has no eigenvalue below 0.01, so the residual's
+        // rounding floor lies far under tol (else it has to be looked at)
+        const bool last = it < 10 && 0.75 * r * r + 0.25 * r * r * r < 0.5 * tol;
+        if (!last) {
+            if ((s = prod_keep(c, N, Y, T, W, true)) != SP2_OK) return s;     // Y_{k+1} = Y_k T_k
+            std::swap(Y, W);
+        }
+        if (it == 0) {
+            std::swap(Zm, T);                                            // Z_1 = T_0 I
+        } else {
+            if ((s = prod_keep(c, N, T, Zm, W, true)) != SP2_OK) return s;    // Z_{k+1} = T_k Z_k
+            std::swap(Zm, W);
+        }
+        if (last) {
+            ++it;
+            converged = true;
+            break;
+        }
     }
     *iters = it + 1;
     if (!converged) return fail(c, SP2_ENOCONV, "inverse factor of S did not converge (S not positive definite?)");
@@ -1025,12 +1049,12 @@ extern "C" sp2_status sp2_density_matrix_nonorth(sp2_ctx* c, int N, const double
     // as a symmetric product (exactly symmetric)
     double* Hp = Y;
     double* Dp = T;
-    if ((s = prod(c, N, H, Zm, W, false)) != SP2_OK) return s;
-    if ((s = prod(c, N, W, Zm, Hp, true)) != SP2_OK) return s;
+    if ((s = prod_keep(c, N, H, Zm, W, false)) != SP2_OK) return s;
+    if ((s = prod_keep(c, N, W, Zm, Hp, true)) != SP2_OK) return s;
     // rho_perp = theta(mu0 I - H_perp) by SP2, then rho = Z rho_perp Z^T the same way
     if ((s = sp2_solve(c, N, Hp, n_occ, o, Dp, stats)) != SP2_OK) return s;
-    if ((s = prod(c, N, Dp, Zm, W, false)) != SP2_OK) return s;
-    if ((s = prod(c, N, W, Zm, D_out, true)) != SP2_OK) return s;
+    if ((s = prod_keep(c, N, Dp, Zm, W, false)) != SP2_OK) return s;
+    if ((s = prod_keep(c, N, W, Zm, D_out, true)) != SP2_OK) return s;
     HIPCHK(c, hipStreamSynchronize(st));
     return SP2_OK;
 }

@@ -17,6 +17,7 @@
 // fill at most half of the slots).  N need not be a multiple of 128: with
 // EDGE the loads outside N read zeros and the stores outside N are skipped.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include "gemm_internal.h"
@@ -29,6 +30,7 @@ namespace {
 
 constexpr int TB = 128;   // tile
 constexpr int TK = 16;    // k per stage
+constexpr int kSmallMaxSplit = 10;   // chunks (waves) of a tile of the small kernel
 
 typedef double d4g __attribute__((ext_vector_type(4)));
 
@@ -215,25 +217,32 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tn_tail(GemmTN g, int tile_grou
     tn_tile<SYM, EDGE>(g, bi, bj, 2, 0, -1, chunk + (size_t)p * nsplit * kF64Chunk, nsplit);
 }
 
+// The K split of a product of T 128 x 128 tiles and nk stages of 16: the
+// sparse last wave of a large product (*r tiles), or every tile of a product
+// whose tiles fill at most half of the workgroup slots (two per CU), into
+// about sqrt(1.4 nk) <= 16 chunks; 1: no split.
+int tn_split(int T, int nk, int* r) {
+    const int slots = 2 * device_cus();
+    *r = 0;
+    if (nk >= 256) {
+        *r = T % slots;
+        if (*r > 0 && 2 * *r <= slots) return std::min(16, slots / *r);
+    } else if (2 * T <= slots) {
+        *r = T;
+        return std::min({16, slots / T, nk, (int)std::lround(std::sqrt(1.4 * nk))});
+    }
+    return 1;
+}
+
 template <bool SYM, bool EDGE>
 hipError_t launch_tn(const GemmTN& g, int tile_group, double* chunk, size_t chunk_bytes, hipStream_t s) {
     const int nt = (g.N + TB - 1) / TB;
     const int T = SYM ? nt * (nt + 1) / 2 : nt * nt;
     const int nk = (g.N + TK - 1) / TK;
-    // Split as the SP2 product does: the sparse last wave of a large
-    // product, or every tile of a product whose tiles fill at most half of
-    // the workgroup slots (two per CU), into about sqrt(1.4 nk) <= 16 chunks.
     int t_full = T, nsplit = 1;
     if (chunk) {
-        const int slots = 2 * device_cus();
         int r = 0;
-        if (nk >= 256) {
-            r = T % slots;
-            if (r > 0 && 2 * r <= slots) nsplit = std::min(16, slots / r);
-        } else if (2 * T <= slots) {
-            r = T;
-            nsplit = std::min({16, slots / T, nk, (int)std::lround(std::sqrt(1.4 * nk))});
-        }
+        nsplit = tn_split(T, nk, &r);
         if (nsplit >= 2 && (size_t)r * nsplit * kF64Chunk * sizeof(double) <= chunk_bytes) t_full = T - r;
         else nsplit = 1;
     }
@@ -245,49 +254,70 @@ hipError_t launch_tn(const GemmTN& g, int tile_group, double* chunk, size_t chun
     return hipGetLastError();
 }
 
-// Small products: one workgroup of NW waves per 32 x 32 tile, K split over its
-// waves, partial tiles added in LDS in wave order (no second launch that reads
-// chunks back).  Chosen as for the SP2 product (small_f64_tile); per symmetric
-// product N = 500 51 -> 11 us, 1020 82 -> 37, 2000 224 -> 164, 3072 779 -> 527.  With sym a tile on the diagonal writes its upper
-// triangle and mirrors it, as above.
-template <bool SYM, bool EDGE, bool VEC, int NW>
-__global__ __launch_bounds__(64 * NW) void k_gemm_tn_small(GemmTN g) {
-    constexpr int PER = kSmallTile * kSmallTile / (64 * NW);
-    __shared__ double red[NW][kSmallTile][kSmallTile + 1];
-    const int N = g.N, nt = (N + kSmallTile - 1) / kSmallTile;
-    int bi, bj;
-    tile_at<SYM>(xcd_deal(blockIdx.x, gridDim.x), nt, 16, bi, bj);
-    const int i0 = bi * kSmallTile, j0 = bj * kSmallTile;
-    const int w = threadIdx.x >> 6, nk = (N + 3) / 4;
+// Small products (chosen as for the SP2 product, small_f64_tile): 32 x 32 tiles,
+// one wave per tile and K chunk, chunks added in order in LDS.  A workgroup has
+// tpw tiles of nsplit waves each; with sym a diagonal tile writes its upper
+// triangle and mirrors it, as above.  With 8 chunks up to N = 512 and 4 above,
+// per symmetric product N = 500 51 -> 11 us, 1020 82 -> 37, 2000 224 -> 164,
+// 3072 779 -> 527 (with the 128 x 128 kernel's chunks instead, 3 of them at N =
+// 2000, about 200: three waves share four SIMDs; packing 4 such tiles into a
+// workgroup of 12 waves was slower, 5.4 ms of products per solve against 4.1).
+template <bool SYM, bool EDGE, bool VEC>
+__global__ __launch_bounds__(640) void k_gemm_tn_small(GemmTN g, int nsplit, int tpw) {
+    extern __shared__ double red[];   // [tile][chunk][32][33]
+    constexpr int LS = kSmallTile * (kSmallTile + 1);
+    const int N = g.N, nt = (N + kSmallTile - 1) / kSmallTile, T = SYM ? nt * (nt + 1) / 2 : nt * nt;
+    const int nk = (N + TK - 1) / TK;
     const double* Cin = g.Cin;
     double* C = g.C;
-    double cin[PER];
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int e = threadIdx.x + 64 * NW * q, gi = i0 + (e >> 5), gj = j0 + (e & 31);
-        cin[q] = Cin && (!EDGE || (gi < N && gj < N)) && (!SYM || gi <= gj) ? Cin[(size_t)gi * N + gj] : 0.0;
+    auto coords = [&](int tile, int& i0, int& j0) {
+        int bi, bj;
+        tile_at<SYM>(tile, nt, 16, bi, bj);
+        i0 = bi * kSmallTile;
+        j0 = bj * kSmallTile;
+    };
+    const int first = xcd_deal(blockIdx.x, gridDim.x) * tpw;
+    const int w = threadIdx.x >> 6, tile = first + w / nsplit, ch = w % nsplit;
+    int i0, j0;
+    if (tile < T) {
+        coords(tile, i0, j0);
+        const int s0 = ch * nk / nsplit * (TK / 4), s1 = min((ch + 1) * nk / nsplit * (TK / 4), (N + 3) / 4);
+        d4s acc[2][2];
+        small_mma<EDGE, VEC>(g.A, g.B, N, N, i0, j0, s0, s1, acc);
+        small_store(red + (size_t)w * LS, acc);
     }
-    d4s acc[2][2];
-    small_mma<EDGE, VEC>(g.A, g.B, N, N, i0, j0, w * nk / NW, (w + 1) * nk / NW, acc);
-    small_store(red, acc);
     __syncthreads();
-#pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int e = threadIdx.x + 64 * NW * q, r = e >> 5, c = e & 31, gi = i0 + r, gj = j0 + c;
-        if ((EDGE && (gi >= N || gj >= N)) || (SYM && gi > gj)) continue;
-        double v = g.alpha * small_sum<NW>(red, r, c);
-        if (Cin) v += g.beta * cin[q];
-        if (gi == gj) v += g.gamma;
-        C[(size_t)gi * N + gj] = v;
-        if (SYM && gi != gj) C[(size_t)gj * N + gi] = v;
+    for (int t = 0; t < tpw && first + t < T; ++t) {
+        coords(first + t, i0, j0);
+        const double* part = red + (size_t)t * nsplit * LS;
+        for (int e = threadIdx.x; e < kSmallTile * kSmallTile; e += blockDim.x) {
+            const int r = e >> 5, c = e & 31, gi = i0 + r, gj = j0 + c;
+            if ((EDGE && (gi >= N || gj >= N)) || (SYM && gi > gj)) continue;
+            double acc = part[r * (kSmallTile + 1) + c];
+            for (int k = 1; k < nsplit; ++k) acc += part[k * LS + r * (kSmallTile + 1) + c];
+            double v = g.alpha * acc;
+            if (Cin) v += g.beta * Cin[(size_t)gi * N + gj];
+            if (gi == gj) v += g.gamma;
+            C[(size_t)gi * N + gj] = v;
+            if (SYM && gi != gj) C[(size_t)gj * N + gi] = v;
+        }
     }
 }
 
 template <bool SYM, bool EDGE, bool VEC>
-hipError_t launch_tn_small(const GemmTN& g, hipStream_t s) {
+hipError_t launch_tn_small(const GemmTN& g, int nsplit, hipStream_t s) {
     const int nt = (g.N + kSmallTile - 1) / kSmallTile, T = SYM ? tri_tiles(nt) : nt * nt;
-    if (g.N <= kSmallWideLd) hipLaunchKernelGGL((k_gemm_tn_small<SYM, EDGE, VEC, 8>), dim3(T), dim3(512), 0, s, g);
-    else hipLaunchKernelGGL((k_gemm_tn_small<SYM, EDGE, VEC, 4>), dim3(T), dim3(256), 0, s, g);
+    const int tpw = std::max(4 / nsplit, 1);
+    const size_t lds = (size_t)tpw * nsplit * kSmallTile * (kSmallTile + 1) * sizeof(double);
+    static std::atomic<unsigned long long> attr_done{0};
+    hipError_t e = once_per_device(attr_done, [] {
+        return hipFuncSetAttribute((const void*)k_gemm_tn_small<SYM, EDGE, VEC>,
+                                   hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   kSmallMaxSplit * kSmallTile * (kSmallTile + 1) * (int)sizeof(double));
+    });
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_gemm_tn_small<SYM, EDGE, VEC>), dim3((T + tpw - 1) / tpw), dim3(64 * tpw * nsplit), lds, s, g,
+                       nsplit, tpw);
     return hipGetLastError();
 }
 
@@ -296,12 +326,17 @@ hipError_t launch_tn_small(const GemmTN& g, hipStream_t s) {
 hipError_t launch_gemm_tn(const GemmTN& g, bool sym, int tile_group, double* chunk, size_t chunk_bytes,
                           hipStream_t s) {
     if (g.N < 1 || !g.A || !g.B || !g.C || (g.beta != 0.0 && !g.Cin)) return hipErrorInvalidValue;
-    if (small_f64_tile((g.N + TB - 1) / TB * TB)) {
+    const int nt128 = (g.N + TB - 1) / TB;
+    // g.keep_split: the chunks of the 128 x 128 kernel's split, so that C is the
+    // same bit for bit whichever kernel runs
+    int r = 0, nsplit = g.N <= kSmallWideLd ? 8 : 4;
+    if (g.keep_split) nsplit = chunk ? tn_split(sym ? tri_tiles(nt128) : nt128 * nt128, (g.N + TK - 1) / TK, &r) : 1;
+    if (small_f64_tile(nt128 * TB) && nsplit <= kSmallMaxSplit) {
         const bool vec = g.N % 2 == 0 && (reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) % 16 == 0;
         if (g.N % kSmallTile == 0 && vec)
-            return sym ? launch_tn_small<true, false, true>(g, s) : launch_tn_small<false, false, true>(g, s);
-        if (vec) return sym ? launch_tn_small<true, true, true>(g, s) : launch_tn_small<false, true, true>(g, s);
-        return sym ? launch_tn_small<true, true, false>(g, s) : launch_tn_small<false, true, false>(g, s);
+            return sym ? launch_tn_small<true, false, true>(g, nsplit, s) : launch_tn_small<false, false, true>(g, nsplit, s);
+        if (vec) return sym ? launch_tn_small<true, true, true>(g, nsplit, s) : launch_tn_small<false, true, true>(g, nsplit, s);
+        return sym ? launch_tn_small<true, true, false>(g, nsplit, s) : launch_tn_small<false, true, false>(g, nsplit, s);
     }
     const bool edge = g.N % TB != 0;
     if (sym) return edge ? launch_tn<true, true>(g, tile_group, chunk, chunk_bytes, s)

@@ -14,6 +14,10 @@ struct GemmTN {
     double* C;
     int N;
     double alpha, beta, gamma;
+    // C must not depend on the kernel that runs: a product that an int8 SP2
+    // solve takes its digits from, which would carry a last-bit change of H
+    // into a rounding of its own
+    bool keep_split;
 };
 
 // sym: A^T B is symmetric (the caller's assertion): only the upper tiles are

@@ -12,12 +12,15 @@ namespace sp2 {
 hipError_t launch_row_abs_max(const double* S, int N, unsigned long long* mx, hipStream_t s);
 // Zero one 64-bit word (graph-safe, no memset).
 hipError_t launch_zero_word(unsigned long long* w, hipStream_t s);
-// Y <- S / c with c = the bound in mx, Z <- I (N x N row-major).
-hipError_t launch_ns_init(const double* S, int N, const unsigned long long* mx, double* Y, double* Z, hipStream_t s);
-// T <- 1.5 I - 0.5 T in place, and part[b] = sum over block b of (T - I)^2
+// Y <- S / c with c = the bound in mx (N x N row-major).
+hipError_t launch_ns_init(const double* S, int N, const unsigned long long* mx, double* Y, hipStream_t s);
+// Z <- I.
+hipError_t launch_identity(double* Z, int N, hipStream_t s);
+// T <- 1.5 I - 0.5 P (T may be P unless mirror, which reads the upper triangle
+// of P for the lower one), and part[b] = sum over block b of (P - I)^2
 // (fixed grid of kNsBlocks workgroups, fixed order inside each).
 constexpr int kNsBlocks = 1024;
-hipError_t launch_ns_step(double* T, int N, double* part, hipStream_t s);
+hipError_t launch_ns_step(const double* P, bool mirror, double* T, int N, double* part, hipStream_t s);
 // out[0] <- sqrt(sum of part[0 .. n)) in fixed order (one workgroup).
 hipError_t launch_sum_sqrt(const double* part, int n, double* out, hipStream_t s);
 // Z <- Z / sqrt(c) with c the bound in mx.

@@ -75,10 +75,9 @@ __device__ __forceinline__ void small_mma(const double* __restrict__ A, const do
     }
 }
 
-// The waves' partial tiles (each over its share of K) to LDS; after the
-// barrier small_sum(red, r, c) adds element (r, c) in wave order.
-__device__ __forceinline__ void small_store(double (*red)[kSmallTile][kSmallTile + 1], const d4s (&acc)[2][2]) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+// A wave's partial tile to LDS, rows of 33 doubles.
+__device__ __forceinline__ void small_store(double* red, const d4s (&acc)[2][2]) {
+    const int lane = threadIdx.x & 63;
     // v_mfma_f64_16x16x4f64 result: lane l, element r is row (l >> 4) + 4 r, column l & 15 of block (m, n)
 #pragma unroll
     for (int m = 0; m < 2; ++m)
@@ -86,14 +85,7 @@ __device__ __forceinline__ void small_store(double (*red)[kSmallTile][kSmallTile
         for (int n = 0; n < 2; ++n)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                red[w][2 * ((lane >> 4) + 4 * r) + m][2 * (lane & 15) + n] = acc[m][n][r];
-}
-template <int NW>
-__device__ __forceinline__ double small_sum(const double (*red)[kSmallTile][kSmallTile + 1], int r, int c) {
-    double p = red[0][r][c];
-#pragma unroll
-    for (int w = 1; w < NW; ++w) p += red[w][r][c];
-    return p;
+                red[(2 * ((lane >> 4) + 4 * r) + m) * (kSmallTile + 1) + 2 * (lane & 15) + n] = acc[m][n][r];
 }
 
 }  // namespace sp2

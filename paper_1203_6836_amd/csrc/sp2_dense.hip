@@ -636,7 +636,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_f64_small(double* __restrict__
     const int nk = ld / 4;
     d4s acc[2][2];
     small_mma<false, true>(Xc, Xc, ld, ld, i0, j0, w * nk / NW, (w + 1) * nk / NW, acc);
-    small_store(red, acc);
+    small_store(&red[w][0][0], acc);
     __syncthreads();
     const int br = st->branch;
     double tr = 0.0, fro = 0.0, idm = 0.0;
@@ -645,7 +645,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_f64_small(double* __restrict__
         const int e = tid + 64 * NW * q, r = e >> 5, c = e & 31;
         const int gi = i0 + r, gj = j0 + c;
         if (gi > gj) continue;
-        const double p = small_sum<NW>(red, r, c);
+        double p = red[0][r][c];
+#pragma unroll
+        for (int v = 1; v < NW; ++v) p += red[v][r][c];
         const double xn = br ? 2.0 * x[q] - p : p;
         const double wgt = gi == gj ? 1.0 : 2.0;   // the mirrored element's share
         Xn[(size_t)gi * ld + gj] = xn;

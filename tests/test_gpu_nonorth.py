@@ -348,3 +348,21 @@ def test_nonorth_thresholded_gapped_wire_vs_oracle(ctx):
     assert s64["iterations"] == r.iterations
     assert e64 <= 1e-9
     assert e8 <= 1e-6
+
+
+@pytest.mark.parametrize("n", [64, 130, 417, 2900])
+def test_factor_and_transforms_at_the_small_products_sizes(ctx, n):
+    """The factor's first iteration, whose products are left out, and the
+    transforms at sizes of every K split of the small product kernel
+    (3, 5 and 7 chunks, and none): S = 4 I ends in the first iteration with
+    Z = I / 2, so the solve is exactly the orthogonal one of H / 4."""
+    import paper_1203_6836_amd as p
+    say(f"case transform products N={n}")
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n))
+    H = 0.5 * (A + A.T) / np.sqrt(n)
+    n_occ = n // 3 + 1
+    D1, _, its1 = ctx.sp2_density_matrix_nonorth(to_dev(H), to_dev(4.0 * np.eye(n)), n_occ, p.options("fp64"))
+    D0, _ = ctx.sp2_density_matrix(to_dev(0.25 * H), n_occ, p.options("fp64"))
+    assert its1 == 1
+    assert np.array_equal(4.0 * D1.cpu().numpy(), D0.cpu().numpy())
