@@ -62,8 +62,9 @@ struct sp2_ctx {
     size_t xcap = 0;          // elements per buffer
     double* part = nullptr;
     size_t partcap = 0;
-    State* st = nullptr;
+    State* st = nullptr;      // two records (folded control alternates between them)
     State* st_host = nullptr; // pinned
+    int* progress = nullptr;  // pinned, written by the folded control step
     double* scal = nullptr;   // device scalars
     double* scal_host = nullptr;
     double* chk = nullptr;    // H check partials (2 per check workgroup)
@@ -228,7 +229,8 @@ sp2_status sp2_ctx_create(sp2_ctx** out, int device, void* stream) {
     sp2_ctx* c = new sp2_ctx();
     c->device = device;
     c->stream = (hipStream_t)stream;
-    if (hipMalloc((void**)&c->st, sizeof(State)) != hipSuccess ||
+    if (hipMalloc((void**)&c->st, 2 * sizeof(State)) != hipSuccess ||
+        hipHostMalloc((void**)&c->progress, sizeof(int), hipHostMallocCoherent) != hipSuccess ||
         hipHostMalloc((void**)&c->st_host, sizeof(State), hipHostMallocDefault) != hipSuccess ||
         hipMalloc((void**)&c->scal, 64 * sizeof(double)) != hipSuccess ||
         hipMalloc((void**)&c->chk, 2 * kCheckGrid * sizeof(double)) != hipSuccess ||
@@ -263,6 +265,7 @@ void sp2_ctx_destroy(sp2_ctx* c) {
         if (p) (void)hipFree(p);
     split_free(c->split);
     if (c->st_host) (void)hipHostFree(c->st_host);
+    if (c->progress) (void)hipHostFree(c->progress);
     if (c->scal_host) (void)hipHostFree(c->scal_host);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
@@ -374,7 +377,8 @@ static size_t solve_part_slots(int N) {
     const int nt = ld / kTile;
     return std::max<size_t>({(size_t)(N + 3) / 4 * 2, (size_t)ld / 4 * 3, (size_t)tri_tiles(nt) * 3, 1024,
                              (size_t)kDotBlocks, split_part_slots(ld) * 3,
-                             ld <= kSmallMaxLd ? (size_t)tri_tiles(ld / 32) * 3 : 0});
+                             // the folded control needs the slots of two products
+                             ld <= kSmallMaxLd ? (size_t)tri_tiles(ld / 32) * 3 * 2 : 0});
 }
 
 static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, const sp2_options& o, double* D,
@@ -497,8 +501,65 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
         HIPCHK(c, launch_init(H, N, ld, buf0, c->st, part, &ns, st, upper ? c->split.rmax : nullptr));
     HIPCHK(c, launch_ctrl_init(part, ns, c->st, a, st));
 
-    int launched = 0;
-    bool finished = false;
+    // Folded control (dense FP64 products on 32 x 32 tiles, dense int8 products
+    // on 64 x 64 tiles): one launch per FP64 product, two per int8 product, and
+    // no read-back until the end.  The host stays kFoldAhead products ahead of
+    // the device's progress, so a finished solve has at most that many empty
+    // products behind it.
+    const int fold_slots = o.tau > 0.0 || c->profile ? 0
+                           : f64_small && o.precision == SP2_PREC_FP64
+                               ? (tri_tiles(ld / 32) <= kFoldSlots ? tri_tiles(ld / 32) : 0)
+                           : upper ? int8x_folded_slots(ld)
+                                   : 0;
+    State* stp = c->st;   // the current record
+    if (fold_slots > 0) {
+        constexpr int kFoldAhead = 6;
+        volatile int* progress = c->progress;
+        *progress = 0;
+        int g = 0, done = 0;
+        for (; g < o.max_iter && !done; ++g) {
+            FoldArgs f;
+            f.part = part + (upper ? 0 : (size_t)((g + 1) & 1) * 3 * fold_slots);
+            f.in = stp;
+            f.out = stp == c->st ? c->st + 1 : c->st;
+            f.progress = c->progress;
+            f.nslots = fold_slots;
+            f.g = g;
+            f.ctrl = a;
+            if (upper) {
+                HIPCHK(c, launch_split_encode(c->split, buf0, buf1, ld, stp, st, &f));
+                if (g > 0) stp = f.out;
+                HIPCHK(c, launch_split_gemm(c->split, buf0, buf1, ld, stp, part, &ns, st, nullptr));
+            } else {
+                HIPCHK(c, launch_gemm_f64_folded(buf0, buf1, ld, f, part + (size_t)(g & 1) * 3 * fold_slots, st));
+                if (g > 0) stp = f.out;
+            }
+            // wait until the device is at most kFoldAhead products behind (the
+            // stream running empty or failing ends the wait as well)
+            for (unsigned spin = 1;; ++spin) {
+                const int v = *progress;
+                done = v & 7;
+                if (done || g - (v >> 3) <= kFoldAhead) break;
+                if (spin % 65536 == 0) {
+                    const hipError_t q = hipStreamQuery(st);
+                    if (q == hipSuccess) break;
+                    if (q != hipErrorNotReady) HIPCHK(c, q);
+                    (void)hipGetLastError();   // not an error of the next launch
+                }
+            }
+        }
+        if (!done)   // the last product's result
+            HIPCHK(c, launch_ctrl_step(part + (upper ? 0 : (size_t)((g - 1) & 1) * 3 * fold_slots), fold_slots, stp, a, st));
+        HIPCHK(c, hipMemcpyAsync(c->st_host, stp, sizeof(State), hipMemcpyDeviceToHost, st));
+        if (done == 0) {
+            HIPCHK(c, hipStreamSynchronize(st));
+            done = c->st_host->done;
+        }
+        if (done == 1 || done == 2)
+            HIPCHK(c, upper ? launch_finalize_upper(buf0, buf1, ld, N, D, stp, st)
+                            : launch_finalize(buf0, buf1, ld, N, D, stp, st));
+    }
+    int launched = fold_slots > 0 ? o.max_iter : 0;
     while (launched < o.max_iter) {
         const int chunk = std::min(launched == 0 ? 24 : 8, o.max_iter - launched);
         for (int k = 0; k < chunk; ++k) {
@@ -526,14 +587,10 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
         launched += chunk;
         HIPCHK(c, hipMemcpyAsync(c->st_host, c->st, sizeof(State), hipMemcpyDeviceToHost, st));
         HIPCHK(c, hipStreamSynchronize(st));
-        if (c->st_host->done) {
-            finished = true;
-            break;
-        }
+        if (c->st_host->done) break;
     }
-    (void)finished;
     const State& h = *c->st_host;
-    if (h.done == 1 || h.done == 2)
+    if (fold_slots == 0 && (h.done == 1 || h.done == 2))
         HIPCHK(c, upper ? launch_finalize_upper(buf0, buf1, ld, N, D, c->st, st)
                         : launch_finalize(buf0, buf1, ld, N, D, c->st, st));
     HIPCHK(c, hipEventRecord(c->ev1, st));

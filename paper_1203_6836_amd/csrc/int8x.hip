@@ -34,6 +34,7 @@
 #include <atomic>
 #include <algorithm>
 
+#include "fold.h"
 #include "split_internal.h"
 
 namespace sp2 {
@@ -269,17 +270,21 @@ __device__ __forceinline__ double scale_inv(unsigned long long bits, double* s_o
     return row_scale(__longlong_as_double((long long)bits), s_out);
 }
 
-template <int S>
+template <int S, bool FOLD>
 __global__ __launch_bounds__(256) void k_encode_int8_upper(const double* __restrict__ buf0,
                                                            const double* __restrict__ buf1, int ld,
                                                            const State* __restrict__ st,
                                                            int8_t* __restrict__ digits,
                                                            double* __restrict__ scale,
-                                                           unsigned long long* __restrict__ rmax) {
-    if (st->done || st->phase != 1) return;
-    const double* __restrict__ X = st->cur ? buf1 : buf0;
-    const unsigned long long* __restrict__ rm = rmax + (size_t)st->cur * ld;
-    unsigned long long* __restrict__ rm_next = rmax + (size_t)(1 - st->cur) * ld;
+                                                           unsigned long long* __restrict__ rmax, FoldArgs f) {
+    if (!FOLD && (st->done || st->phase != 1)) return;
+    __shared__ FoldShared fsh;
+    FoldPart fp;
+    if (FOLD) fp.load(f);
+    const int cur = FOLD ? f.g & 1 : st->cur;
+    const double* __restrict__ X = cur ? buf1 : buf0;
+    const unsigned long long* __restrict__ rm = rmax + (size_t)cur * ld;
+    unsigned long long* __restrict__ rm_next = rmax + (size_t)(1 - cur) * ld;
     const int nb = ld >> 5;
     // block (I, J) of the upper triangle, row-major over I
     const int t = blockIdx.x;
@@ -293,8 +298,14 @@ __global__ __launch_bounds__(256) void k_encode_int8_upper(const double* __restr
     const size_t plane = (size_t)ld * ld;
     const double4 v = *reinterpret_cast<const double4*>(X + (size_t)(I * 32 + r) * ld + J * 32 + c0);
     const double x[4] = {v.x, v.y, v.z, v.w};
+    const unsigned long long mi = rm[I * 32 + r], mj = rm[J * 32 + r];
+    if (FOLD) {
+        int done, br;
+        fold_decide<false>(f, fp, fsh, &done, &br);
+        if (done) return;
+    }
     double sc;
-    const double inv = scale_inv(rm[I * 32 + r], &sc);
+    const double inv = scale_inv(mi, &sc);
     pack_digits4(x, inv, S, digit_bits(ld, S), digits + ((size_t)I * nb + J) * 1024 + r * 32 + 16 * ((c0 >> 4) ^ dswz(r)) + (c0 & 15),
                  plane);
     if (I == J) {
@@ -312,7 +323,7 @@ __global__ __launch_bounds__(256) void k_encode_int8_upper(const double* __restr
     __syncthreads();
     // row J*32 + r of X, columns I*32 + c0 .. + 3 = column r of the block, rows c0 ..
     const double xt[4] = {T[c0][r], T[c0 + 1][r], T[c0 + 2][r], T[c0 + 3][r]};
-    const double invt = scale_inv(rm[J * 32 + r], nullptr);
+    const double invt = scale_inv(mj, nullptr);
     pack_digits4(xt, invt, S, digit_bits(ld, S), digits + ((size_t)J * nb + I) * 1024 + r * 32 + 16 * ((c0 >> 4) ^ dswz(r)) + (c0 & 15),
                  plane);
 }
@@ -1285,6 +1296,11 @@ static bool use_tile64(int ld) {
     return t64 < t128;
 }
 
+int int8x_folded_slots(int ld) {
+    const int T = tri_tiles(ld / QT);
+    return use_tile64(ld) && T <= kFoldSlots ? T : 0;
+}
+
 template <int S, int NL>
 static hipError_t launch_t64(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                              hipStream_t stream) {
@@ -1359,7 +1375,7 @@ __global__ __launch_bounds__(256) void k_encode_int8_env(const double* __restric
 
 template <int S>
 static hipError_t run_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
-                             hipStream_t stream) {
+                             hipStream_t stream, const FoldArgs* f) {
     if (s.env) {
         hipLaunchKernelGGL(k_encode_int8_env<S>, dim3(ld / 4), dim3(256), 0, stream, buf0, buf1, ld, st, s.digits,
                            s.scale, s.env);
@@ -1367,8 +1383,13 @@ static hipError_t run_encode(SplitScratch& s, const double* buf0, const double* 
     }
     if (s.upper) {
         const int nb = ld / 32;
-        hipLaunchKernelGGL(k_encode_int8_upper<S>, dim3(nb * (nb + 1) / 2), dim3(256), 0, stream, buf0, buf1, ld,
-                           st, s.digits, s.scale, s.rmax);
+        const dim3 grid(nb * (nb + 1) / 2);
+        if (f)
+            hipLaunchKernelGGL((k_encode_int8_upper<S, true>), grid, dim3(256), 0, stream, buf0, buf1, ld, st, s.digits,
+                               s.scale, s.rmax, *f);
+        else
+            hipLaunchKernelGGL((k_encode_int8_upper<S, false>), grid, dim3(256), 0, stream, buf0, buf1, ld, st, s.digits,
+                               s.scale, s.rmax, FoldArgs{});
     } else if (ld <= 2048 * ENC_CH)
         hipLaunchKernelGGL(k_encode_int8_reg<S>, dim3(ld), dim3(256), 0, stream, buf0, buf1, ld, st, s.digits,
                            s.scale);
@@ -1406,13 +1427,13 @@ hipError_t launch_int8x_grouped(int slices, int levels, const GroupDesc* g, int 
 }
 
 hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
-                               hipStream_t stream) {
+                               hipStream_t stream, const FoldArgs* f) {
     switch (s.slices) {
-        case 2: return run_encode<2>(s, buf0, buf1, ld, st, stream);
-        case 3: return run_encode<3>(s, buf0, buf1, ld, st, stream);
-        case 4: return run_encode<4>(s, buf0, buf1, ld, st, stream);
-        case 5: return run_encode<5>(s, buf0, buf1, ld, st, stream);
-        case 6: return run_encode<6>(s, buf0, buf1, ld, st, stream);
+        case 2: return run_encode<2>(s, buf0, buf1, ld, st, stream, f);
+        case 3: return run_encode<3>(s, buf0, buf1, ld, st, stream, f);
+        case 4: return run_encode<4>(s, buf0, buf1, ld, st, stream, f);
+        case 5: return run_encode<5>(s, buf0, buf1, ld, st, stream, f);
+        case 6: return run_encode<6>(s, buf0, buf1, ld, st, stream, f);
         default: return hipErrorInvalidValue;
     }
 }

@@ -14,6 +14,7 @@
 #include <cmath>
 #include <type_traits>
 
+#include "fold.h"
 #include "small_f64.h"
 #include "sp2_internal.h"
 
@@ -240,30 +241,6 @@ __device__ void reduce3(const double* __restrict__ part, int nslots, double out[
     out[2] = block_sum256(c, sh);
 }
 
-// Branch rule: X^2 if its trace is at least as close to n_occ as that of
-// 2X - X^2 (Tr X^2 = t2, Tr(2X - X^2) = 2 t1 - t2).
-__device__ __forceinline__ int choose_branch(double t1, double t2, double nocc) {
-    return fabs(t2 - nocc) <= fabs(2.0 * t1 - t2 - nocc) ? 0 : 1;
-}
-
-__device__ __forceinline__ void set_bit(State* st, int n, int b) {
-    if (n < 128 && b) st->bits[n >> 6] |= (1ull << (n & 63));
-}
-__device__ __forceinline__ void clear_bit(State* st, int n) {
-    if (n < 128) st->bits[n >> 6] &= ~(1ull << (n & 63));
-}
-
-// Kept-block fraction of the threshold pass that just ran (if any).
-__device__ __forceinline__ double take_fill(State* st, const CtrlArgs& a) {
-    if (a.total_blocks <= 0.0) return -1.0;
-    const double f = (double)st->kept / a.total_blocks;
-    st->kept = 0ull;
-    st->full_fill = f >= a.dense_fill ? 1 : 0;
-    st->fill_min = fmin(st->fill_min, f);
-    st->fill_max = fmax(st->fill_max, f);
-    return f;
-}
-
 __global__ __launch_bounds__(256) void k_ctrl_init(const double* __restrict__ part, int nslots,
                                                    State* __restrict__ st, CtrlArgs a) {
     double r[3];
@@ -282,74 +259,12 @@ __global__ __launch_bounds__(256) void k_ctrl_init(const double* __restrict__ pa
     }
 }
 
-// After product n: the partials hold Tr X_{n+1}, ||X_{n+1}||_F^2 and
-// ||X_n^2 - X_n||_F^2.  Stop rules: e_n < idem_tol (converged, D = X_n);
-// n >= 4, e_n >= r e_{n-2}, e_n < stall_tol (stalled at the floor of the
-// idempotency error, D = X_n; r = 1, or 1/2 with a threshold, whose floor
-// keeps creeping down); n + 1 == max_iter (not converged).  Otherwise X_{n+1} becomes
-// current and the next branch is chosen from its traces.
 __device__ __forceinline__ void ctrl_step_body(const double* __restrict__ part, int nslots, State* __restrict__ st,
-                               const CtrlArgs& a) {
+                                               const CtrlArgs& a) {
     if (st->done) return;
     double r[3];
     reduce3(part, nslots, r);
-    if (threadIdx.x != 0) return;
-    const int n = st->iter;
-    const double e = sqrt(r[2]);
-    st->idem[n] = e;
-    const double f = take_fill(st, a);
-    if (f >= 0.0) st->fill[n] = (float)f;
-    st->iter = n + 1;
-    if (st->phase == 0) st->fp64_products += 1;   // FP64 products (the whole solve, or the head)
-    const bool stall = n >= 4 && e >= a.stall_ratio * st->idem[n - 2] && e < a.stall_tol;
-    // BF16X2 runs its own schedule: a stall of the BF16 stage starts a fixed
-    // FP32 tail instead of stopping
-    // a projector whose trace is not n_occ could not pick the occupied set:
-    // the Fermi level is degenerate (done = 4)
-    const int gap_or = fabs(st->t1 - a.n_occ) > 0.5 ? 4 : 0;
-    if (e < a.idem_tol || (stall && a.mixed != 2)) {
-        st->done = gap_or ? gap_or : ((e < a.idem_tol) ? 1 : 2);
-        st->result = st->cur;
-        clear_bit(st, n);
-        return;
-    }
-    if (n + 1 >= a.max_iter) {
-        st->done = (a.max_iter >= kGapMinIter && e >= kGapIdem) ? 4 : 3;
-        st->result = 1 - st->cur;
-        return;
-    }
-    if (a.mixed == 2 && st->phase == 2) {
-        // tail product: its update X_{n+1} is applied; after fp32_tail of them, stop
-        st->tail_left -= 1;
-        if (st->tail_left <= 0) {
-            st->done = fabs(r[0] - a.n_occ) > 0.5 ? 4 : 2;
-            st->result = 1 - st->cur;
-            st->t1 = r[0];
-            st->t2 = r[1];
-            return;
-        }
-    }
-    if (a.mixed == 2 && st->phase == 1 && stall) {
-        if (a.fp32_tail <= 0) {
-            st->done = gap_or ? gap_or : 2;
-            st->result = st->cur;
-            clear_bit(st, n);
-            return;
-        }
-        st->phase = 2;
-        st->tail_left = a.fp32_tail;
-        st->head_switch = n + 1;
-    }
-    st->cur = 1 - st->cur;
-    st->t1 = r[0];
-    st->t2 = r[1];
-    const int b = choose_branch(r[0], r[1], a.n_occ);
-    st->branch = b;
-    set_bit(st, n + 1, b);
-    if (a.mixed != 0 && st->phase == 0 && n + 1 >= a.fp64_head && a.fp64_head >= 0) {
-        st->phase = 1;
-        st->head_switch = n + 1;
-    }
+    if (threadIdx.x == 0) ctrl_apply(r, st, a);
 }
 
 __global__ __launch_bounds__(256) void k_ctrl_step(const double* __restrict__ part, int nslots,
@@ -612,16 +527,20 @@ __global__ __launch_bounds__(256, 2) void k_gemm_f64(double* __restrict__ buf0,
 // 1024 (48.4), 75 at 1536 (149; 100 on 128 x 128 tiles), 169 at 2048 (282;
 // 200).  At N = 1024 and above the matrix cores are busy 45-70 % of it; 64 x 32
 // tiles (a quarter less L2 traffic, half the waves) took 175 us at 2048.
-template <int NW>
+template <int NW, bool FOLD>
 __global__ __launch_bounds__(64 * NW) void k_gemm_f64_small(double* __restrict__ buf0, double* __restrict__ buf1,
                                                             int ld, const State* __restrict__ st,
-                                                            double* __restrict__ part) {
+                                                            double* __restrict__ part, FoldArgs f) {
     constexpr int PER = kSmallTile * kSmallTile / (64 * NW);
     __shared__ double red[NW][kSmallTile][kSmallTile + 1];
     __shared__ double sh[NW];
-    if (st->done || st->phase != 0) return;
-    const double* __restrict__ Xc = st->cur ? buf1 : buf0;
-    double* __restrict__ Xn = st->cur ? buf0 : buf1;
+    __shared__ FoldShared fsh;
+    if (!FOLD && (st->done || st->phase != 0)) return;
+    const int cur = FOLD ? f.g & 1 : st->cur;
+    FoldPart fp;
+    if (FOLD) fp.load(f);
+    const double* __restrict__ Xc = cur ? buf1 : buf0;
+    double* __restrict__ Xn = cur ? buf0 : buf1;
     const int nts = ld / kSmallTile;
     int bi, bj;
     tile_of_block(blockIdx.x, nts, 16, bi, bj);
@@ -637,8 +556,15 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_f64_small(double* __restrict__
     d4s acc[2][2];
     small_mma<false, true>(Xc, Xc, ld, ld, i0, j0, w * nk / NW, (w + 1) * nk / NW, acc);
     small_store(&red[w][0][0], acc);
-    __syncthreads();
-    const int br = st->branch;
+    int done = 0, br;
+    if (FOLD) {
+        fold_decide<true>(f, fp, fsh, &done, &br);   // its barriers cover red
+        if (done) return;
+        if (f.g == 0) __syncthreads();
+    } else {
+        br = st->branch;
+        __syncthreads();
+    }
     double tr = 0.0, fro = 0.0, idm = 0.0;
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
@@ -829,6 +755,15 @@ bool small_f64_tile(int ld) {
     const int cus = device_cus(), rounds = (tri_tiles(ld / GB) + cus - 1) / cus;
     return 1.82e-8 * (256.0 / cus) * ld * ld < 0.13 * rounds;
 }
+hipError_t launch_gemm_f64_folded(double* buf0, double* buf1, int ld, const FoldArgs& f, double* part_out,
+                                  hipStream_t s) {
+    const int T = tri_tiles(ld / kSmallTile);
+    if (ld <= kSmallWideLd)
+        hipLaunchKernelGGL((k_gemm_f64_small<8, true>), dim3(T), dim3(512), 0, s, buf0, buf1, ld, f.in, part_out, f);
+    else
+        hipLaunchKernelGGL((k_gemm_f64_small<4, true>), dim3(T), dim3(256), 0, s, buf0, buf1, ld, f.in, part_out, f);
+    return hipGetLastError();
+}
 hipError_t launch_gemm_f64(double* buf0, double* buf1, int ld, State* st, double* part,
                            int* nslots, hipStream_t s, const int* env, int tile_group, double* tail_buf,
                            size_t tail_bytes, int split_cap, bool small_ok) {
@@ -836,9 +771,9 @@ hipError_t launch_gemm_f64(double* buf0, double* buf1, int ld, State* st, double
         const int T = tri_tiles(ld / kSmallTile);
         *nslots = T;
         if (ld <= kSmallWideLd)
-            hipLaunchKernelGGL(k_gemm_f64_small<8>, dim3(T), dim3(512), 0, s, buf0, buf1, ld, st, part);
+            hipLaunchKernelGGL((k_gemm_f64_small<8, false>), dim3(T), dim3(512), 0, s, buf0, buf1, ld, st, part, FoldArgs{});
         else
-            hipLaunchKernelGGL(k_gemm_f64_small<4>, dim3(T), dim3(256), 0, s, buf0, buf1, ld, st, part);
+            hipLaunchKernelGGL((k_gemm_f64_small<4, false>), dim3(T), dim3(256), 0, s, buf0, buf1, ld, st, part, FoldArgs{});
         return hipGetLastError();
     }
     const int nt = ld / GB;

@@ -51,6 +51,29 @@ struct CtrlArgs {
     double dense_fill;    // kept fraction from which State::full_fill is set (> 1: never)
 };
 
+// Control folded into the first kernel of the next product.  At small N a
+// control launch (2.9-4.6 us and the gaps around it) is a third of a product, and
+// all its one workgroup does is add a few hundred partials.  So the kernel that
+// starts product g (the FP64 product itself, the int8 encode) has every
+// workgroup add the partials of product g - 1 in the control kernel's order
+// and take the same decision; workgroup 0 writes the new state to the other
+// of two State records and its product count and `done` to host memory, where
+// the host sees how far the solve is without waiting for it.  Used while a
+// solve's partials are at most kFoldSlots triples, one per thread.  Per solve:
+// FP64 N = 128 536 -> 392 us, 500 912 -> 742; int8 N = 128 749 -> 632, 720 1396 ->
+// 1216, 1400 2007 -> 1853.  With 528 triples it was level (FP64 N = 1020) or 3 %
+// slower (int8 N = 2048), as each of 528-2080 workgroups reads them all.
+constexpr int kFoldSlots = 256;
+struct FoldArgs {
+    const double* part;   // partials of product g - 1 (nslots triples)
+    const State* in;      // state before its result
+    State* out;           // state after it
+    int* progress;        // host: (products whose result is known) << 3 | done
+    int nslots;
+    int g;                // this product; X_g is in buffer g & 1
+    CtrlArgs ctrl;
+};
+
 // ---- grouped (multi-system) launches used by the serving loop ----
 constexpr int kMaxGroup = 64;
 
@@ -257,6 +280,10 @@ constexpr int kSmallMaxLd = 3968;
 // 3840-3968 on 256 CUs), and from 4096 on, where it splits its last round
 // (1165 against 1235 us).
 bool small_f64_tile(int ld);
+// The folded form of the small product: f.g == 0 takes branch and done from
+// f.in; part_out must not be f.part.
+hipError_t launch_gemm_f64_folded(double* buf0, double* buf1, int ld, const FoldArgs& f, double* part_out,
+                                  hipStream_t s);
 hipError_t launch_gemm_f64(double* buf0, double* buf1, int ld, State* st, double* part,
                            int* nslots, hipStream_t s, const int* env = nullptr, int tile_group = 8,
                            double* tail_buf = nullptr, size_t tail_bytes = 0, int split_cap = 16,

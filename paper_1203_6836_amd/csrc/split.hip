@@ -353,8 +353,8 @@ size_t split_part_slots(int ld) {
 }
 
 hipError_t launch_split_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
-                               hipStream_t stream) {
-    if (s.slices > 0) return launch_int8x_encode(s, buf0, buf1, ld, st, stream);
+                               hipStream_t stream, const FoldArgs* f) {
+    if (s.slices > 0) return launch_int8x_encode(s, buf0, buf1, ld, st, stream, f);
     if (s.bf16) return launch_bf16x2_encode(s, buf0, buf1, ld, st, stream);
     return hipErrorNotSupported;
 }

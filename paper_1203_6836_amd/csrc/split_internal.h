@@ -47,8 +47,10 @@ size_t split_part_slots(int ld);
 
 // Encode the current X_n (buffer st->cur) into the split operands when the
 // control state says the next product is a reduced-precision one.
+// f (upper-only int8 only, may be null): with the control step of the product
+// before folded in; st is then not read.
 hipError_t launch_split_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
-                               hipStream_t stream);
+                               hipStream_t stream, const FoldArgs* f = nullptr);
 // Reduced-precision product with the fused SP2 update (no-op in FP64 phase).
 hipError_t launch_split_gemm(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                              int* nslots, hipStream_t stream, const int* env = nullptr);
@@ -76,7 +78,10 @@ hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, dou
 
 // int8 digit-plane product (int8x.hip)
 hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
-                               hipStream_t stream);
+                               hipStream_t stream, const FoldArgs* f);
+// Partial slots of a dense upper-only product of padded size ld whose control
+// step is folded into the encode (64 x 64 tiles, at most kFoldSlots), else 0.
+int int8x_folded_slots(int ld);
 hipError_t launch_int8x_gemm(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                              int* nslots, hipStream_t stream, const int* env = nullptr);
 

@@ -303,3 +303,57 @@ def test_context_reuse_across_sizes(ctx):
             torch.cuda.synchronize()
             fresh.close()
             assert torch.equal(D0, D1), (prec, H.shape)
+
+
+@pytest.mark.parametrize("n_atoms,precision,kw", [(2, "fp64", {}), (32, "fp64", {}), (130, "fp64", {}), (176, "fp64", {}),
+                                                  (177, "fp64", {}), (32, "int8x", {}), (300, "int8x", {"slices": 4, "levels": 5}),
+                                                  (352, "int8x", {}), (353, "int8x", {})])
+def test_control_folded_into_the_next_product(ctx, n_atoms, precision, kw):
+    """Small solves take branch and stop decisions in the kernel that starts the
+    next product; with profiling on, every product is followed by the control
+    kernel.  Both ways give the same D and the same statistics, for solves that
+    converge, stop at every kind of max_iter (first product, just before and at
+    convergence) and for a degenerate level and an invalid H, at sizes on both
+    sides of the largest folded one (padded N 640 / 768 in FP64, 1408 / 1536 in
+    int8)."""
+    import torch
+    import paper_1203_6836_amd as p
+    pos = synth.lattice_positions(synth.cube_dims_for(n_atoms), seed=5, n_atoms=n_atoms)
+    H = otb.hamiltonian(pos, None, synth.STATIC_MODEL)
+    N = H.shape[0]
+    say(f"case folded control N={N} {precision} {kw}")
+    bad = H.copy()
+    bad[0, 1] = np.nan
+    deg = np.kron(np.eye(2 * n_atoms), np.ones((2, 2)))   # two levels, half filling at 2 n_atoms + 1 splits one
+
+    def both(h, n_occ, **o):
+        out = []
+        for prof in (False, True):
+            ctx.sp2_ctx_set_profiling(prof)
+            hd = torch.from_numpy(np.ascontiguousarray(h)).cuda()
+            D = torch.zeros_like(hd)
+            try:
+                _, st = ctx.sp2_density_matrix(hd, n_occ, p.options(precision, **kw, **o), D_out=D)
+                code = 0
+            except p.Sp2Error as e:
+                code, st = e.status, ctx.sp2_density_matrix_status(hd, n_occ, p.options(precision, **kw, **o))[1]
+            ctx.sp2_ctx_set_profiling(False)
+            st = {k: v for k, v in st.items() if k not in ("ms", "prod_ms", "prod_count", "encode_ms", "post_ms")}
+            out.append((code, D.cpu().numpy(), st))
+        (c0, D0, s0), (c1, D1, s1) = out
+        assert c0 == c1
+        assert np.array_equal(D0, D1)
+        # NaN bounds of an invalid H compare equal as text
+        assert repr(s0) == repr(s1)
+        return c0, s0
+
+    code, st = both(H, 2 * n_atoms)
+    assert code == 0 and st["iterations"] > 2
+    its = st["iterations"]
+    for m in (1, 2, its - 1, its, its + 1):
+        code, st = both(H, 2 * n_atoms, max_iter=m)
+        assert (code == 0) == (m >= its), (m, code)
+    code, _ = both(bad, 2 * n_atoms)
+    assert code == p.SP2_EINVAL
+    code, _ = both(deg, 2 * n_atoms + 1)
+    assert code == p.SP2_EGAP
