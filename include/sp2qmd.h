@@ -597,7 +597,8 @@ void sp2_server_options_default(sp2_server_options *opt);
 /* Start a server on the context's device with its own stream and scheduler
  * thread.  Requests are admitted in arrival order whenever a slot is free and
  * their device footprint (about 37 N^2 bytes for 5 planes) fits in the arena;
- * every tick advances all admitted systems by one product in grouped,
+ * they start in that order while the running ones leave room on the chip;
+ * every tick advances all started systems by one product in grouped,
  * graph-replayed launches, and finished systems are retired and replaced
  * between ticks.  Each result is independent of the other requests in flight. */
 sp2_status sp2_server_create(sp2_ctx *ctx, const sp2_server_options *opt, sp2_server **out);

@@ -270,6 +270,15 @@ __device__ __forceinline__ double scale_inv(unsigned long long bits, double* s_o
     return row_scale(__longlong_as_double((long long)bits), s_out);
 }
 
+// Block (I, J), I <= J, at index t of the upper triangle of nb x nb blocks, row-major.
+__device__ __forceinline__ void upper_block(int t, int nb, int& I, int& J) {
+    I = (int)((2.0 * nb + 1.0 - sqrt((2.0 * nb + 1.0) * (2.0 * nb + 1.0) - 8.0 * (double)t)) / 2.0);
+    I = max(0, min(I, nb - 1));
+    while (I > 0 && I * nb - I * (I - 1) / 2 > t) --I;
+    while (I + 1 < nb && (I + 1) * nb - (I + 1) * I / 2 <= t) ++I;
+    J = I + (t - (I * nb - I * (I - 1) / 2));
+}
+
 template <int S, bool FOLD>
 __global__ __launch_bounds__(256) void k_encode_int8_upper(const double* __restrict__ buf0,
                                                            const double* __restrict__ buf1, int ld,
@@ -286,13 +295,8 @@ __global__ __launch_bounds__(256) void k_encode_int8_upper(const double* __restr
     const unsigned long long* __restrict__ rm = rmax + (size_t)cur * ld;
     unsigned long long* __restrict__ rm_next = rmax + (size_t)(1 - cur) * ld;
     const int nb = ld >> 5;
-    // block (I, J) of the upper triangle, row-major over I
-    const int t = blockIdx.x;
-    int I = (int)((2.0 * nb + 1.0 - sqrt((2.0 * nb + 1.0) * (2.0 * nb + 1.0) - 8.0 * (double)t)) / 2.0);
-    I = max(0, min(I, nb - 1));
-    while (I > 0 && I * nb - I * (I - 1) / 2 > t) --I;
-    while (I + 1 < nb && (I + 1) * nb - (I + 1) * I / 2 <= t) ++I;
-    const int J = I + (t - (I * nb - I * (I - 1) / 2));
+    int I, J;
+    upper_block(blockIdx.x, nb, I, J);
     const int tid = threadIdx.x;
     const int r = tid >> 3, c0 = (tid & 7) * 4;
     const size_t plane = (size_t)ld * ld;
@@ -328,17 +332,47 @@ __global__ __launch_bounds__(256) void k_encode_int8_upper(const double* __restr
                  plane);
 }
 
-// Grouped: work item = 4 rows of one system; fixed grid, grid-stride loop.
+// Grouped: work item = one upper 32 x 32 block of one system, as
+// k_encode_int8_upper; fixed grid, grid-stride loop.
 template <int S>
 __global__ __launch_bounds__(256) void k_encode_int8_grouped(const GroupDesc* __restrict__ g) {
-    const int total = g->total_rowq;
+    __shared__ double T[32][33];
+    const int total = g->total_blks;
+    const int tid = threadIdx.x, r = tid >> 3, c0 = (tid & 7) * 4;
     for (int item = blockIdx.x; item < total; item += gridDim.x) {
-        const int s = group_find(g->row_off, g->nsys, item);
+        const int s = group_find(g->blk_off, g->nsys, item);
         const SysView& v = g->sys[s];
         const State* st = v.st;
         if (st->done || st->phase != 1) continue;
-        const int i = (item - g->row_off[s]) * 4 + (threadIdx.x >> 6);
-        encode_row<S>(st->cur ? v.buf1 : v.buf0, v.ld, i, threadIdx.x & 63, v.digits, v.scale, 0, v.ld);
+        const int ld = v.ld, nb = ld >> 5, t = item - g->blk_off[s], cur = st->cur;
+        int I, J;
+        upper_block(t, nb, I, J);
+        const double* __restrict__ X = cur ? v.buf1 : v.buf0;
+        const unsigned long long* __restrict__ rm = v.rmax + (size_t)cur * ld;
+        unsigned long long* __restrict__ rm_next = v.rmax + (size_t)(1 - cur) * ld;
+        const size_t plane = (size_t)ld * ld;
+        const double4 x4 = *reinterpret_cast<const double4*>(X + (size_t)(I * 32 + r) * ld + J * 32 + c0);
+        const unsigned long long mi = rm[I * 32 + r], mj = rm[J * 32 + r];
+        const double x[4] = {x4.x, x4.y, x4.z, x4.w};
+        double sc;
+        const double inv = scale_inv(mi, &sc);
+        const int W = digit_bits(ld, S), off = r * 32 + 16 * ((c0 >> 4) ^ dswz(r)) + (c0 & 15);
+        pack_digits4(x, inv, S, W, v.digits + ((size_t)I * nb + J) * 1024 + off, plane);
+        if (I == J) {
+            if ((tid & 7) == 0) {
+                v.scale[I * 32 + r] = sc;
+                rm_next[I * 32 + r] = 0ull;
+            }
+            continue;
+        }
+        __syncthreads();   // the item before has read T
+        T[r][c0] = x[0];
+        T[r][c0 + 1] = x[1];
+        T[r][c0 + 2] = x[2];
+        T[r][c0 + 3] = x[3];
+        __syncthreads();
+        const double xt[4] = {T[c0][r], T[c0 + 1][r], T[c0 + 2][r], T[c0 + 3][r]};
+        pack_digits4(xt, scale_inv(mj, nullptr), S, W, v.digits + ((size_t)J * nb + I) * 1024 + off, plane);
     }
 }
 
@@ -819,6 +853,7 @@ __global__ __launch_bounds__(512) void k_gemm_int8x(double* __restrict__ buf0, d
 // deeper ring or 32-k stages changed nothing.  Above N = 3400 the operand
 // traffic, twice that of 128 x 128 tiles, costs more than the balance gives.
 constexpr int QT = 64;
+static_assert(kGroupTile == QT, "grouped products run this tile");
 
 template <int S> struct I8Stage64 {
     static constexpr int KS = S <= 5 ? 2 : 1;    // 32-k blocks per stage
@@ -1181,22 +1216,30 @@ __global__ __launch_bounds__(256) void k_chunk_sum(int* __restrict__ chunk_acc, 
     }
 }
 
-// Grouped: every upper-triangular tile of every system in the group; a fixed
-// grid loops over them (so the launch can be captured once and replayed).
+// Grouped: every upper-triangular 64 x 64 tile of every system in the group,
+// upper-only.  A fixed grid (so the launch can be captured once and replayed),
+// a whole number of workgroups per XCD (they are dealt to the XCDs
+// round-robin): those of XCD x take every per-th tile of its run, whose tiles
+// share row panels in its L2 and come in order of falling size.  Two
+// workgroups share a CU, so one's waits for digits that just left another L2,
+// its X_n tile and its row maxima pass under the other's products: with one
+// workgroup of a 128 x 128 tile per CU (57 % of the wave cycles were waits) a
+// burst of 24 requests of N = 148-2048 took 50 ms, upper-only 46-48, on these
+// tiles 37.  Handing tiles out by an atomic counter instead of the fixed
+// stride cost 5-15 ms of it.
 template <int S, int NL>
-__global__ __launch_bounds__(512) void k_gemm_int8x_grouped(const GroupDesc* __restrict__ g) {
+__global__ __launch_bounds__(256, 2) void k_gemm_int8x_grouped(const GroupDesc* __restrict__ g) {
     extern __shared__ __align__(16) int8_t smem_raw[];
-    I8Smem<S>& sm = *reinterpret_cast<I8Smem<S>*>(smem_raw);
-    const int total = g->total_tiles;
-    for (int item = blockIdx.x; item < total; item += gridDim.x) {
+    I8Smem64<S>& sm = *reinterpret_cast<I8Smem64<S>*>(smem_raw);
+    const int x = blockIdx.x % kXcds, per = gridDim.x / kXcds, end = g->xcd_off[x + 1];
+    for (int item = g->xcd_off[x] + blockIdx.x / kXcds; item < end; item += per) {
         const int s = group_find(g->tile_off, g->nsys, item);
         const SysView& v = g->sys[s];
         if (v.st->done || v.st->phase != 1) continue;
-        int bi = 0, bj = 0, tl = item - g->tile_off[s], nt = v.ld / QB, off = 0;
-        while (tl >= off + (nt - bi)) { off += nt - bi; ++bi; }
-        bj = bi + (tl - off);
-        int8x_tile<S, NL, false, false>(v.buf0, v.buf1, v.ld, v.st, v.digits, v.scale, v.part, bi, bj, sm, nullptr,
-                                     nullptr);
+        int bi, bj;
+        order_tile(item - g->tile_off[s], v.ld / QT, 16, bi, bj);
+        int8x_tile64<S, NL>(v.buf0, v.buf1, v.ld, v.st, v.digits, v.scale, v.part, bi, bj, sm,
+                            v.rmax + (size_t)(1 - v.st->cur) * v.ld);
         __syncthreads();
     }
 }
@@ -1400,28 +1443,29 @@ static hipError_t run_encode(SplitScratch& s, const double* buf0, const double* 
 }
 
 template <int S, int NL>
-static hipError_t run_grouped(const GroupDesc* g, int gemm_blocks, hipStream_t stream) {
-    const size_t lds = sizeof(I8Smem<S>);
+static hipError_t run_grouped(const GroupDesc* g, hipStream_t stream) {
+    const size_t lds = sizeof(I8Smem64<S>);
     static std::atomic<unsigned long long> attr_done{0};
     hipError_t e = once_per_device(attr_done, [&] {
         return hipFuncSetAttribute((const void*)k_gemm_int8x_grouped<S, NL>,
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     });
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_encode_int8_grouped<S>, dim3(1024), dim3(256), 0, stream, g);
-    hipLaunchKernelGGL((k_gemm_int8x_grouped<S, NL>), dim3(gemm_blocks), dim3(512), lds, stream, g);
+    hipLaunchKernelGGL(k_encode_int8_grouped<S>, dim3(2048), dim3(256), 0, stream, g);
+    const int grid = std::max(2 * device_cus() / kXcds, 1) * kXcds;
+    hipLaunchKernelGGL((k_gemm_int8x_grouped<S, NL>), dim3(grid), dim3(256), lds, stream, g);
     return hipGetLastError();
 }
 
-hipError_t launch_int8x_grouped(int slices, int levels, const GroupDesc* g, int gemm_blocks, hipStream_t stream) {
+hipError_t launch_int8x_grouped(int slices, int levels, const GroupDesc* g, hipStream_t stream) {
     const bool next = levels == slices + 1;
     if (!next && levels != slices) return hipErrorInvalidValue;
     switch (slices) {
-        case 2: return next ? run_grouped<2, 3>(g, gemm_blocks, stream) : run_grouped<2, 2>(g, gemm_blocks, stream);
-        case 3: return next ? run_grouped<3, 4>(g, gemm_blocks, stream) : run_grouped<3, 3>(g, gemm_blocks, stream);
-        case 4: return next ? run_grouped<4, 5>(g, gemm_blocks, stream) : run_grouped<4, 4>(g, gemm_blocks, stream);
-        case 5: return next ? run_grouped<5, 6>(g, gemm_blocks, stream) : run_grouped<5, 5>(g, gemm_blocks, stream);
-        case 6: return next ? hipErrorInvalidValue : run_grouped<6, 6>(g, gemm_blocks, stream);
+        case 2: return next ? run_grouped<2, 3>(g, stream) : run_grouped<2, 2>(g, stream);
+        case 3: return next ? run_grouped<3, 4>(g, stream) : run_grouped<3, 3>(g, stream);
+        case 4: return next ? run_grouped<4, 5>(g, stream) : run_grouped<4, 4>(g, stream);
+        case 5: return next ? run_grouped<5, 6>(g, stream) : run_grouped<5, 5>(g, stream);
+        case 6: return next ? hipErrorInvalidValue : run_grouped<6, 6>(g, stream);
         default: return hipErrorInvalidValue;
     }
 }

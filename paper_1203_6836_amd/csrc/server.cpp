@@ -6,7 +6,8 @@
 // hbm_budget_bytes made at creation, carved by a first-fit allocator), runs
 // H is uploaded on a copy stream; once it has landed, the per-system start
 // kernels (H check, bounds, X_0, first branch) run on the compute stream and
-// the system joins the group, which advances every started system by
+// the system joins the group, in order of arrival while the group has room
+// (kGroupFill); the group advances every started system by
 // iters_per_tick SP2 products per tick with grouped launches (encode,
 // product, control) that cover all tiles of all systems in the group.  The
 // launches are captured once in a hipGraph and replayed every tick; only the
@@ -24,6 +25,7 @@
 #include <algorithm>
 #include <chrono>
 #include <atomic>
+#include <cmath>
 #include <condition_variable>
 #include <cstring>
 #include <deque>
@@ -92,11 +94,11 @@ struct Arena {
 
 // Device footprint of one request and its layout inside its arena block.
 struct Layout {
-    size_t H, X, digits, scale, part, chk, D, q, total;
+    size_t H, X, digits, scale, part, chk, rmax, D, q, total;
 };
 Layout layout_for(int N, int slices) {
     const size_t ld = align_up((size_t)N, kTile);
-    const size_t nt = ld / kTile;
+    const size_t nt = ld / kGroupTile;
     Layout L;
     size_t o = 0;
     L.H = o;      o = align_up(o + (size_t)N * N * 8, 256);
@@ -105,7 +107,9 @@ Layout layout_for(int N, int slices) {
     L.scale = o;  o = align_up(o + ld * 8, 256);
     L.part = o;   o = align_up(o + std::max<size_t>(nt * (nt + 1) / 2, ld / 4) * 3 * 8, 256);
     L.chk = o;    o = align_up(o + 2 * (size_t)kCheckGrid * 8, 256);
-    L.D = o;      o = align_up(o + (size_t)N * N * 8, 256);
+    // the row maxima are last used by the last product, D is formed after it
+    L.D = L.rmax = o;
+    o = align_up(o + std::max((size_t)N * N * 8, 2 * ld * 8), 256);
     L.q = o;      o = align_up(o + (size_t)(N / 4 + 1) * 8, 256);
     L.total = o;
     return L;
@@ -207,16 +211,34 @@ struct sp2_server {
     void build_group();
 };
 
+// Most product tiles of a group before further systems wait to join it (at
+// least one system runs): four rounds over the two workgroups of each CU keep
+// the chip busy, and with fewer systems side by side the first ones finish,
+// and their results leave for the host, while the others compute (24 requests
+// of N = 128-2048: 47 ms without a limit, 42 at 1024-2048, 45 at 3072, 47 at 600).
+constexpr int kGroupFill = 2048;
+
+static int group_tiles(int N) { return tri_tiles((int)(align_up((size_t)N, kTile) / kGroupTile)); }
+
 static bool fits_int8(int N) { return N >= 2 && N <= 65536; }
 
+// The started systems, largest first (a run's last tiles are then its
+// shortest), and the cut of their tiles into XCD runs of equal work.
 void sp2_server::build_group() {
     GroupDesc& g = *g_host;
-    int n = 0, toff = 0, roff = 0;
-    for (int s = 0; s < (int)slots.size(); ++s) {
+    std::vector<int> order;
+    for (int s = 0; s < (int)slots.size(); ++s)
+        if (slots[s] && slots[s]->started) order.push_back(s);
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return slots[a]->N > slots[b]->N; });
+    int n = 0, toff = 0, boff = 0;
+    double work = 0.0;
+    // a tile's K loop and its epilogue, the latter worth about 400 columns (0 to
+    // 900 made no difference)
+    auto tile_work = [](int ld) { return ld + 400.0; };
+    for (int s : order) {
         Request* r = slots[s];
-        if (!r || !r->started) continue;
         const int ld = (int)align_up((size_t)r->N, kTile);
-        const int nt = ld / kTile;
+        const int nt = ld / kGroupTile, nb = ld / 32;
         char* b = arena.base + r->off;
         SysView& v = g.sys[n];
         v.buf0 = reinterpret_cast<double*>(b + r->L.X);
@@ -224,6 +246,7 @@ void sp2_server::build_group() {
         v.digits = reinterpret_cast<int8_t*>(b + r->L.digits);
         v.scale = reinterpret_cast<double*>(b + r->L.scale);
         v.part = reinterpret_cast<double*>(b + r->L.part);
+        v.rmax = reinterpret_cast<unsigned long long*>(b + r->L.rmax);
         v.st = st_dev + s;
         v.ld = ld;
         v.ctrl.n_occ = (double)r->n_occ;
@@ -236,16 +259,31 @@ void sp2_server::build_group() {
         v.ctrl.mixed = 1;
         v.ctrl.total_blocks = 0.0;
         g.tile_off[n] = toff;
-        g.row_off[n] = roff;
-        toff += nt * (nt + 1) / 2;
-        roff += ld / 4;
+        g.blk_off[n] = boff;
+        toff += tri_tiles(nt);
+        boff += tri_tiles(nb);
+        work += tri_tiles(nt) * tile_work(ld);
         ++n;
     }
     g.tile_off[n] = toff;
-    g.row_off[n] = roff;
+    g.blk_off[n] = boff;
     g.nsys = n;
     g.total_tiles = toff;
-    g.total_rowq = roff;
+    g.total_blks = boff;
+    // run x ends where the work before it reaches (x + 1) / 8 of the whole
+    double before = 0.0;
+    int x = 0;
+    g.xcd_off[0] = 0;
+    for (int k = 0; k < n; ++k) {
+        const int T = g.tile_off[k + 1] - g.tile_off[k];
+        const double tw = tile_work(g.sys[k].ld);
+        while (x + 1 < kXcds && before + T * tw >= (x + 1) * work / kXcds) {
+            const int in = std::min(T, (int)std::ceil(((x + 1) * work / kXcds - before) / tw));
+            g.xcd_off[++x] = g.tile_off[k] + std::max(in, 0);
+        }
+        before += T * tw;
+    }
+    while (x < kXcds) g.xcd_off[++x] = toff;
 }
 
 bool sp2_server::admit_locked(std::vector<Request*>& fresh) {
@@ -306,7 +344,8 @@ sp2_status sp2_server::start_system(Request* r) {
     if (launch_check_h(H, N, chk, &nchk, stream) != hipSuccess) return SP2_EDEVICE;
     if (launch_gershgorin(H, N, part, &ns, stream) != hipSuccess) return SP2_EDEVICE;
     if (launch_bounds(part, ns, chk, nchk, st, stream) != hipSuccess) return SP2_EDEVICE;
-    if (launch_init(H, N, ld, X0, st, part, &ns, stream) != hipSuccess) return SP2_EDEVICE;
+    if (launch_init(H, N, ld, X0, st, part, &ns, stream, reinterpret_cast<unsigned long long*>(b + r->L.rmax)) !=
+        hipSuccess) return SP2_EDEVICE;
     if (launch_ctrl_init(part, ns, st, a, stream) != hipSuccess) return SP2_EDEVICE;
     return SP2_OK;
 }
@@ -343,7 +382,7 @@ sp2_status sp2_server::retire(std::vector<Request*>& finished) {
             r->status = h.done == 3 ? SP2_ENOCONV : (h.done == 4 ? SP2_EGAP : (h.done == 5 ? SP2_EINVAL : SP2_OK));
         bool issued = false;
         if (r->status == SP2_OK && (h.done == 1 || h.done == 2)) {
-            issued = launch_finalize(X0, X0 + (size_t)ld * ld, ld, N, D, st_dev + r->slot, stream) == hipSuccess &&
+            issued = launch_finalize_upper(X0, X0 + (size_t)ld * ld, ld, N, D, st_dev + r->slot, stream) == hipSuccess &&
                      (N % 4 != 0 || launch_mulliken(D, N / 4, 4.0, q, stream) == hipSuccess) &&
                      hipEventRecord(r->ev_up, stream) == hipSuccess &&
                      hipStreamWaitEvent(copy, r->ev_up, 0) == hipSuccess &&
@@ -435,8 +474,13 @@ void sp2_server::loop() {
             uploading.push_back(r);
             if (rc == SP2_OK) rc = begin_upload(r);
         }
-        // systems whose H has landed start and join the group
+        // systems whose H has landed start and join the group, in order of
+        // arrival while the group has room
+        int tiles = 0;
+        for (Request* r : slots)
+            if (r && r->started) tiles += group_tiles(r->N);
         for (auto it = uploading.begin(); rc == SP2_OK && it != uploading.end();) {
+            if (tiles > 0 && tiles + group_tiles((*it)->N) > kGroupFill) break;
             const hipError_t e = hipEventQuery((*it)->ev_up);
             if (e == hipErrorNotReady) {
                 ++it;
@@ -447,6 +491,7 @@ void sp2_server::loop() {
                 break;
             }
             (*it)->started = true;
+            tiles += group_tiles((*it)->N);
             group_dirty = true;
             it = uploading.erase(it);
         }
@@ -550,14 +595,14 @@ sp2_status sp2_server_create(sp2_ctx* ctx, const sp2_server_options* opt, sp2_se
     // capture one tick: iters_per_tick x (grouped encode, product, control)
     ok = hipMemcpy(s->g_dev, s->g_host, sizeof(GroupDesc), hipMemcpyHostToDevice) == hipSuccess;
     // make the lazily set kernel attributes happen outside the capture
-    ok = ok && launch_int8x_grouped(o.slices, o.levels, s->g_dev, 256, s->stream) == hipSuccess;
+    ok = ok && launch_int8x_grouped(o.slices, o.levels, s->g_dev, s->stream) == hipSuccess;
     ok = ok && launch_ctrl_step_grouped(s->g_dev, s->stream) == hipSuccess;
     ok = ok && hipStreamSynchronize(s->stream) == hipSuccess;
     hipGraph_t g = nullptr;
     ok = ok && hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
     if (ok) {
         for (int k = 0; k < o.iters_per_tick && ok; ++k) {
-            ok = launch_int8x_grouped(o.slices, o.levels, s->g_dev, 256, s->stream) == hipSuccess;
+            ok = launch_int8x_grouped(o.slices, o.levels, s->g_dev, s->stream) == hipSuccess;
             ok = ok && launch_ctrl_step_grouped(s->g_dev, s->stream) == hipSuccess;
         }
         ok = (hipStreamEndCapture(s->stream, &g) == hipSuccess) && ok;

@@ -86,21 +86,27 @@ struct SysView {
     double* scale;
     double* part;
     State* st;
+    unsigned long long* rmax;   // 2 x ld row maxima of |X| (bit patterns), one row per X buffer
     int ld;
     int pad_;
     CtrlArgs ctrl;
 };
 
 // Work description of a grouped launch (device resident, rewritten by the
-// host between ticks).  tile_off / row_off are prefix sums of each system's
-// upper-triangular 128 x 128 tiles and of its encode work items (ld / 4).
+// host between ticks).  tile_off / blk_off are prefix sums of each system's
+// upper-triangular 64 x 64 product tiles and of its upper 32 x 32
+// encode blocks.  The tiles are cut into one contiguous run per XCD, [xcd_off[x],
+// xcd_off[x + 1]), of about equal work.
+constexpr int kXcds = 8;
+constexpr int kGroupTile = 64;
 struct GroupDesc {
     int nsys;
     int total_tiles;
-    int total_rowq;
+    int total_blks;
     int pad_;
     int tile_off[kMaxGroup + 1];
-    int row_off[kMaxGroup + 1];
+    int blk_off[kMaxGroup + 1];
+    int xcd_off[kXcds + 1];
     SysView sys[kMaxGroup];
 };
 

@@ -91,8 +91,8 @@ hipError_t launch_bf16x2_encode(SplitScratch& s, const double* buf0, const doubl
 hipError_t launch_bf16x2_gemm(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                               int* nslots, hipStream_t stream);
 
-// Grouped encode + product over every system of g (fixed grids: 1024 encode
-// workgroups, gemm_blocks product workgroups), for the serving loop.
-hipError_t launch_int8x_grouped(int slices, int levels, const GroupDesc* g, int gemm_blocks, hipStream_t stream);
+// Grouped upper-only encode + product over every system of g (fixed grids),
+// for the serving loop.
+hipError_t launch_int8x_grouped(int slices, int levels, const GroupDesc* g, hipStream_t stream);
 
 }  // namespace sp2

@@ -170,3 +170,22 @@ def test_server_largest_requests_against_oracle(ctx):
         say(f"  N={N}: products {sm['iterations']} (oracle {ref.iterations}), err/sqrtN {err:.2e}, max|dq| {dq:.2e}")
         assert np.array_equal(Da, Dm) and np.array_equal(qa, qm)
         assert err <= 1e-6 and dq <= 1e-6
+
+
+@pytest.mark.parametrize("n_atoms,recipe", [(875, {"slices": 4, "levels": 5}), (875, {"slices": 6})])
+def test_served_tiles_equal_the_large_output_tile(ctx, n_atoms, recipe):
+    """N = 3500: the direct solve runs 128 x 128 output tiles, the server 64 x 64
+    (a run of them per XCD, beside a small system's); the digit sums are exact
+    and the update's arithmetic the same, so D is the same bit for bit."""
+    import torch
+    import paper_1203_6836_amd as p
+    say(f"case served tiles N={4 * n_atoms} {recipe}")
+    H, small = request_H(n_atoms, 41), request_H(33, 42)
+    srv = p.Server(ctx, max_slots=3, **recipe)
+    tk = [(srv.sp2_server_submit(h, h.shape[0] // 2), h) for h in (small, H, small)]
+    out = [srv.sp2_server_wait(t, h.shape[0]) for t, h in tk]
+    srv.close()
+    for (_, h), (D, _, st) in zip(tk, out):
+        Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(h).cuda(), h.shape[0] // 2, p.options("int8x", **recipe))
+        assert st["branches"] == sd["branches"]
+        assert np.array_equal(D, Dd.cpu().numpy())
