@@ -877,7 +877,8 @@ template <int S, int NL>
 __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
                                              const State* __restrict__ st, const int8_t* __restrict__ digits,
                                              const double* __restrict__ scale, double* __restrict__ part, int bi,
-                                             int bj, I8Smem64<S>& sm, unsigned long long* __restrict__ rmax_next) {
+                                             int bj, I8Smem64<S>& sm, unsigned long long* __restrict__ rmax_next,
+                                             int slot) {
     using G = I8Stage64<S>;
     constexpr int KS = G::KS, NST = G::NST, PER = G::PER;
     static_assert(NL == S || NL == S + 1, "levels: the triangle or one more");
@@ -1010,7 +1011,7 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
         }
     }
     if (tid == 0) {
-        const int t = tri_index(bi, bj, ld / QT);
+        const int t = slot;
         const double wgt = mirror ? 2.0 : 1.0;
         part[3 * t + 0] = (sm.e.red[0][0] + sm.e.red[0][1]) + (sm.e.red[0][2] + sm.e.red[0][3]);
         part[3 * t + 1] = wgt * ((sm.e.red[1][0] + sm.e.red[1][1]) + (sm.e.red[1][2] + sm.e.red[1][3]));
@@ -1030,7 +1031,38 @@ __global__ __launch_bounds__(256, 2) void k_gemm_int8x_t64(double* __restrict__ 
     I8Smem64<S>& sm = *reinterpret_cast<I8Smem64<S>*>(smem_raw);
     int bi, bj;
     tile_of_block(blockIdx.x, ld / QT, tile_group, bi, bj);
-    int8x_tile64<S, NL>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, rmax + (size_t)(1 - st->cur) * ld);
+    int8x_tile64<S, NL>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, rmax + (size_t)(1 - st->cur) * ld,
+                        tri_index(bi, bj, ld / QT));
+}
+
+// The 128 x 128 tiles of a last round that would leave at least half of the CUs
+// idle (visiting positions t_full .. T - 1), as four 64 x 64 tiles each: sub-tile
+// 0 takes the tile's partial slot, the others slots from T on; the one below
+// the diagonal of a diagonal tile has none of the sums.  Against K chunks with
+// a sum and an epilogue launch behind them, per product with its encode (4
+// planes, 5 levels): N = 4096 (16 tiles left of 528) 413 -> 394 us, 4224 (33 of
+// 561) 438 -> 408.
+template <int S, int NL>
+__global__ __launch_bounds__(256, 2) void k_gemm_int8x_left(double* __restrict__ buf0, double* __restrict__ buf1,
+                                                            int ld, const State* __restrict__ st,
+                                                            const int8_t* __restrict__ digits,
+                                                            const double* __restrict__ scale,
+                                                            double* __restrict__ part,
+                                                            unsigned long long* __restrict__ rmax, int tile_group,
+                                                            int t_full) {
+    if (st->done || st->phase != 1) return;
+    extern __shared__ __align__(16) int8_t smem_raw[];
+    I8Smem64<S>& sm = *reinterpret_cast<I8Smem64<S>*>(smem_raw);
+    const int nt = ld / QB, p = blockIdx.x >> 2, sub = blockIdx.x & 3;
+    int bi, bj;
+    order_tile(t_full + p, nt, tile_group, bi, bj);
+    const int slot = sub == 0 ? tri_index(bi, bj, nt) : nt * (nt + 1) / 2 + 3 * p + sub - 1;
+    if (bi == bj && sub == 2) {
+        if (threadIdx.x < 3) part[3 * slot + threadIdx.x] = 0.0;
+        return;
+    }
+    int8x_tile64<S, NL>(buf0, buf1, ld, st, digits, scale, part, 2 * bi + (sub >> 1), 2 * bj + (sub & 1), sm,
+                        rmax + (size_t)(1 - st->cur) * ld, slot);
 }
 
 // order_tile with one step per super-tile row instead of one per super-tile
@@ -1239,7 +1271,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_int8x_grouped(const GroupDesc* 
         int bi, bj;
         order_tile(item - g->tile_off[s], v.ld / QT, 16, bi, bj);
         int8x_tile64<S, NL>(v.buf0, v.buf1, v.ld, v.st, v.digits, v.scale, v.part, bi, bj, sm,
-                            v.rmax + (size_t)(1 - v.st->cur) * v.ld);
+                            v.rmax + (size_t)(1 - v.st->cur) * v.ld, tri_index(bi, bj, v.ld / QT));
         __syncthreads();
     }
 }
@@ -1258,6 +1290,34 @@ int device_cus() {
     return n;
 }
 
+// Tiles of a dense product's last round that are handed out in pieces: when they
+// would leave at least half of the CUs idle and a tile's K loop covers at least
+// 4096 columns (shorter tiles cost less than what the pieces add).
+static int left_tiles(const SplitScratch& s, int ld) {
+    const int nt = ld / QB, cus = device_cus(), r = nt * (nt + 1) / 2 % cus;
+    return s.tail_split != 0 && ld / QK >= 128 && 2 * r <= cus ? r : 0;
+}
+
+// Whether they are 64 x 64 pieces (upper-only products): up to four rounds of
+// tiles.  Beyond, the chip is at its power limit and the pieces' operand
+// traffic costs what their balance gives (N = 8192: 0.6 % slower than chunks).
+static bool left_in_pieces(int ld) { return tri_tiles(ld / QB) < 4 * device_cus(); }
+
+template <int S, int NL>
+static hipError_t launch_left(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
+                              hipStream_t stream, int r) {
+    const size_t lds = sizeof(I8Smem64<S>);
+    static std::atomic<unsigned long long> attr_done{0};
+    hipError_t e = once_per_device(attr_done, [&] {
+        return hipFuncSetAttribute((const void*)k_gemm_int8x_left<S, NL>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   (int)lds);
+    });
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_gemm_int8x_left<S, NL>), dim3(4 * r), dim3(256), lds, stream, buf0, buf1, ld, st, s.digits,
+                       s.scale, part, s.rmax, s.tile_group, tri_tiles(ld / QB) - r);
+    return hipGetLastError();
+}
+
 template <int S, int NL, bool THR, bool UPPER, int C = 0>
 static hipError_t launch_tile_kernel(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                                      hipStream_t stream, const int* env, int when_full = 0) {
@@ -1274,23 +1334,21 @@ static hipError_t launch_tile_kernel(SplitScratch& s, double* buf0, double* buf1
         return r;
     });
     if (e != hipSuccess) return e;
-    // Tiles of a last wave that would leave at least half of the CUs idle
-    // are split along K into nsplit <= 8 chunks (wave quantisation of the
-    // tail), when a tile's K loop covers at least 4096 columns: shorter tiles
-    // cost less than summing their chunks.
+    // The left tiles: 64 x 64 pieces, else nsplit <= 8 chunks along K.
     int t_full = T, nsplit = 1;
-    if (!THR && s.tail_split != 0 && s.tail_acc && ld / QK >= 128) {
-        const int cus = device_cus();
-        const int r = T % cus;
-        if (r > 0 && 2 * r <= cus) {
-            nsplit = std::min(8, cus / r);
-            if (nsplit >= 2 && (size_t)r * nsplit * NL * 2 * 16 * 512 * sizeof(int) <= s.tail_bytes) t_full = T - r;
-            else nsplit = 1;
-        }
+    const int r = THR ? 0 : left_tiles(s, ld);
+    const bool pieces = UPPER && r > 0 && left_in_pieces(ld);
+    if (pieces) {
+        t_full = T - r;
+    } else if (r > 0 && s.tail_acc) {
+        nsplit = std::min(8, device_cus() / r);
+        if (nsplit >= 2 && (size_t)r * nsplit * NL * 2 * 16 * 512 * sizeof(int) <= s.tail_bytes) t_full = T - r;
+        else nsplit = 1;
     }
-    const int grid = t_full + (T - t_full) * nsplit;
+    const int grid = t_full + (pieces ? 0 : (T - t_full) * nsplit);
     hipLaunchKernelGGL((k_gemm_int8x<S, NL, THR, UPPER, C>), dim3(grid), dim3(512), lds, stream, buf0, buf1, ld, st,
                        s.digits, s.scale, part, env, s.rmax, s.tile_group, t_full, nsplit, s.tail_acc, when_full);
+    if (pieces) return launch_left<S, NL>(s, buf0, buf1, ld, st, part, stream, r);
     if (t_full < T) {
         hipLaunchKernelGGL(k_chunk_sum<NL>, dim3((T - t_full) * kChunkSumParts), dim3(256), 0, stream, s.tail_acc,
                            nsplit, st, when_full);
@@ -1484,8 +1542,8 @@ hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double
 
 hipError_t launch_int8x_gemm(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                              int* nslots, hipStream_t stream, const int* env) {
-    const int nt = ld / (s.upper && !env && use_tile64(ld) ? QT : QB);
-    *nslots = nt * (nt + 1) / 2;
+    const bool small = s.upper && !env && use_tile64(ld);
+    *nslots = tri_tiles(ld / (small ? QT : QB)) + (s.upper && !env && !small && left_in_pieces(ld) ? 3 * left_tiles(s, ld) : 0);
     const bool next = s.levels == s.slices + 1;
     if (!next && s.levels != s.slices) return hipErrorInvalidValue;
     switch (s.slices) {

@@ -189,3 +189,21 @@ def test_served_tiles_equal_the_large_output_tile(ctx, n_atoms, recipe):
         Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(h).cuda(), h.shape[0] // 2, p.options("int8x", **recipe))
         assert st["branches"] == sd["branches"]
         assert np.array_equal(D, Dd.cpu().numpy())
+
+
+@pytest.mark.parametrize("n_atoms,recipe", [(1021, {"slices": 4, "levels": 5}), (1053, {"slices": 5}), (1280, {"slices": 4})])
+def test_tiles_left_over_in_the_last_round(ctx, n_atoms, recipe):
+    """Direct solves of 128 x 128 tiles whose last round has few of them run
+    these as 64 x 64 pieces: N = 4084 (ragged, 16 tiles left of 528 on 256 CUs),
+    4212 (49 of 561, a diagonal tile among them) and 5120 (52 of 820).  The
+    server runs 64 x 64 tiles throughout; D is the same bit for bit."""
+    import torch
+    import paper_1203_6836_amd as p
+    say(f"case left tiles N={4 * n_atoms} {recipe}")
+    H = request_H(n_atoms, 51)
+    srv = p.Server(ctx, max_slots=2, **recipe)
+    D, _, st = srv.sp2_server_wait(srv.sp2_server_submit(H, 2 * n_atoms), H.shape[0])
+    srv.close()
+    Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(H).cuda(), 2 * n_atoms, p.options("int8x", **recipe))
+    assert st["branches"] == sd["branches"]
+    assert np.array_equal(D, Dd.cpu().numpy())
