@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <map>
 #include <tuple>
@@ -14,6 +15,7 @@
 #include <sstream>
 #include <cstring>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/sp2qmd.h"
@@ -64,7 +66,7 @@ struct sp2_ctx {
     size_t partcap = 0;
     State* st = nullptr;      // two records (folded control alternates between them)
     State* st_host = nullptr; // pinned
-    int* progress = nullptr;  // pinned, written by the folded control step
+    int* progress = nullptr;  // pinned, written by the control steps
     double* scal = nullptr;   // device scalars
     double* scal_host = nullptr;
     double* chk = nullptr;    // H check partials (2 per check workgroup)
@@ -501,11 +503,37 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
         HIPCHK(c, launch_init(H, N, ld, buf0, c->st, part, &ns, st, upper ? c->split.rmax : nullptr));
     HIPCHK(c, launch_ctrl_init(part, ns, c->st, a, st));
 
+    // The host reads no state back before the end: each control step writes the
+    // device's progress to host memory, and the host stays a few products
+    // ahead of it, so the stream never runs empty between products and a
+    // finished solve has at most that many empty products behind it.  It
+    // read the state back after 24 products and every 8 from then on: with it
+    // and the dense tile kernels launched always, a thresholded solve of
+    // N = 16384 took 10.7 ms, now 10.3; dense solves are level.
+    volatile int* progress = c->progress;
+    *progress = 0;
+    int seen = 0;   // the last progress word read
+    // Product g has been launched: wait until the device is at most `ahead`
+    // products behind (the stream running empty or failing ends the wait as well).
+    auto follow = [&](int g, int ahead) -> hipError_t {
+        for (unsigned spin = 1;; ++spin) {
+            seen = *progress;
+            if (progress_done(seen) || g - progress_products(seen) <= ahead) return hipSuccess;
+            if (spin % 65536 == 0) {
+                const hipError_t q = hipStreamQuery(st);
+                if (q == hipSuccess) {
+                    seen = *progress;
+                    return hipSuccess;
+                }
+                if (q != hipErrorNotReady) return q;
+                (void)hipGetLastError();   // not an error of the next launch
+                std::this_thread::sleep_for(std::chrono::microseconds(20));
+            }
+        }
+    };
+
     // Folded control (dense FP64 products on 32 x 32 tiles, dense int8 products
-    // on 64 x 64 tiles): one launch per FP64 product, two per int8 product, and
-    // no read-back until the end.  The host stays kFoldAhead products ahead of
-    // the device's progress, so a finished solve has at most that many empty
-    // products behind it.
+    // on 64 x 64 tiles): one launch per FP64 product, two per int8 product.
     const int fold_slots = o.tau > 0.0 || c->profile ? 0
                            : f64_small && o.precision == SP2_PREC_FP64
                                ? (tri_tiles(ld / 32) <= kFoldSlots ? tri_tiles(ld / 32) : 0)
@@ -514,10 +542,8 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     State* stp = c->st;   // the current record
     if (fold_slots > 0) {
         constexpr int kFoldAhead = 6;
-        volatile int* progress = c->progress;
-        *progress = 0;
-        int g = 0, done = 0;
-        for (; g < o.max_iter && !done; ++g) {
+        int g = 0;
+        for (; g < o.max_iter && !progress_done(seen); ++g) {
             FoldArgs f;
             f.part = part + (upper ? 0 : (size_t)((g + 1) & 1) * 3 * fold_slots);
             f.in = stp;
@@ -534,37 +560,19 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
                 HIPCHK(c, launch_gemm_f64_folded(buf0, buf1, ld, f, part + (size_t)(g & 1) * 3 * fold_slots, st));
                 if (g > 0) stp = f.out;
             }
-            // wait until the device is at most kFoldAhead products behind (the
-            // stream running empty or failing ends the wait as well)
-            for (unsigned spin = 1;; ++spin) {
-                const int v = *progress;
-                done = v & 7;
-                if (done || g - (v >> 3) <= kFoldAhead) break;
-                if (spin % 65536 == 0) {
-                    const hipError_t q = hipStreamQuery(st);
-                    if (q == hipSuccess) break;
-                    if (q != hipErrorNotReady) HIPCHK(c, q);
-                    (void)hipGetLastError();   // not an error of the next launch
-                }
-            }
+            HIPCHK(c, follow(g, kFoldAhead));
         }
-        if (!done)   // the last product's result
-            HIPCHK(c, launch_ctrl_step(part + (upper ? 0 : (size_t)((g - 1) & 1) * 3 * fold_slots), fold_slots, stp, a, st));
-        HIPCHK(c, hipMemcpyAsync(c->st_host, stp, sizeof(State), hipMemcpyDeviceToHost, st));
-        if (done == 0) {
-            HIPCHK(c, hipStreamSynchronize(st));
-            done = c->st_host->done;
-        }
-        if (done == 1 || done == 2)
-            HIPCHK(c, upper ? launch_finalize_upper(buf0, buf1, ld, N, D, stp, st)
-                            : launch_finalize(buf0, buf1, ld, N, D, stp, st));
-    }
-    int launched = fold_slots > 0 ? o.max_iter : 0;
-    while (launched < o.max_iter) {
-        const int chunk = std::min(launched == 0 ? 24 : 8, o.max_iter - launched);
-        for (int k = 0; k < chunk; ++k) {
-            const int g = launched + k;
+        if (!progress_done(seen))   // the last product's result
+            HIPCHK(c, launch_ctrl_step(part + (upper ? 0 : (size_t)((g - 1) & 1) * 3 * fold_slots), fold_slots, stp, a,
+                                       c->progress, g, st));
+    } else {
+        // ahead: 3 products of 50 us and more cover the host's launches and
+        // the word's way; the empty products at the end cost 3 us a kernel
+        constexpr int kAhead = 3;
+        bool dense = dense_switch;
+        for (int g = 0; g < o.max_iter && !progress_done(seen); ++g) {
             hipEvent_t* pe = c->profile ? &c->pev[5 * g] : nullptr;
+            c->split.dense_switch = dense;
             if (pe) HIPCHK(c, hipEventRecord(pe[0], st));
             if (int8x || bf16x) HIPCHK(c, launch_split_encode(c->split, buf0, buf1, ld, c->st, st));
             if (bf16x || fp32) HIPCHK(c, launch_encode_f32(buf0, buf1, ld, c->st, c->split.x32, st));
@@ -579,20 +587,29 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
             if (pe) HIPCHK(c, hipEventRecord(pe[3], st));
             if (o.tau > 0.0)
                 HIPCHK(c, launch_block_threshold(buf0, buf1, ld, N, o.tau, o.threshold, c->st, part, &ns, 0, st,
-                                                 env, tz, tz ? tz + (size_t)2 * tri_tiles(nt) : nullptr,
-                                                 dense_switch));
+                                                 env, tz, tz ? tz + (size_t)2 * tri_tiles(nt) : nullptr, dense));
             if (pe) HIPCHK(c, hipEventRecord(pe[4], st));
-            HIPCHK(c, launch_ctrl_step(part, ns, c->st, a, st));
+            // The dense tile kernels (17 us a product where they find
+            // nothing to do) are launched behind the list's while the kept
+            // fraction is unknown or within a factor of 8 of dense_fill, and
+            // the control step switches to them only for a product that has them.
+            dense = dense_switch &&
+                    (progress_products(seen) == 0 || progress_fill(seen) >= o.dense_fill / 8.0 - 1.0 / 256.0);
+            a.dense_fill = dense ? o.dense_fill : 2.0;
+            HIPCHK(c, launch_ctrl_step(part, ns, c->st, a, c->progress, g + 1, st));
+            HIPCHK(c, follow(g, kAhead));
         }
-        launched += chunk;
-        HIPCHK(c, hipMemcpyAsync(c->st_host, c->st, sizeof(State), hipMemcpyDeviceToHost, st));
-        HIPCHK(c, hipStreamSynchronize(st));
-        if (c->st_host->done) break;
     }
+    HIPCHK(c, hipMemcpyAsync(c->st_host, stp, sizeof(State), hipMemcpyDeviceToHost, st));
+    int done = progress_done(seen);
+    if (done == 0) {
+        HIPCHK(c, hipStreamSynchronize(st));
+        done = c->st_host->done;
+    }
+    if (done == 1 || done == 2)
+        HIPCHK(c, upper ? launch_finalize_upper(buf0, buf1, ld, N, D, stp, st)
+                        : launch_finalize(buf0, buf1, ld, N, D, stp, st));
     const State& h = *c->st_host;
-    if (fold_slots == 0 && (h.done == 1 || h.done == 2))
-        HIPCHK(c, upper ? launch_finalize_upper(buf0, buf1, ld, N, D, c->st, st)
-                        : launch_finalize(buf0, buf1, ld, N, D, c->st, st));
     HIPCHK(c, hipEventRecord(c->ev1, st));
     HIPCHK(c, hipEventSynchronize(c->ev1));
     float ms = 0.f;

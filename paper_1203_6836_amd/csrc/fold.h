@@ -165,7 +165,7 @@ __device__ __forceinline__ void fold_decide(const FoldArgs& f, const FoldPart& p
         sh.dec[1] = b;
         if (writer) {
             if (!p.done) ctrl_apply(r, f.out, f.ctrl);
-            __hip_atomic_store(f.progress, f.g << 3 | f.out->done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(f.progress, progress_word(f.g, f.out->done, 0.0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     __syncthreads();

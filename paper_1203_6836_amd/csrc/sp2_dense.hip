@@ -228,23 +228,30 @@ __global__ __launch_bounds__(256) void k_init(const double* __restrict__ H, int 
 
 // --------------------------------------------------------------- control
 // Fixed-order reduction of nslots x 3 partials (trace, ||X||^2, ||P - X||^2).
+template <int NW>
 __device__ void reduce3(const double* __restrict__ part, int nslots, double out[3]) {
     double a = 0.0, b = 0.0, c = 0.0;
-    for (int k = threadIdx.x; k < nslots; k += 256) {
+    for (int k = threadIdx.x; k < nslots; k += 64 * NW) {
         a += part[3 * k];
         b += part[3 * k + 1];
         c += part[3 * k + 2];
     }
-    __shared__ double sh[4];
-    out[0] = block_sum256(a, sh);
-    out[1] = block_sum256(b, sh);
-    out[2] = block_sum256(c, sh);
+    __shared__ double sh[NW];
+    if constexpr (NW == 4) {
+        out[0] = block_sum256(a, sh);
+        out[1] = block_sum256(b, sh);
+        out[2] = block_sum256(c, sh);
+    } else {
+        out[0] = block_sum<NW>(a, sh);
+        out[1] = block_sum<NW>(b, sh);
+        out[2] = block_sum<NW>(c, sh);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_ctrl_init(const double* __restrict__ part, int nslots,
                                                    State* __restrict__ st, CtrlArgs a) {
     double r[3];
-    reduce3(part, nslots, r);
+    reduce3<4>(part, nslots, r);
     if (threadIdx.x == 0) {
         (void)take_fill(st, a);
         st->t1 = r[0];
@@ -259,17 +266,28 @@ __global__ __launch_bounds__(256) void k_ctrl_init(const double* __restrict__ pa
     }
 }
 
+template <int NW>
 __device__ __forceinline__ void ctrl_step_body(const double* __restrict__ part, int nslots, State* __restrict__ st,
                                                const CtrlArgs& a) {
     if (st->done) return;
     double r[3];
-    reduce3(part, nslots, r);
+    reduce3<NW>(part, nslots, r);
     if (threadIdx.x == 0) ctrl_apply(r, st, a);
 }
 
-__global__ __launch_bounds__(256) void k_ctrl_step(const double* __restrict__ part, int nslots,
-                                                   State* __restrict__ st, CtrlArgs a) {
-    ctrl_step_body(part, nslots, st, a);
+// Control step after product g - 1; writes the progress word (progress_word)
+// to host memory.  One workgroup adds all the partials, so its time is a chain
+// of loads: 4 waves up to 2048 triples (4.6-7.5 us), 16 beyond (N = 16384, 8256
+// triples: 15.2 us on 4 waves, 9.5 on 16).
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_ctrl_step(const double* __restrict__ part, int nslots,
+                                                       State* __restrict__ st, CtrlArgs a, int* __restrict__ progress,
+                                                       int g) {
+    ctrl_step_body<NW>(part, nslots, st, a);
+    if (threadIdx.x == 0)
+        __hip_atomic_store(progress,
+                           progress_word(g, st->done, a.total_blocks > 0.0 ? (double)st->fill[g - 1] : 0.0),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // One workgroup per system of a grouped launch.
@@ -277,7 +295,7 @@ __global__ __launch_bounds__(256) void k_ctrl_step_grouped(const GroupDesc* __re
     const int s = blockIdx.x;
     if (s >= g->nsys) return;
     const SysView& v = g->sys[s];
-    ctrl_step_body(v.part, g->tile_off[s + 1] - g->tile_off[s], v.st, v.ctrl);
+    ctrl_step_body<4>(v.part, g->tile_off[s + 1] - g->tile_off[s], v.st, v.ctrl);
 }
 
 // ------------------------------------------------- FP64 symmetric product
@@ -742,8 +760,12 @@ hipError_t launch_ctrl_init(const double* part, int nslots, State* st, CtrlArgs 
     hipLaunchKernelGGL(k_ctrl_init, dim3(1), dim3(256), 0, s, part, nslots, st, a);
     return hipGetLastError();
 }
-hipError_t launch_ctrl_step(const double* part, int nslots, State* st, CtrlArgs a, hipStream_t s) {
-    hipLaunchKernelGGL(k_ctrl_step, dim3(1), dim3(256), 0, s, part, nslots, st, a);
+hipError_t launch_ctrl_step(const double* part, int nslots, State* st, CtrlArgs a, int* progress, int g,
+                            hipStream_t s) {
+    if (nslots <= 2048)
+        hipLaunchKernelGGL(k_ctrl_step<4>, dim3(1), dim3(256), 0, s, part, nslots, st, a, progress, g);
+    else
+        hipLaunchKernelGGL(k_ctrl_step<16>, dim3(1), dim3(1024), 0, s, part, nslots, st, a, progress, g);
     return hipGetLastError();
 }
 hipError_t launch_ctrl_step_grouped(const GroupDesc* g, hipStream_t s) {

@@ -64,11 +64,21 @@ struct CtrlArgs {
 // 1216, 1400 2007 -> 1853.  With 528 triples it was level (FP64 N = 1020) or 3 %
 // slower (int8 N = 2048), as each of 528-2080 workgroups reads them all.
 constexpr int kFoldSlots = 256;
+
+// What a control step tells the host: the products whose result is known,
+// State::done, and the kept fraction of the last of them in 1/256.
+__host__ __device__ inline int progress_word(int products, int done, double fill) {
+    return (int)(fill * 256.0) << 16 | products << 3 | done;
+}
+inline int progress_products(int v) { return (v >> 3) & 0x1fff; }
+inline int progress_done(int v) { return v & 7; }
+inline double progress_fill(int v) { return (double)(v >> 16) / 256.0; }
+
 struct FoldArgs {
     const double* part;   // partials of product g - 1 (nslots triples)
     const State* in;      // state before its result
     State* out;           // state after it
-    int* progress;        // host: (products whose result is known) << 3 | done
+    int* progress;        // host: progress_word
     int nslots;
     int g;                // this product; X_g is in buffer g & 1
     CtrlArgs ctrl;
@@ -263,7 +273,8 @@ hipError_t launch_bounds(const double* part, int nslots, const double* chk, int 
 hipError_t launch_init(const double* H, int N, int ld, double* X0, State* st, double* part,
                        int* nslots, hipStream_t s, unsigned long long* rmax0 = nullptr);
 hipError_t launch_ctrl_init(const double* part, int nslots, State* st, CtrlArgs a, hipStream_t s);
-hipError_t launch_ctrl_step(const double* part, int nslots, State* st, CtrlArgs a, hipStream_t s);
+hipError_t launch_ctrl_step(const double* part, int nslots, State* st, CtrlArgs a, int* progress, int g,
+                            hipStream_t s);   // after product g - 1
 hipError_t launch_ctrl_step_grouped(const GroupDesc* g, hipStream_t s);
 // env (may be null): per 128-row panel p, [env[2p], env[2p+1]] is the range
 // of 32-column blocks holding nonzeros of a thresholded X.
