@@ -416,7 +416,7 @@ static sp2_status sp2_solve(sp2_ctx* c, int N, const double* H, int n_occ, const
         if ((s = f64_tail_buffer(c, ld, o.tail_split, &sc.f64tail, &sc.f64tail_bytes)) != SP2_OK) return s;
     if (o.tau > 0.0) {
         size_t eb = c->envcap;
-        if ((s = grow(c, (void**)&c->env, &eb, env_bytes(ld))) != SP2_OK) return s;
+        if ((s = grow(c, (void**)&c->env, &eb, 2 * env_bytes(ld))) != SP2_OK) return s;
         c->envcap = eb;
         sc.env = c->env;
     }
@@ -424,8 +424,10 @@ static sp2_status sp2_solve(sp2_ctx* c, int N, const double* H, int n_occ, const
     // product does not keep them)
     if (o.tau > 0.0 && int8x && o.fp64_head == 0) {
         size_t zb = c->tzcap;
-        // 2 T flags, then the product's work list (T entries) and its 2 counters
-        if ((s = grow(c, (void**)&c->tz, &zb, ((size_t)3 * tri_tiles(nt) + 2) * sizeof(int))) != SP2_OK) return s;
+        // 2 T flags, then the product's work list (T entries) and its 2
+        // counters, then the block flags of H
+        const size_t hb = (size_t)((N + 31) / 32) * ((N + 31) / 32);
+        if ((s = grow(c, (void**)&c->tz, &zb, ((size_t)3 * tri_tiles(nt) + 2 + hb) * sizeof(int))) != SP2_OK) return s;
         c->tzcap = zb;
         sc.tz = c->tz;
     }
@@ -484,6 +486,10 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     int* tz = sc.tz;
     c->split.env = int8x ? env : nullptr;
     c->split.tz = tz;
+    unsigned* hz = tz ? reinterpret_cast<unsigned*>(tz) + (size_t)3 * tri_tiles(nt) + 2 : nullptr;
+    // the work-list path alternates two env buffers: product g reads the g-th
+    // (mod 2) and clears the other for the threshold pass behind it
+    int* envs[2] = {env, tz ? env + env_bytes(ld) / sizeof(int) : env};
     // thresholded int8 products from the first one on (work-list path): the
     // dense tile kernel takes over while X_n's kept fraction is at least
     // dense_fill
@@ -493,12 +499,12 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     hipStream_t st = c->stream;
     HIPCHK(c, hipEventRecord(c->ev0, st));
     int ns = 0, nchk = 0;
-    HIPCHK(c, launch_check_h(H, N, c->chk, &nchk, st));
-    HIPCHK(c, launch_gershgorin(H, N, part, &ns, st));
+    HIPCHK(c, launch_check_h(H, N, c->chk, &nchk, st, hz));
+    HIPCHK(c, launch_gershgorin(H, N, part, &ns, st, hz));
     HIPCHK(c, launch_bounds(part, ns, c->chk, nchk, c->st, st));
     if (o.tau > 0.0)   // X_0 formed and thresholded in one pass over H
         HIPCHK(c, launch_block_threshold(buf0, buf1, ld, N, o.tau, o.threshold, c->st, part, &ns, 1, st, env, tz,
-                                         nullptr, false, H));
+                                         nullptr, false, H, hz));
     else
         HIPCHK(c, launch_init(H, N, ld, buf0, c->st, part, &ns, st, upper ? c->split.rmax : nullptr));
     HIPCHK(c, launch_ctrl_init(part, ns, c->st, a, st));
@@ -509,7 +515,7 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     // finished solve has at most that many empty products behind it.  It
     // read the state back after 24 products and every 8 from then on: with it
     // and the dense tile kernels launched always, a thresholded solve of
-    // N = 16384 took 10.7 ms, now 10.3; dense solves are level.
+    // N = 16384 went from 10.7 to 10.3 ms; dense solves are level.
     volatile int* progress = c->progress;
     *progress = 0;
     int seen = 0;   // the last progress word read
@@ -573,21 +579,24 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
         for (int g = 0; g < o.max_iter && !progress_done(seen); ++g) {
             hipEvent_t* pe = c->profile ? &c->pev[5 * g] : nullptr;
             c->split.dense_switch = dense;
+            int* env_g = envs[g & 1];
+            c->split.env = int8x ? env_g : nullptr;
+            c->split.env_next = envs[(g + 1) & 1];
             if (pe) HIPCHK(c, hipEventRecord(pe[0], st));
             if (int8x || bf16x) HIPCHK(c, launch_split_encode(c->split, buf0, buf1, ld, c->st, st));
             if (bf16x || fp32) HIPCHK(c, launch_encode_f32(buf0, buf1, ld, c->st, c->split.x32, st));
             if (pe) HIPCHK(c, hipEventRecord(pe[1], st));
             if (f64p)
-                HIPCHK(c, launch_gemm_f64(buf0, buf1, ld, c->st, part, &ns, st, env, tile_group, f64tail,
+                HIPCHK(c, launch_gemm_f64(buf0, buf1, ld, c->st, part, &ns, st, env_g, tile_group, f64tail,
                                           f64tail_bytes, f64c.split_cap, f64_small));
             if (pe) HIPCHK(c, hipEventRecord(pe[2], st));
-            if (int8x || bf16x) HIPCHK(c, launch_split_gemm(c->split, buf0, buf1, ld, c->st, part, &ns, st, env));
+            if (int8x || bf16x) HIPCHK(c, launch_split_gemm(c->split, buf0, buf1, ld, c->st, part, &ns, st, env_g));
             if (bf16x || fp32)
                 HIPCHK(c, launch_gemm_f32(buf0, buf1, ld, c->st, c->split.x32, part, &ns, tile_group, st));
             if (pe) HIPCHK(c, hipEventRecord(pe[3], st));
             if (o.tau > 0.0)
                 HIPCHK(c, launch_block_threshold(buf0, buf1, ld, N, o.tau, o.threshold, c->st, part, &ns, 0, st,
-                                                 env, tz, tz ? tz + (size_t)2 * tri_tiles(nt) : nullptr, dense));
+                                                 envs[(g + 1) & 1], tz, tz ? tz + (size_t)2 * tri_tiles(nt) : nullptr, dense));
             if (pe) HIPCHK(c, hipEventRecord(pe[4], st));
             // The dense tile kernels (17 us a product where they find
             // nothing to do) are launched behind the list's while the kept
@@ -608,6 +617,7 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     }
     if (done == 1 || done == 2)
         HIPCHK(c, upper ? launch_finalize_upper(buf0, buf1, ld, N, D, stp, st)
+                  : tz  ? launch_finalize_tiles(buf0, buf1, ld, N, D, stp, tz, st)
                         : launch_finalize(buf0, buf1, ld, N, D, stp, st));
     const State& h = *c->st_host;
     HIPCHK(c, hipEventRecord(c->ev1, st));

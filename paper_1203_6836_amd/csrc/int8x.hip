@@ -431,13 +431,15 @@ struct I8Smem {
 // only (no mirrored copy below the diagonal) and fold its row and column
 // maxima of |X_{n+1}| into rmax_next (bit patterns of non-negative doubles
 // order like the values, so atomicMax on them is exact and order-free).
+// x_zero (THR): the X_n tile is zero whatever its memory holds.
 template <int S, int NL, bool THR, bool UPPER, int C = 0>
 __device__ __forceinline__ void int8x_tile(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
                            const State* __restrict__ st, const int8_t* __restrict__ digits,
                            const double* __restrict__ scale, double* __restrict__ part, int bi, int bj,
                            I8Smem<S, C>& sm, const int* __restrict__ env,
                            unsigned long long* __restrict__ rmax_next, int kmode = 0, int kc0 = 0,
-                           int kc1 = -1, int* __restrict__ chunk_acc = nullptr, int nchunks = 0) {
+                           int kc1 = -1, int* __restrict__ chunk_acc = nullptr, int nchunks = 0,
+                           bool x_zero = false) {
     const int nt = ld / QB;
     const int t = tri_index(bi, bj, nt);
     const int i0 = bi * QB, j0 = bj * QB;
@@ -686,7 +688,7 @@ __device__ __forceinline__ void int8x_tile(double* __restrict__ buf0, double* __
         // s_i s_j first: the product is then the same for (i, j) and (j, i)
         // (the diagonal tiles form both), so X stays exactly symmetric
         const double p = v * (scale[gi] * sj);
-        const double x = UPPER ? sm.mx.xs[gi - i0][gj - j0] : Xc[(size_t)gi * ld + gj];
+        const double x = UPPER ? sm.mx.xs[gi - i0][gj - j0] : (THR && x_zero ? 0.0 : Xc[(size_t)gi * ld + gj]);
         const double xn = br ? 2.0 * x - p : p;
         Xn[(size_t)gi * ld + gj] = xn;
         if (gi == gj) trc[c] += xn;
@@ -1097,27 +1099,32 @@ __device__ __forceinline__ void order_tile_rows(int t, int nt, int G, int& bi, i
 // ---- thresholded products driven by a work list (int8 from the first product on)
 //
 // Zero-tile flags tz (one row of T upper tiles per X buffer, kept with the
-// threshold pass): a tile whose K range is empty and whose X_n tile is all
-// zero has X_{n+1} = 0 there under either branch.  k_tile_list visits the
-// tiles in the product's G x G super-tile order; such a tile gets zero
-// partials and is left out when its destination tile is already all zero,
-// or is listed for plain zero stores (no reads) when it is not; every other
-// tile is listed for the product.  The list holds (zero_store << 30) |
-// (bi << 15) | bj; list_ctr[0] counts entries, list_ctr[1] hands them out in
-// list order, so whatever the order the work is balanced, and concurrent
-// workgroups work on nearby tiles that share row panels.
-__global__ void k_list_reset(int* __restrict__ list_ctr, const State* __restrict__ st) {
-    if (st->done || st->phase != 1 || st->full_fill) return;
-    if (threadIdx.x < 2) list_ctr[threadIdx.x] = 0;
-}
-
+// threshold pass; a flagged tile is zero whatever its memory holds): a tile
+// whose K range is empty and whose X_n tile is all zero has X_{n+1} = 0 there
+// under either branch.  k_tile_list visits the tiles in the product's G x G
+// super-tile order; such a tile gets its flag and zero partials, every other
+// tile is listed for the product.  The list holds (bi << 15) | bj; list_ctr[0]
+// counts entries (both counters cleared by the encode), list_ctr[1] hands them
+// out in list order, so whatever the order the work is balanced, and
+// concurrent workgroups work on nearby tiles that share row panels.  Also
+// empties the ranges and masks env_next, which the threshold pass behind the
+// product fills (nobody reads them in between).  The first product of a banded
+// N = 16384, which stored zeros to 2 GB of the other buffer: 485 -> 96 us.
 __global__ __launch_bounds__(256) void k_tile_list(const State* __restrict__ st, const int* __restrict__ env,
-                                                   const int* __restrict__ tz, int nt, int tile_group,
-                                                   double* __restrict__ part, int* __restrict__ list,
+                                                   int* __restrict__ env_next, int* __restrict__ tz, int nt,
+                                                   int tile_group, double* __restrict__ part, int* __restrict__ list,
                                                    int* __restrict__ list_ctr) {
-    if (st->done || st->phase != 1 || st->full_fill) return;
+    if (st->done || st->phase != 1) return;
     const int T = nt * (nt + 1) / 2;
     const int pos = blockIdx.x * 256 + threadIdx.x;
+    for (int p = pos; p < nt * mask_words(nt * QB); p += gridDim.x * 256) {
+        if (p < nt) {
+            env_next[2 * p] = 0x7fffffff;
+            env_next[2 * p + 1] = -1;
+        }
+        env_mask(env_next, nt)[p] = 0ull;
+    }
+    if (st->full_fill) return;
     bool listed = false;
     int item = 0;
     if (pos < T) {
@@ -1128,14 +1135,14 @@ __global__ __launch_bounds__(256) void k_tile_list(const State* __restrict__ st,
         const unsigned long long* mk = env_mask(env, nt);
         const int W = mask_words(nt * QB), nbk = nt * QB / QK;
         const bool k_empty = next_common_block(mk + (size_t)bi * W, mk + (size_t)bj * W, 0, nbk) >= nbk;
-        const bool zero_next = k_empty && tz[(size_t)st->cur * T + t] != 0;
-        if (zero_next && tz[(size_t)(1 - st->cur) * T + t] != 0) {
+        if (k_empty && tz[(size_t)st->cur * T + t] != 0) {
             part[3 * t + 0] = 0.0;
             part[3 * t + 1] = 0.0;
             part[3 * t + 2] = 0.0;
+            tz[(size_t)(1 - st->cur) * T + t] = 1;
         } else {
             listed = true;
-            item = ((zero_next ? 1 : 0) << 30) | (bi << 15) | bj;
+            item = (bi << 15) | bj;
         }
     }
     // one atomic per wave
@@ -1155,7 +1162,7 @@ __global__ __launch_bounds__(512) void k_gemm_int8x_list(double* __restrict__ bu
                                                          const int8_t* __restrict__ digits,
                                                          const double* __restrict__ scale,
                                                          double* __restrict__ part, const int* __restrict__ env,
-                                                         int* __restrict__ tz, const int* __restrict__ list,
+                                                         const int* __restrict__ tz, const int* __restrict__ list,
                                                          int* __restrict__ list_ctr) {
     if (st->done || st->phase != 1 || st->full_fill) return;
     extern __shared__ __align__(16) int8_t smem_raw[];
@@ -1166,8 +1173,6 @@ __global__ __launch_bounds__(512) void k_gemm_int8x_list(double* __restrict__ bu
     volatile int& s_k = *reinterpret_cast<int*>(smem_raw);
     const int nt = ld / QB, T = nt * (nt + 1) / 2;
     const int n = list_ctr[0];
-    int* __restrict__ tzn = tz + (size_t)(1 - st->cur) * T;
-    double* __restrict__ Xn = st->cur ? buf0 : buf1;
     for (;;) {
         if (threadIdx.x == 0) s_k = atomicAdd(&list_ctr[1], 1);
         __syncthreads();
@@ -1175,25 +1180,10 @@ __global__ __launch_bounds__(512) void k_gemm_int8x_list(double* __restrict__ bu
         __syncthreads();
         if (k >= n) break;
         const int it = list[k];
-        const int bi = (it >> 15) & 0x7fff, bj = it & 0x7fff;
-        const int t = tri_index(bi, bj, nt);
-        if (it >> 30) {
-            const double2 z = make_double2(0.0, 0.0);
-            for (int e = threadIdx.x; e < QB * QB / 2; e += 512) {
-                const int r = e / (QB / 2), c = 2 * (e % (QB / 2));
-                *reinterpret_cast<double2*>(Xn + (size_t)(bi * QB + r) * ld + bj * QB + c) = z;
-                if (bi != bj) *reinterpret_cast<double2*>(Xn + (size_t)(bj * QB + r) * ld + bi * QB + c) = z;
-            }
-            if (threadIdx.x == 0) {
-                part[3 * t + 0] = 0.0;
-                part[3 * t + 1] = 0.0;
-                part[3 * t + 2] = 0.0;
-                tzn[t] = 1;
-            }
-        } else {
-            int8x_tile<S, NL, true, false>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, env, nullptr);
-            if (threadIdx.x == 0) tzn[t] = 0;
-        }
+        const int bi = it >> 15, bj = it & 0x7fff;
+        const bool x_zero = tz[(size_t)st->cur * T + tri_index(bi, bj, nt)] != 0;
+        int8x_tile<S, NL, true, false>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, env, nullptr, 0, 0, -1,
+                                       nullptr, 0, x_zero);
         __syncthreads();
     }
 }
@@ -1372,9 +1362,8 @@ static hipError_t launch_list_kernel(SplitScratch& s, double* buf0, double* buf1
     if (e != hipSuccess) return e;
     int* list = s.tz + (size_t)2 * T;
     int* ctr = list + T;
-    hipLaunchKernelGGL(k_list_reset, dim3(1), dim3(64), 0, stream, ctr, st);
-    hipLaunchKernelGGL(k_tile_list, dim3((T + 255) / 256), dim3(256), 0, stream, st, env, s.tz, nt, s.tile_group, part,
-                       list, ctr);
+    hipLaunchKernelGGL(k_tile_list, dim3((T + 255) / 256), dim3(256), 0, stream, st, env, s.env_next, s.tz, nt,
+                       s.tile_group, part, list, ctr);
     const int grid = std::min(T, device_cus());
     hipLaunchKernelGGL((k_gemm_int8x_list<S, NL>), dim3(grid), dim3(512), lds, stream, buf0, buf1, ld, st, s.digits, s.scale,
                        part, env, s.tz, list, ctr);
@@ -1446,40 +1435,112 @@ static hipError_t run_int8x(SplitScratch& s, double* buf0, double* buf1, int ld,
     return launch_tile_kernel<S, NL, false, false>(s, buf0, buf1, ld, st, part, stream, nullptr);
 }
 
+// Eight columns j .. j + 7 of a row into its digit blocks.
+template <int S>
+__device__ __forceinline__ void store_digits8(const double4& a, const double4& b, double inv, int W, size_t rowblk,
+                                              int r32, int j, int8_t* __restrict__ digits, size_t plane) {
+    double y[8] = {a.x * inv, a.y * inv, a.z * inv, a.w * inv, b.x * inv, b.y * inv, b.z * inv, b.w * inv};
+    const size_t off = (rowblk + (j >> 5)) * 1024 + r32 * 32 + 16 * (((j >> 4) & 1) ^ dswz(r32)) + (j & 15);
+    unsigned long long packed[S];
+    pack_digits8<S>(y, W, packed);
+#pragma unroll
+    for (int t = 0; t < S; ++t) *reinterpret_cast<unsigned long long*>(digits + t * plane + off) = packed[t];
+}
+__device__ __forceinline__ double abs_max8(const double4& a, const double4& b) {
+    return fmax(fmax(fmax(fabs(a.x), fabs(a.y)), fmax(fabs(a.z), fabs(a.w))),
+                fmax(fmax(fabs(b.x), fabs(b.y)), fmax(fabs(b.z), fabs(b.w))));
+}
+
 // Thresholded X: one wave per padded row, over the columns of its row panel's
 // range of nonzero 32-column blocks only, rounded out to whole K stages the
-// way the product rounds its K range (X is zero outside the range, and no
-// product reads digits outside it).  Same digits as encode_row.  A panel with
-// no nonzero block is read by no product.
+// way the product rounds its K range (no product reads digits outside it);
+// blocks without a nonzero are zeros, read or not.  Same digits as encode_row.
+// A panel with no nonzero block is read by no product.  Ranges of up to 2048
+// columns are held in registers between the maximum and the digits (one read of
+// X instead of two): N = 16384 banded, 65 -> 51 us a product.  With tz (the work-list
+// path) tiles flagged zero may hold anything: the masks leave them out here,
+// and before the dense tile kernel, which reads every X_n tile, zeros are
+// stored.  Also clears the work list's two counters.
 template <int S>
-__global__ __launch_bounds__(256) void k_encode_int8_env(const double* __restrict__ buf0,
-                                                         const double* __restrict__ buf1, int ld,
+__global__ __launch_bounds__(256) void k_encode_int8_env(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
                                                          const State* __restrict__ st,
                                                          int8_t* __restrict__ digits,
-                                                         double* __restrict__ scale, const int* __restrict__ env) {
+                                                         double* __restrict__ scale, const int* __restrict__ env,
+                                                         const int* __restrict__ tz, int* __restrict__ list_ctr) {
     if (st->done || st->phase != 1) return;
+    if (list_ctr && blockIdx.x == 0 && threadIdx.x < 2) list_ctr[threadIdx.x] = 0;
     constexpr int KS = I8Stage<S>::KS;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (st->full_fill) {   // the dense tile kernel reads every K block
-        encode_row<S>(st->cur ? buf1 : buf0, ld, i, lane, digits, scale, 0, ld);
+    const int nt = ld / QB, p = i / QB;
+    double* __restrict__ X = st->cur ? buf1 : buf0;
+    if (st->full_fill) {   // the dense tile kernel reads every K block and X_n tile
+        if (tz) {
+            const int* __restrict__ f = tz + (size_t)st->cur * (nt * (nt + 1) / 2);
+            for (int q = 0; q < nt; ++q)
+                if (f[tri_index(min(p, q), max(p, q), nt)])
+                    *reinterpret_cast<double2*>(X + (size_t)i * ld + q * QB + 2 * lane) = make_double2(0.0, 0.0);
+            // encode_row below reads columns other lanes of this wave stored
+            __threadfence_block();
+        }
+        encode_row<S>(X, ld, i, lane, digits, scale, 0, ld);
         return;
     }
-    const int p = i / QB;
     const int lo = env[2 * p], hi = env[2 * p + 1];
     if (lo > hi) {
         if (lane == 0) scale[i] = 1.0;
         return;
     }
     const int c0 = (lo / KS) * KS * 32, c1 = min(ld, (hi / KS + 1) * KS * 32);
-    encode_row<S>(st->cur ? buf1 : buf0, ld, i, lane, digits, scale, c0, c1);
+    const unsigned long long* __restrict__ mk = env_mask(env, nt) + (size_t)p * mask_words(ld);
+    const double4 z4 = make_double4(0.0, 0.0, 0.0, 0.0);
+    const double* __restrict__ row = X + (size_t)i * ld;
+    const int W = digit_bits(ld, S);
+    const size_t plane = (size_t)ld * ld, rowblk = (size_t)(i >> 5) * (ld >> 5);
+    const int r32 = i & 31;
+    auto kept = [&](int j) { return j < c1 && (mk[j >> 11] >> ((j >> 5) & 63) & 1ull); };
+    auto load = [&](int j, double4& a, double4& b) {
+        a = b = z4;
+        if (kept(j)) {
+            a = *reinterpret_cast<const double4*>(row + j);
+            b = *reinterpret_cast<const double4*>(row + j + 4);
+        }
+    };
+    double m = 0.0, sc;
+    if (c1 - c0 <= 2048) {
+        double4 a[4], b[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) load(c0 + 8 * lane + 512 * c, a[c], b[c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) m = fmax(m, abs_max8(a[c], b[c]));
+        const double inv = row_scale(wred_max(m), &sc);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const int j = c0 + 8 * lane + 512 * c;
+            if (j < c1) store_digits8<S>(a[c], b[c], inv, W, rowblk, r32, j, digits, plane);
+        }
+    } else {
+        double4 a, b;
+        for (int j = c0 + 8 * lane; j < c1; j += 512) {
+            load(j, a, b);
+            m = fmax(m, abs_max8(a, b));
+        }
+        const double inv = row_scale(wred_max(m), &sc);
+        for (int j = c0 + 8 * lane; j < c1; j += 512) {
+            load(j, a, b);
+            store_digits8<S>(a, b, inv, W, rowblk, r32, j, digits, plane);
+        }
+    }
+    if (lane == 0) scale[i] = sc;
 }
 
 template <int S>
 static hipError_t run_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
                              hipStream_t stream, const FoldArgs* f) {
     if (s.env) {
-        hipLaunchKernelGGL(k_encode_int8_env<S>, dim3(ld / 4), dim3(256), 0, stream, buf0, buf1, ld, st, s.digits,
-                           s.scale, s.env);
+        const int nt = ld / QB;
+        hipLaunchKernelGGL(k_encode_int8_env<S>, dim3(ld / 4), dim3(256), 0, stream, const_cast<double*>(buf0),
+                           const_cast<double*>(buf1), ld, st, s.digits, s.scale, s.env, s.tz,
+                           s.tz ? s.tz + (size_t)3 * tri_tiles(nt) : nullptr);
         return hipGetLastError();
     }
     if (s.upper) {

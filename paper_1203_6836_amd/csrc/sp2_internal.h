@@ -202,7 +202,7 @@ __host__ __device__ __forceinline__ unsigned long long* env_mask(int* env, int n
 __host__ __device__ __forceinline__ const unsigned long long* env_mask(const int* env, int nt) {
     return reinterpret_cast<const unsigned long long*>(env + 2 * nt);
 }
-// Env buffer bytes for nt panels of an ld-wide X.
+// Bytes of one env buffer for nt panels of an ld-wide X.
 inline size_t env_bytes(int ld) {
     const int nt = ld / kTile;
     return (size_t)2 * nt * sizeof(int) + (size_t)nt * mask_words(ld) * sizeof(unsigned long long);
@@ -263,10 +263,14 @@ constexpr int kCheckGrid = 2048;   // workgroups (and partial pairs) of the H ch
 constexpr int kDotBlocks = 2048;   // workgroups (and partials) of the trace-of-product kernel
 
 // ---- launchers (sp2_dense.hip) ----
-hipError_t launch_gershgorin(const double* H, int N, double* part, int* nslots, hipStream_t s);
+// hz (may be null): block flags of H from launch_check_h.
+hipError_t launch_gershgorin(const double* H, int N, double* part, int* nslots, hipStream_t s,
+                             const unsigned* hz = nullptr);
 // out[2 b] = max |H_ij - H_ji| (+inf if a non-finite entry was seen),
 // out[2 b + 1] = max |H_ij| over the 32 x 32 tile pairs of workgroup b.
-hipError_t launch_check_h(const double* H, int N, double* out, int* nout, hipStream_t s);
+// With hz non-null (nb^2 words, nb = ceil(N / 32)): hz[br nb + bc] != 0 where
+// block (br, bc) of H holds a nonzero.
+hipError_t launch_check_h(const double* H, int N, double* out, int* nout, hipStream_t s, unsigned* hz = nullptr);
 // Resets the state, sets the Gershgorin bounds and flags an invalid H (done = 5)
 // or a flat spectrum (done = 4).
 hipError_t launch_bounds(const double* part, int nslots, const double* chk, int nchk, State* st, hipStream_t s);
@@ -322,6 +326,10 @@ hipError_t once_per_device(std::atomic<unsigned long long>& done, F set) {
 }
 // compute units of the current device (cached on first use)
 int device_cus();
+// D of a thresholded int8 solve: tiles flagged in tz (2 x T, see
+// launch_block_threshold) are zero whatever their memory holds.
+hipError_t launch_finalize_tiles(const double* buf0, const double* buf1, int ld, int N, double* D, const State* st,
+                                 const int* tz, hipStream_t s);
 hipError_t launch_finalize(const double* buf0, const double* buf1, int ld, int N, double* D,
                            const State* st, hipStream_t s);
 // D from the upper triangle of the result buffer (upper-only int8 products).

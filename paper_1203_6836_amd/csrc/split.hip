@@ -34,7 +34,8 @@ __device__ __forceinline__ void tri_coords_t(int t, int nt, int& bi, int& bj) {
 // (eps_max - eps_min) is formed here from H instead of read from X (zero
 // outside N x N) and every block is written, the mirror of an off-diagonal
 // tile from its upper copy: one pass over H instead of forming X_0 and
-// thresholding it in two.
+// thresholding it in two.  With tz, a tile of X_0 that is all zero after the
+// threshold is flagged and not written (see launch_block_threshold).
 template <bool FROM_H>
 __device__ void threshold_tile(double* __restrict__ X, int ld, int N, double tau, int elem, State* __restrict__ st,
                                double* __restrict__ part, int init, int* __restrict__ env, int* __restrict__ tz,
@@ -65,6 +66,26 @@ __device__ void threshold_tile(double* __restrict__ X, int ld, int N, double tau
                 const int e = lane + 64 * m, r = e >> 5, c = e & 31;
                 const int i = r0 + r, j = c0 + c;
                 vv[s][m] = (i < N && j < N) ? ((i == j ? emax : 0.0) - H[(size_t)i * N + j]) * inv : 0.0;
+            }
+        }
+        if (tz) {
+            bool any = false;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                double ss = 0.0;
+                bool nz = false;
+#pragma unroll
+                for (int m = 0; m < 16; ++m) {
+                    nz = nz || (vv[s][m] != 0.0 && !(fabs(vv[s][m]) < tau));
+                    ss += vv[s][m] * vv[s][m];
+                }
+                ss = wsum64(ss);
+                any = any || (elem ? nz : !(ss < tau * tau));
+            }
+            if (!__syncthreads_or(any)) {
+                if (threadIdx.x < 3) part[3 * t + threadIdx.x] = 0.0;
+                if (threadIdx.x == 0) tz[(size_t)xb * T + t] = 1;
+                return;
             }
         }
     }
@@ -165,10 +186,7 @@ __device__ void threshold_tile(double* __restrict__ X, int ld, int N, double tau
         if (init) part[3 * t + 2] = 0.0;
         const int k = s_k[0] + s_k[1] + s_k[2] + s_k[3];
         atomicAdd(&st->kept, (unsigned long long)(mirror ? 2 * k : k));
-        if (tz) {
-            tz[(size_t)xb * T + t] = k == 0 ? 1 : 0;
-            if (init) tz[(size_t)T + t] = 0;
-        }
+        if (tz) tz[(size_t)xb * T + t] = k == 0 ? 1 : 0;
         if (env) {
             int e[4] = {s_env[0][0], s_env[0][1], s_env[0][2], s_env[0][3]};
             for (int q = 1; q < 4; ++q) {
@@ -209,16 +227,6 @@ __global__ __launch_bounds__(256) void k_block_threshold(double* __restrict__ bu
     const int nt = ld / 128;
     const int t = blockIdx.x;
     const int T = nt * (nt + 1) / 2;
-    // a tile the product wrote as all zero: nothing to threshold or record
-    // (after the dense tile kernel, which writes every tile and no flags,
-    // every tile is thresholded and its flag rewritten)
-    if (tz && !init && !when_full && tz[(size_t)xb * T + t]) {
-        if (threadIdx.x == 0) {
-            part[3 * t + 0] = 0.0;
-            part[3 * t + 1] = 0.0;
-        }
-        return;
-    }
     int bi, bj;
     tri_coords_t(t, nt, bi, bj);
     threshold_tile<false>(xb == 0 ? buf0 : buf1, ld, N, tau, elem, st, part, init, env, tz, xb, T, t, bi, bj,
@@ -226,23 +234,35 @@ __global__ __launch_bounds__(256) void k_block_threshold(double* __restrict__ bu
 }
 
 // The X_0 pass of a thresholded solve, X_0 formed from H (N x N) on the fly.
+// With hz (the block flags of the H check) and tz, an off-diagonal tile whose H
+// is all zero is flagged without reading or writing it: N = 16384 banded, 1042
+// -> 78 us.
 __global__ __launch_bounds__(256) void k_block_threshold_x0(const double* __restrict__ H, double* __restrict__ X,
                                                             int ld, int N, double tau, int elem,
                                                             State* __restrict__ st, double* __restrict__ part,
-                                                            int* __restrict__ env, int* __restrict__ tz) {
+                                                            int* __restrict__ env, int* __restrict__ tz,
+                                                            const unsigned* __restrict__ hz) {
     if (st->done) return;
     const int nt = ld / 128;
     const int t = blockIdx.x;
     const int T = nt * (nt + 1) / 2;
     int bi, bj;
     tri_coords_t(t, nt, bi, bj);
+    if (hz && bi != bj) {
+        const int nb = (N + 31) / 32, l = threadIdx.x & 15, r = 4 * bi + (l >> 2), c = 4 * bj + (l & 3);
+        if (!__any(r < nb && c < nb && hz[(size_t)r * nb + c] != 0u)) {
+            if (threadIdx.x < 3) part[3 * t + threadIdx.x] = 0.0;
+            if (threadIdx.x == 0) tz[t] = 1;
+            return;
+        }
+    }
     threshold_tile<true>(X, ld, N, tau, elem, st, part, 1, env, tz, 0, T, t, bi, bj, H);
 }
 
-// Thresholded int8 products driven by a work list (entries (zero_store << 30)
-// | (bi << 15) | bj, list_ctr[0] of them): only the tiles the product
-// computed are visited.  Every other tile is all zero, with zero partials
-// and its flag set, by the list kernel or by the product's zero stores.
+// Thresholded int8 products driven by a work list (entries (bi << 15) | bj,
+// list_ctr[0] of them): only the tiles the product computed are visited.
+// Every other tile is all zero, with zero partials and its flag set by the
+// list kernel.
 __global__ __launch_bounds__(256) void k_block_threshold_list(double* __restrict__ buf0, double* __restrict__ buf1,
                                                               int ld, int N, double tau, int elem,
                                                               State* __restrict__ st, double* __restrict__ part,
@@ -256,8 +276,7 @@ __global__ __launch_bounds__(256) void k_block_threshold_list(double* __restrict
     const int n = list_ctr[0];
     for (int k = blockIdx.x; k < n; k += gridDim.x) {
         const int it = list[k];
-        if (it >> 30) continue;
-        const int bi = (it >> 15) & 0x7fff, bj = it & 0x7fff;
+        const int bi = it >> 15, bj = it & 0x7fff;
         threshold_tile<false>(X, ld, N, tau, elem, st, part, 0, env, tz, xb, T, tri_index(bi, bj, nt), bi, bj, nullptr);
         __syncthreads();   // the tile's shared sums are reused by the next entry
     }
@@ -276,11 +295,11 @@ __global__ void k_env_reset(int* __restrict__ env, int npanel, int nwords, const
 
 hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, double tau, int elem, State* st,
                                   double* part, int* nslots, int init, hipStream_t stream, int* env, int* tz,
-                                  const int* list, bool dense_switch, const double* H) {
+                                  const int* list, bool dense_switch, const double* H, const unsigned* hz) {
     const int nt = ld / 128;
     const int T = nt * (nt + 1) / 2;
     *nslots = T;
-    if (env) {
+    if (env && (init || !list)) {   // the list kernel has reset it otherwise
         const int W = mask_words(ld);
         hipLaunchKernelGGL(k_env_reset, dim3((nt * W + 255) / 256), dim3(256), 0, stream, env, nt, W, st);
     }
@@ -293,7 +312,7 @@ hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, dou
     } else {
         if (init && H)
             hipLaunchKernelGGL(k_block_threshold_x0, dim3(T), dim3(256), 0, stream, H, buf0, ld, N, tau, elem, st,
-                               part, env, tz);
+                               part, env, tz, hz);
         else
             hipLaunchKernelGGL(k_block_threshold, dim3(T), dim3(256), 0, stream, buf0, buf1, ld, N, tau, elem, st,
                                part, init, env, tz, 0);

@@ -34,6 +34,7 @@ struct SplitScratch {
     // products from the first product on only; null otherwise), followed by
     // room for the product's work list (T entries) and 2 counters
     const int* env = nullptr;
+    int* env_next = nullptr;    // with tz: the buffer the threshold pass behind the next product records into
     int* tz = nullptr;
     // thresholded int8 products: besides the work-list product, launch the
     // dense tile kernel, which runs (and the work-list kernels return at
@@ -59,22 +60,24 @@ hipError_t launch_split_gemm(SplitScratch& s, double* buf0, double* buf1, int ld
 // element below tau (elem != 0); rewrite the trace and norm partials of the
 // 128 x 128 tiles (keeping the idempotency partial).  With env non-null, also
 // records each panel's range of 32-column blocks that still hold a nonzero
-// (reset first), for the products' K ranges.  With tz non-null (2 x T flags,
-// T upper-triangular tiles, one row per X buffer): tiles the product marked
-// as written all zero are skipped, and every other tile's flag is set to
-// whether it is all zero after thresholding; the X_0 pass reads no flags,
-// sets those of buffer 0 and clears those of buffer 1.  With list non-null
+// (reset first; with a list the product's list kernel has reset it), for the
+// products' K ranges.  With tz non-null (2 x T flags, T upper-triangular tiles,
+// one row per X buffer): every visited tile's flag is set to whether it is
+// all zero after thresholding.  A tile whose flag is set is zero whatever its
+// memory holds: the X_0 pass and the products leave such tiles unwritten, and
+// every reader of X asks the flag first.  The X_0 pass sets the flags of
+// buffer 0 only (the first product sets those of buffer 1).  With list non-null
 // as well (the int8 product's work list: T entries, then its entry count),
 // updates visit only the tiles the product computed; with dense_switch as
 // well, a pass over every tile is launched beside it, and of the two the
 // list pass runs while State::full_fill is clear, the full pass while it is
 // set (the product then ran the dense tile kernel and built no list).  With
 // init and H (N x N) non-null, the X_0 pass forms X_0 from H itself (no
-// launch_init before it).
+// launch_init before it); hz (may be null, needs tz): the block flags of H.
 hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, double tau, int elem, State* st,
                                   double* part, int* nslots, int init, hipStream_t stream, int* env = nullptr,
                                   int* tz = nullptr, const int* list = nullptr, bool dense_switch = false,
-                                  const double* H = nullptr);
+                                  const double* H = nullptr, const unsigned* hz = nullptr);
 
 // int8 digit-plane product (int8x.hip)
 hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,

@@ -377,3 +377,40 @@ def test_blocksparse_scattered_n16384_fp64_against_oracle(ctx):
     assert est <= 1e-9 and dq <= 1e-9
     del D, H
     torch.cuda.empty_cache()
+
+@pytest.mark.parametrize("N,rule", [(129, 0), (770, 1), (1001, 0), (1536, 1)])
+def test_unwritten_zero_tiles(ctx, N, rule):
+    """The work-list products leave tiles of X that are all zero unwritten, and
+    the passes over H skip its zero blocks: a banded gapped H with far blocks
+    off the band (one padded tile with a remainder, even and odd N, whole
+    tiles), solved in buffers that hold an earlier dense solve's X, equals the
+    oracle, the solve in a fresh context and the one through the dense tile
+    kernel (which does read every tile), the last two bit for bit."""
+    import paper_1203_6836_amd as p
+    rng = np.random.default_rng(N)
+    H = rng.uniform(-0.05, 0.05, (N, N))
+    d = np.abs(np.subtract.outer(np.arange(N), np.arange(N)))
+    far = np.zeros((N, N), dtype=bool)
+    far[:20, N - 24:N - 4] = True
+    H = np.where((d <= 24) | far, H, 0.0)
+    H = np.triu(H, 1)
+    H = H + H.T + np.diag(np.where(np.arange(N) % 2 == 0, -2.0, 2.0))
+    n_occ = (N + 1) // 2
+    say(f"case unwritten tiles N={N} rule={rule}")
+    tau = 1e-7
+    G = rng.uniform(-1.0, 1.0, (N, N))
+    ctx.sp2_density_matrix(to_dev((G + G.T) / 2 + np.diag(np.where(np.arange(N) % 2 == 0, -4.0 * N, 4.0 * N))), n_occ,
+                           p.options("int8x"))   # a full X in the buffers
+    out = []
+    fresh = p.Context(0)
+    for c, fill in ((ctx, 2.0), (fresh, 2.0), (ctx, 0.95), (ctx, 0.0), (ctx, 0.05)):
+        D, st = c.sp2_density_matrix(to_dev(H), n_occ, p.options("int8x", tau=tau, threshold=rule, dense_fill=fill))
+        out.append((D.cpu().numpy(), st))
+    fresh.close()
+    D0, s0 = out[0]
+    ref = osp2.sp2(H, n_occ, tau=tau, threshold=("block", "element")[rule])
+    say(f"  {s0['iterations']} products, fill {s0['fill_min']:.3f}..{s0['fill_max']:.3f}")
+    assert np.linalg.norm(D0 - ref.D) / np.sqrt(N) <= TOL_D
+    for D, st in out[1:]:
+        assert np.array_equal(D, D0)
+        assert st["branches"] == s0["branches"] and st["fill_hist"] == s0["fill_hist"]
