@@ -124,8 +124,11 @@ typedef struct {
                             every upper tile (rows of X_n encoded whole)
                             instead of the work-list kernel over the kept
                             blocks; the same D either way (exact integer
-                            sums of the same digits).  Default 0.95 (3-10 %
-                            faster solves at N = 2048-8192 on 3-D lattices,
+                            sums of the same digits).  Only above padded
+                            N = 4096; a kept fraction that rises from below
+                            dense_fill / 8 within four products switches up
+                            to four products later.  Default 0.95 (3-5 %
+                            faster solves at N = 4800-8192 on 3-D lattices,
                             no change at N = 16384); > 1: always the
                             work-list kernel.  SP2_EINVAL below 0          */
 } sp2_options;

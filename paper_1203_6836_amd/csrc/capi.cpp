@@ -492,8 +492,10 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     int* envs[2] = {env, tz ? env + env_bytes(ld) / sizeof(int) : env};
     // thresholded int8 products from the first one on (work-list path): the
     // dense tile kernel takes over while X_n's kept fraction is at least
-    // dense_fill
-    const bool dense_switch = int8x && tz && env && o.dense_fill <= 1.0;
+    // dense_fill, above ld = 4096 (up to there the 64 x 64 list tiles are
+    // faster on a full X too, solves of N = 720 2.3 against 4.0 ms, 2048 6.7 /
+    // 7.4, 4000 34.4 / 36.6; N = 4800 53 / 51, 8192 214 / 207)
+    const bool dense_switch = int8x && tz && env && o.dense_fill <= 1.0 && ld > 4096;
     c->split.dense_switch = dense_switch;
     a.dense_fill = dense_switch ? o.dense_fill : 2.0;
     hipStream_t st = c->stream;
@@ -582,6 +584,13 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
             int* env_g = envs[g & 1];
             c->split.env = int8x ? env_g : nullptr;
             c->split.env_next = envs[(g + 1) & 1];
+            // Work-list products on 64 x 64 tiles up to ld = 4096 and while a
+            // tile's K range averages at most 2048 columns (kept fraction times
+            // ld, of the last product seen, taken as none before the first): N = 8192, 983
+            // columns 366 -> 245 us, 1589 525 -> 470, 2261 746 against 768,
+            // 3703 1247 against 1497; N = 4000, all of it, 505 -> 405.
+            // Either way X and the partials are the same bit for bit.
+            c->split.list64 = ld <= 4096 || progress_fill(seen) * ld <= 2048.0;
             if (pe) HIPCHK(c, hipEventRecord(pe[0], st));
             if (int8x || bf16x) HIPCHK(c, launch_split_encode(c->split, buf0, buf1, ld, c->st, st));
             if (bf16x || fp32) HIPCHK(c, launch_encode_f32(buf0, buf1, ld, c->st, c->split.x32, st));
@@ -596,7 +605,8 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
             if (pe) HIPCHK(c, hipEventRecord(pe[3], st));
             if (o.tau > 0.0)
                 HIPCHK(c, launch_block_threshold(buf0, buf1, ld, N, o.tau, o.threshold, c->st, part, &ns, 0, st,
-                                                 envs[(g + 1) & 1], tz, tz ? tz + (size_t)2 * tri_tiles(nt) : nullptr, dense));
+                                                 envs[(g + 1) & 1], tz, tz ? tz + (size_t)2 * tri_tiles(nt) : nullptr, dense,
+                                                 nullptr, nullptr, c->split.list64));
             if (pe) HIPCHK(c, hipEventRecord(pe[4], st));
             // The dense tile kernels (17 us a product where they find
             // nothing to do) are launched behind the list's while the kept

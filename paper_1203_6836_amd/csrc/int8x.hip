@@ -414,7 +414,7 @@ struct I8Smem {
         struct {
             double xs[128][128];                   // the X_n tile (upper-only mode), staged for the update
             unsigned long long rm[128], cm[128];   // tile row / column maxima (upper-only mode)
-            double red[3][8];                      // per-wave partials, after the last use of tr / rm / cm
+            double red[4][8];                      // per-wave partials, after the last use of tr / rm / cm
         } mx;
     };
 };
@@ -431,15 +431,13 @@ struct I8Smem {
 // only (no mirrored copy below the diagonal) and fold its row and column
 // maxima of |X_{n+1}| into rmax_next (bit patterns of non-negative doubles
 // order like the values, so atomicMax on them is exact and order-free).
-// x_zero (THR): the X_n tile is zero whatever its memory holds.
 template <int S, int NL, bool THR, bool UPPER, int C = 0>
 __device__ __forceinline__ void int8x_tile(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
                            const State* __restrict__ st, const int8_t* __restrict__ digits,
                            const double* __restrict__ scale, double* __restrict__ part, int bi, int bj,
                            I8Smem<S, C>& sm, const int* __restrict__ env,
                            unsigned long long* __restrict__ rmax_next, int kmode = 0, int kc0 = 0,
-                           int kc1 = -1, int* __restrict__ chunk_acc = nullptr, int nchunks = 0,
-                           bool x_zero = false) {
+                           int kc1 = -1, int* __restrict__ chunk_acc = nullptr, int nchunks = 0) {
     const int nt = ld / QB;
     const int t = tri_index(bi, bj, nt);
     const int i0 = bi * QB, j0 = bj * QB;
@@ -687,8 +685,10 @@ __device__ __forceinline__ void int8x_tile(double* __restrict__ buf0, double* __
         for (int L = NL - 1; L >= 0; --L) v += ldexp((double)acc[L][c][r], -(E2 + W * L));
         // s_i s_j first: the product is then the same for (i, j) and (j, i)
         // (the diagonal tiles form both), so X stays exactly symmetric
-        const double p = v * (scale[gi] * sj);
-        const double x = UPPER ? sm.mx.xs[gi - i0][gj - j0] : (THR && x_zero ? 0.0 : Xc[(size_t)gi * ld + gj]);
+        double p = v * (scale[gi] * sj);
+        // p rounded once for every use, as in the 64 x 64 tile
+        if constexpr (!UPPER) asm("" : "+v"(p));
+        const double x = UPPER ? sm.mx.xs[gi - i0][gj - j0] : Xc[(size_t)gi * ld + gj];
         const double xn = br ? 2.0 * x - p : p;
         Xn[(size_t)gi * ld + gj] = xn;
         if (gi == gj) trc[c] += xn;
@@ -759,26 +759,35 @@ __device__ __forceinline__ void int8x_tile(double* __restrict__ buf0, double* __
             }
         }
     }
-    double tr = trc[0] + trc[1], fro = froc[0] + froc[1], idm = idmc[0] + idmc[1];
+    double tr = trc[0] + trc[1], fro = froc[0] + froc[1], idm = UPPER ? idmc[0] + idmc[1] : idmc[0];
     tr = wred_sum(tr);
     fro = wred_sum(fro);
     idm = wred_sum(idm);
+    const double idm1 = UPPER ? 0.0 : wred_sum(idmc[1]);
     double (*red)[8] = sm.mx.red;
     if (lane == 0) {
         red[0][w] = tr;
         red[1][w] = fro;
         red[2][w] = idm;
+        red[3][w] = idm1;
     }
     __syncthreads();
     if (tid == 0) {
-        double s3[3];
-        for (int q = 0; q < 3; ++q)
-            s3[q] = ((red[q][0] + red[q][1]) + (red[q][2] + red[q][3])) +
-                    ((red[q][4] + red[q][5]) + (red[q][6] + red[q][7]));
         const double wgt = mirror ? 2.0 : 1.0;
-        part[3 * t + 0] = s3[0];
-        part[3 * t + 1] = wgt * s3[1];
-        part[3 * t + 2] = wgt * s3[2];
+        for (int q = 0; q < (UPPER ? 3 : 2); ++q)
+            part[3 * t + q] = (q ? wgt : 1.0) * (((red[q][0] + red[q][1]) + (red[q][2] + red[q][3])) +
+                                                 ((red[q][4] + red[q][5]) + (red[q][6] + red[q][7])));
+        if (!UPPER) {
+            // by 32 x 32 blocks within 64 x 64 quadrants, the order of the
+            // work-list product on 64 x 64 tiles (the lower quadrant of a
+            // diagonal tile counted as the upper one's mirror)
+            auto quad = [&](int qr, int qc) {
+                const int a = 4 * qr + qc, b = a + 2;
+                return (red[2][a] + red[3][a]) + (red[2][b] + red[3][b]);
+            };
+            part[3 * t + 2] = mirror ? (2.0 * quad(0, 0) + 2.0 * quad(0, 1)) + (2.0 * quad(1, 0) + 2.0 * quad(1, 1))
+                                     : (quad(0, 0) + 2.0 * quad(0, 1)) + (0.0 + quad(1, 1));
+        }
     }
 }
 
@@ -875,12 +884,19 @@ struct I8Smem64 {
     };
 };
 
-template <int S, int NL>
+//
+// THR: of a thresholded X, K stages with a 32-column block set in both masks mi
+// and mj (of the 128-row panels the tile lies in) only; the mirrored copy is
+// written too, rmax_next is not used, X_n is zero if x_zero, and of the
+// partials only the idempotency one is written, to part[slot].
+template <int S, int NL, bool THR = false>
 __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
                                              const State* __restrict__ st, const int8_t* __restrict__ digits,
                                              const double* __restrict__ scale, double* __restrict__ part, int bi,
                                              int bj, I8Smem64<S>& sm, unsigned long long* __restrict__ rmax_next,
-                                             int slot) {
+                                             int slot, const unsigned long long* __restrict__ mi = nullptr,
+                                             const unsigned long long* __restrict__ mj = nullptr,
+                                             bool x_zero = false) {
     using G = I8Stage64<S>;
     constexpr int KS = G::KS, NST = G::NST, PER = G::PER;
     static_assert(NL == S || NL == S + 1, "levels: the triangle or one more");
@@ -944,16 +960,42 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
         }
     };
     const int nk = ld / (QK * KS);
-    for (int q = 0; q < NST - 1; ++q)
-        if (q < nk) issue(q, q);
-    for (int kt = 0; kt < nk; ++kt) {
-        // as in int8x_tile: this wave's blocks of stage kt have landed, the
-        // barrier covers the other waves'
-        if (NST >= 3 && kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F70 | PER);   // vmcnt(PER)
-        else __builtin_amdgcn_s_waitcnt(0x0F70);                                 // vmcnt(0)
-        __builtin_amdgcn_s_barrier();
-        if (kt + NST - 1 < nk) issue(kt + NST - 1, (kt + NST - 1) % NST);
-        compute(kt % NST);
+    if constexpr (THR) {
+        const unsigned long long mword = common_mask_word(mi, mj, nb);
+        auto next_stage = [&](int s) -> int {      // first working stage >= s, or nk
+            const int b = next_block_in_wave(mword, s * KS, nb);
+            return b >= nb ? nk : b / KS;
+        };
+        int ic = next_stage(0), n_iss = 0, n_done = 0;
+        while (n_iss < NST - 1 && ic < nk) {
+            issue(ic, n_iss % NST);
+            ++n_iss;
+            ic = next_stage(ic + 1);
+        }
+        while (n_done < n_iss) {
+            if (NST >= 3 && n_iss - n_done >= 2) __builtin_amdgcn_s_waitcnt(0x0F70 | PER);   // vmcnt(PER)
+            else __builtin_amdgcn_s_waitcnt(0x0F70);                                         // vmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            if (ic < nk) {
+                issue(ic, n_iss % NST);
+                ++n_iss;
+                ic = next_stage(ic + 1);
+            }
+            compute(n_done % NST);
+            ++n_done;
+        }
+    } else {
+        for (int q = 0; q < NST - 1; ++q)
+            if (q < nk) issue(q, q);
+        for (int kt = 0; kt < nk; ++kt) {
+            // as in int8x_tile: this wave's blocks of stage kt have landed, the
+            // barrier covers the other waves'
+            if (NST >= 3 && kt + 1 < nk) __builtin_amdgcn_s_waitcnt(0x0F70 | PER);   // vmcnt(PER)
+            else __builtin_amdgcn_s_waitcnt(0x0F70);                                 // vmcnt(0)
+            __builtin_amdgcn_s_barrier();
+            if (kt + NST - 1 < nk) issue(kt + NST - 1, (kt + NST - 1) % NST);
+            compute(kt % NST);
+        }
     }
 
     const int br = st->branch;
@@ -965,7 +1007,7 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
     double x[16], si[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        x[r] = Xc[(size_t)(i0 + row_of(r)) * ld + gj];
+        x[r] = THR && x_zero ? 0.0 : Xc[(size_t)(i0 + row_of(r)) * ld + gj];
         si[r] = scale[i0 + row_of(r)];
     }
     const double sj = scale[gj];
@@ -977,13 +1019,14 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
         double v = 0.0;
 #pragma unroll
         for (int L = NL - 1; L >= 0; --L) v += ldexp((double)acc[L][r], -(E2 + W * L));
-        const double p = v * (si[r] * sj);
+        double p = v * (si[r] * sj);
+        if constexpr (THR) asm("" : "+v"(p));
         const double xn = br ? 2.0 * x[r] - p : p;
         Xn[(size_t)gi * ld + gj] = xn;
         if (gi == gj) tr += xn;
         fro += xn * xn;
         idm += (p - x[r]) * (p - x[r]);
-        sm.e.ax[row_of(r)][wc * 32 + (lane & 31)] = fabs(xn);
+        sm.e.ax[row_of(r)][wc * 32 + (lane & 31)] = THR ? xn : fabs(xn);
     }
     tr = wred_sum(tr);
     fro = wred_sum(fro);
@@ -994,6 +1037,19 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
         sm.e.red[2][w] = idm;
     }
     __syncthreads();
+    if constexpr (THR) {
+        if (mirror) {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int r = w + 4 * k;
+                Xn[(size_t)(j0 + r) * ld + i0 + lane] = sm.e.ax[lane][r];
+            }
+        }
+        if (tid == 0)
+            part[slot] = (mirror ? 2.0 : 1.0) *
+                         ((sm.e.red[2][0] + sm.e.red[2][1]) + (sm.e.red[2][2] + sm.e.red[2][3]));
+        return;
+    }
     // row maxima: four lanes per row, 16 columns each; column maxima the same
     // way off the diagonal (a diagonal tile is symmetric)
     {
@@ -1181,9 +1237,56 @@ __global__ __launch_bounds__(512) void k_gemm_int8x_list(double* __restrict__ bu
         if (k >= n) break;
         const int it = list[k];
         const int bi = it >> 15, bj = it & 0x7fff;
-        const bool x_zero = tz[(size_t)st->cur * T + tri_index(bi, bj, nt)] != 0;
-        int8x_tile<S, NL, true, false>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, env, nullptr, 0, 0, -1,
-                                       nullptr, 0, x_zero);
+        if (tz[(size_t)st->cur * T + tri_index(bi, bj, nt)]) {
+            // the epilogue reads X_n: store the zeros the flag stands for (a
+            // test per element would keep its loads from being in flight together)
+            double* __restrict__ Xc = st->cur ? buf1 : buf0;
+            for (int e = threadIdx.x; e < QB * QB / 2; e += 512)
+                *reinterpret_cast<double2*>(Xc + (size_t)(bi * QB + e / (QB / 2)) * ld + bj * QB + 2 * (e % (QB / 2))) =
+                    make_double2(0.0, 0.0);
+            __syncthreads();
+        }
+        int8x_tile<S, NL, true, false>(buf0, buf1, ld, st, digits, scale, part, bi, bj, sm, env, nullptr);
+        __syncthreads();
+    }
+}
+
+// The same on 64 x 64 tiles, four per entry (the one below the diagonal of a
+// diagonal tile is left out), for lists whose tiles have short K ranges: two
+// workgroups share a CU, so one's X_n tile, mirrored stores and masks pass
+// under the other's products.  A whole number of workgroups per XCD, those of
+// XCD x take every per-th tile of its run of the list.  The idempotency
+// partials go to part[3 T + 4 t + q]; the threshold pass adds them to the sum
+// the 128 x 128 tile forms.  Banded N = 16384 (875 entries of 8 stages): 228 ->
+// 130 us, of which the products alone would be 66.
+template <int S, int NL>
+__global__ __launch_bounds__(256, 2) void k_gemm_int8x_list64(double* __restrict__ buf0, double* __restrict__ buf1,
+                                                            int ld, const State* __restrict__ st,
+                                                            const int8_t* __restrict__ digits,
+                                                            const double* __restrict__ scale,
+                                                            double* __restrict__ part, const int* __restrict__ env,
+                                                            const int* __restrict__ tz, const int* __restrict__ list,
+                                                            const int* __restrict__ list_ctr) {
+    if (st->done || st->phase != 1 || st->full_fill) return;
+    extern __shared__ __align__(16) int8_t smem_raw[];
+    I8Smem64<S>& sm = *reinterpret_cast<I8Smem64<S>*>(smem_raw);
+    const int nt = ld / QB, T = nt * (nt + 1) / 2;
+    const int n = 4 * list_ctr[0];
+    const unsigned long long* __restrict__ mk = env_mask(env, nt);
+    const int W = mask_words(ld);
+    const int x = blockIdx.x % kXcds, per = gridDim.x / kXcds;
+    const int end = (int)((long long)n * (x + 1) / kXcds);
+    for (int k = (int)((long long)n * x / kXcds) + blockIdx.x / kXcds; k < end; k += per) {
+        const int it = list[k >> 2], q = k & 3;
+        const int bi = it >> 15, bj = it & 0x7fff;
+        const int t = tri_index(bi, bj, nt);
+        if (bi == bj && q == 2) {
+            if (threadIdx.x == 0) part[3 * T + 4 * t + q] = 0.0;
+            continue;
+        }
+        const bool x_zero = tz[(size_t)st->cur * T + t] != 0;
+        int8x_tile64<S, NL, true>(buf0, buf1, ld, st, digits, scale, part, 2 * bi + (q >> 1), 2 * bj + (q & 1), sm,
+                                  nullptr, 3 * T + 4 * t + q, mk + (size_t)bi * W, mk + (size_t)bj * W, x_zero);
         __syncthreads();
     }
 }
@@ -1353,20 +1456,29 @@ static hipError_t launch_list_kernel(SplitScratch& s, double* buf0, double* buf1
                                      hipStream_t stream, const int* env) {
     const int nt = ld / QB;
     const int T = nt * (nt + 1) / 2;
-    const size_t lds = sizeof(I8Smem<S>);
     static std::atomic<unsigned long long> attr_done{0};
     hipError_t e = once_per_device(attr_done, [&] {
-        return hipFuncSetAttribute((const void*)k_gemm_int8x_list<S, NL>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)lds);
+        hipError_t r = hipFuncSetAttribute((const void*)k_gemm_int8x_list<S, NL>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(I8Smem<S>));
+        if (r == hipSuccess)
+            r = hipFuncSetAttribute((const void*)k_gemm_int8x_list64<S, NL>,
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(I8Smem64<S>));
+        return r;
     });
     if (e != hipSuccess) return e;
     int* list = s.tz + (size_t)2 * T;
     int* ctr = list + T;
     hipLaunchKernelGGL(k_tile_list, dim3((T + 255) / 256), dim3(256), 0, stream, st, env, s.env_next, s.tz, nt,
                        s.tile_group, part, list, ctr);
-    const int grid = std::min(T, device_cus());
-    hipLaunchKernelGGL((k_gemm_int8x_list<S, NL>), dim3(grid), dim3(512), lds, stream, buf0, buf1, ld, st, s.digits, s.scale,
-                       part, env, s.tz, list, ctr);
+    if (s.list64) {
+        const int grid = std::max(2 * device_cus() / kXcds, 1) * kXcds;
+        hipLaunchKernelGGL((k_gemm_int8x_list64<S, NL>), dim3(grid), dim3(256), sizeof(I8Smem64<S>), stream, buf0,
+                           buf1, ld, st, s.digits, s.scale, part, env, s.tz, list, ctr);
+    } else {
+        const int grid = std::min(T, device_cus());
+        hipLaunchKernelGGL((k_gemm_int8x_list<S, NL>), dim3(grid), dim3(512), sizeof(I8Smem<S>), stream, buf0, buf1,
+                           ld, st, s.digits, s.scale, part, env, s.tz, list, ctr);
+    }
     return hipGetLastError();
 }
 

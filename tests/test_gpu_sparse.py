@@ -378,14 +378,15 @@ def test_blocksparse_scattered_n16384_fp64_against_oracle(ctx):
     del D, H
     torch.cuda.empty_cache()
 
-@pytest.mark.parametrize("N,rule", [(129, 0), (770, 1), (1001, 0), (1536, 1)])
+@pytest.mark.parametrize("N,rule", [(129, 0), (770, 1), (1001, 0), (1536, 1), (4225, 0)])
 def test_unwritten_zero_tiles(ctx, N, rule):
     """The work-list products leave tiles of X that are all zero unwritten, and
     the passes over H skip its zero blocks: a banded gapped H with far blocks
     off the band (one padded tile with a remainder, even and odd N, whole
     tiles), solved in buffers that hold an earlier dense solve's X, equals the
-    oracle, the solve in a fresh context and the one through the dense tile
-    kernel (which does read every tile), the last two bit for bit."""
+    oracle, the solve in a fresh context and, at N = 4225, those through the
+    128 x 128 list tiles and the dense tile kernel (which does read every
+    tile), all but the oracle bit for bit."""
     import paper_1203_6836_amd as p
     rng = np.random.default_rng(N)
     H = rng.uniform(-0.05, 0.05, (N, N))
