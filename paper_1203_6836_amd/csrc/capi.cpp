@@ -486,6 +486,8 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     int* tz = sc.tz;
     c->split.env = int8x ? env : nullptr;
     c->split.tz = tz;
+    c->split.tau = o.tau;
+    c->split.elem = o.threshold;
     unsigned* hz = tz ? reinterpret_cast<unsigned*>(tz) + (size_t)3 * tri_tiles(nt) + 2 : nullptr;
     // the work-list path alternates two env buffers: product g reads the g-th
     // (mod 2) and clears the other for the threshold pass behind it

@@ -885,18 +885,30 @@ struct I8Smem64 {
 };
 
 //
-// THR: of a thresholded X, K stages with a 32-column block set in both masks mi
-// and mj (of the 128-row panels the tile lies in) only; the mirrored copy is
-// written too, rmax_next is not used, X_n is zero if x_zero, and of the
-// partials only the idempotency one is written, to part[slot].
+// THR: quadrant th.q of a 128 x 128 tile of a thresholded X: K stages with a
+// 32-column block set in both masks (of the tile's two row panels) only; the
+// threshold is applied here, by the wave to its block, with the sums in the
+// order of threshold_tile; the mirrored copy is written too, rmax_next is not
+// used, and of the partials only the idempotency one is written, to
+// part[slot], beside what k_tile_finish needs of each block.
+struct Thr64 {
+    const unsigned long long* mi;
+    const unsigned long long* mj;
+    double tau;
+    int elem;
+    double* blk;    // of the 128 x 128 tile: ||block||_F^2 of its 16 blocks, -1 where dropped
+    double* tr;     // of a diagonal tile: traces of its 4 diagonal blocks
+    int q;
+    bool diag;      // the 128 x 128 tile is a diagonal one
+    bool x_zero;    // X_n is zero here whatever its memory holds
+};
+
 template <int S, int NL, bool THR = false>
 __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* __restrict__ buf1, int ld,
                                              const State* __restrict__ st, const int8_t* __restrict__ digits,
                                              const double* __restrict__ scale, double* __restrict__ part, int bi,
                                              int bj, I8Smem64<S>& sm, unsigned long long* __restrict__ rmax_next,
-                                             int slot, const unsigned long long* __restrict__ mi = nullptr,
-                                             const unsigned long long* __restrict__ mj = nullptr,
-                                             bool x_zero = false) {
+                                             int slot, const Thr64& th = {}) {
     using G = I8Stage64<S>;
     constexpr int KS = G::KS, NST = G::NST, PER = G::PER;
     static_assert(NL == S || NL == S + 1, "levels: the triangle or one more");
@@ -961,7 +973,7 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
     };
     const int nk = ld / (QK * KS);
     if constexpr (THR) {
-        const unsigned long long mword = common_mask_word(mi, mj, nb);
+        const unsigned long long mword = common_mask_word(th.mi, th.mj, nb);
         auto next_stage = [&](int s) -> int {      // first working stage >= s, or nk
             const int b = next_block_in_wave(mword, s * KS, nb);
             return b >= nb ? nk : b / KS;
@@ -1007,7 +1019,7 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
     double x[16], si[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        x[r] = THR && x_zero ? 0.0 : Xc[(size_t)(i0 + row_of(r)) * ld + gj];
+        x[r] = THR && th.x_zero ? 0.0 : Xc[(size_t)(i0 + row_of(r)) * ld + gj];
         si[r] = scale[i0 + row_of(r)];
     }
     const double sj = scale[gj];
@@ -1022,28 +1034,75 @@ __device__ __forceinline__ void int8x_tile64(double* __restrict__ buf0, double* 
         double p = v * (si[r] * sj);
         if constexpr (THR) asm("" : "+v"(p));
         const double xn = br ? 2.0 * x[r] - p : p;
-        Xn[(size_t)gi * ld + gj] = xn;
-        if (gi == gj) tr += xn;
-        fro += xn * xn;
+        if constexpr (!THR) {
+            Xn[(size_t)gi * ld + gj] = xn;
+            if (gi == gj) tr += xn;
+            fro += xn * xn;
+        }
         idm += (p - x[r]) * (p - x[r]);
         sm.e.ax[row_of(r)][wc * 32 + (lane & 31)] = THR ? xn : fabs(xn);
     }
-    tr = wred_sum(tr);
-    fro = wred_sum(fro);
+    if constexpr (!THR) {
+        tr = wred_sum(tr);
+        fro = wred_sum(fro);
+    }
     idm = wred_sum(idm);
     if (lane == 0) {
-        sm.e.red[0][w] = tr;
-        sm.e.red[1][w] = fro;
+        if constexpr (!THR) {
+            sm.e.red[0][w] = tr;
+            sm.e.red[1][w] = fro;
+        }
         sm.e.red[2][w] = idm;
     }
     __syncthreads();
     if constexpr (THR) {
+        // the wave's block row by row, and transposed
+        const int rb = wr * 32, cb = wc * 32, R = 2 * (th.q >> 1) + wr, C = 2 * (th.q & 1) + wc;
+        auto threshold = [&](double v[16]) -> double {   // ||block||^2, -1 if dropped
+            double ss = 0.0;
+            bool nz = false;
+#pragma unroll
+            for (int m = 0; m < 16; ++m) {
+                if (th.elem && fabs(v[m]) < th.tau) v[m] = 0.0;
+                nz = nz || v[m] != 0.0;
+                ss += v[m] * v[m];
+            }
+            ss = wred_sum(ss);
+            if (th.elem ? __any(nz) : ss >= th.tau * th.tau) return ss;
+#pragma unroll
+            for (int m = 0; m < 16; ++m) v[m] = 0.0;
+            return -1.0;
+        };
+        const int r0 = lane >> 5, c = lane & 31;   // element m of lane l is (r0 + 2 m, c)
+        double v[16];
+#pragma unroll
+        for (int m = 0; m < 16; ++m) v[m] = sm.e.ax[rb + r0 + 2 * m][cb + c];
+        const double ss = threshold(v);
+        if (lane == 0) th.blk[4 * R + C] = ss;
+#pragma unroll
+        for (int m = 0; m < 16; ++m) Xn[(size_t)(i0 + rb + r0 + 2 * m) * ld + j0 + cb + c] = v[m];
+        if (th.diag && R == C) {
+            double t = 0.0;
+#pragma unroll
+            for (int m = 0; m < 16; ++m)
+                if (r0 + 2 * m == c) t += v[m];
+            t = wred_sum(t);
+            if (lane == 0) th.tr[R] = t;   // 0 if dropped
+        }
         if (mirror) {
 #pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const int r = w + 4 * k;
-                Xn[(size_t)(j0 + r) * ld + i0 + lane] = sm.e.ax[lane][r];
+            for (int m = 0; m < 16; ++m) v[m] = sm.e.ax[rb + c][cb + r0 + 2 * m];
+            if (th.diag) {
+                // a block of the diagonal tile's lower half: its own sum
+                const double st2 = threshold(v);
+                if (lane == 0) th.blk[4 * C + R] = st2;
+            } else {
+#pragma unroll
+                for (int m = 0; m < 16; ++m)
+                    if (th.elem ? fabs(v[m]) < th.tau : ss == -1.0) v[m] = 0.0;
             }
+#pragma unroll
+            for (int m = 0; m < 16; ++m) Xn[(size_t)(j0 + cb + r0 + 2 * m) * ld + i0 + rb + c] = v[m];
         }
         if (tid == 0)
             part[slot] = (mirror ? 2.0 : 1.0) *
@@ -1254,19 +1313,31 @@ __global__ __launch_bounds__(512) void k_gemm_int8x_list(double* __restrict__ bu
 // The same on 64 x 64 tiles, four per entry (the one below the diagonal of a
 // diagonal tile is left out), for lists whose tiles have short K ranges: two
 // workgroups share a CU, so one's X_n tile, mirrored stores and masks pass
-// under the other's products.  A whole number of workgroups per XCD, those of
-// XCD x take every per-th tile of its run of the list.  The idempotency
-// partials go to part[3 T + 4 t + q]; the threshold pass adds them to the sum
-// the 128 x 128 tile forms.  Banded N = 16384 (875 entries of 8 stages): 228 ->
-// 130 us, of which the products alone would be 66.
+// under the other's products, and a wave's block is the threshold's, which is
+// applied before X_{n+1} is stored.  A whole number of workgroups per XCD,
+// those of XCD x take every per-th tile of its run of the list.  Banded N =
+// 16384 (875 entries of 8 stages), product and threshold: 228 + 58 us on 128 x
+// 128 tiles, 130 + 58 on these with a threshold pass of its own, 123 + 5 now
+// (k_tile_finish); the matrix instructions alone would be 66.
+// Per listed tile t: idempotency partials idem4[4 t + q], block sums blk[16 t]
+// and traces trd[4 bi].
+struct List64 {
+    double tau;
+    int elem;
+    double* idem4;
+    double* blk;
+    double* trd;
+};
+
 template <int S, int NL>
 __global__ __launch_bounds__(256, 2) void k_gemm_int8x_list64(double* __restrict__ buf0, double* __restrict__ buf1,
-                                                            int ld, const State* __restrict__ st,
-                                                            const int8_t* __restrict__ digits,
-                                                            const double* __restrict__ scale,
-                                                            double* __restrict__ part, const int* __restrict__ env,
-                                                            const int* __restrict__ tz, const int* __restrict__ list,
-                                                            const int* __restrict__ list_ctr) {
+                                                              int ld, const State* __restrict__ st,
+                                                              const int8_t* __restrict__ digits,
+                                                              const double* __restrict__ scale, List64 a,
+                                                              const int* __restrict__ env,
+                                                              const int* __restrict__ tz,
+                                                              const int* __restrict__ list,
+                                                              const int* __restrict__ list_ctr) {
     if (st->done || st->phase != 1 || st->full_fill) return;
     extern __shared__ __align__(16) int8_t smem_raw[];
     I8Smem64<S>& sm = *reinterpret_cast<I8Smem64<S>*>(smem_raw);
@@ -1281,14 +1352,68 @@ __global__ __launch_bounds__(256, 2) void k_gemm_int8x_list64(double* __restrict
         const int bi = it >> 15, bj = it & 0x7fff;
         const int t = tri_index(bi, bj, nt);
         if (bi == bj && q == 2) {
-            if (threadIdx.x == 0) part[3 * T + 4 * t + q] = 0.0;
+            if (threadIdx.x == 0) a.idem4[4 * t + q] = 0.0;
             continue;
         }
-        const bool x_zero = tz[(size_t)st->cur * T + t] != 0;
-        int8x_tile64<S, NL, true>(buf0, buf1, ld, st, digits, scale, part, 2 * bi + (q >> 1), 2 * bj + (q & 1), sm,
-                                  nullptr, 3 * T + 4 * t + q, mk + (size_t)bi * W, mk + (size_t)bj * W, x_zero);
+        const Thr64 th = {mk + (size_t)bi * W, mk + (size_t)bj * W, a.tau, a.elem, a.blk + (size_t)16 * t,
+                          a.trd + 4 * bi, q, bi == bj, tz[(size_t)st->cur * T + t] != 0};
+        int8x_tile64<S, NL, true>(buf0, buf1, ld, st, digits, scale, a.idem4, 2 * bi + (q >> 1), 2 * bj + (q & 1), sm,
+                                  nullptr, 4 * t + q, th);
         __syncthreads();
     }
+}
+
+// What the threshold pass leaves behind beside X, from the block sums of the
+// 64 x 64 tiles: the tile's partials and flag, its panels' ranges and masks,
+// and the kept count.  One thread per listed tile; the same sums in the same
+// order as threshold_tile.
+__global__ __launch_bounds__(64) void k_tile_finish(State* __restrict__ st, int nt, List64 a, double* __restrict__ part,
+                                                    int* __restrict__ env, int* __restrict__ tz,
+                                                    const int* __restrict__ list, const int* __restrict__ list_ctr) {
+    if (st->done || st->phase != 1 || st->full_fill) return;
+    const int T = nt * (nt + 1) / 2, n = list_ctr[0];
+    const int W = mask_words(nt * QB);
+    int* __restrict__ tzn = tz + (size_t)(1 - st->cur) * T;
+    unsigned long long* __restrict__ mk = env_mask(env, nt);
+    int kept = 0;
+    for (int k = blockIdx.x * 64 + threadIdx.x; k < n; k += gridDim.x * 64) {
+        const int bi = list[k] >> 15, bj = list[k] & 0x7fff, t = tri_index(bi, bj, nt);
+        const bool mirror = bi != bj;
+        double f[4];
+        int bits = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            f[r] = 0.0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const double ss = a.blk[(size_t)16 * t + 4 * r + c];
+                if (ss != -1.0) {
+                    f[r] += ss;
+                    bits |= 1 << (4 * r + c);
+                }
+            }
+        }
+        const double* __restrict__ tr = a.trd + 4 * bi;
+        const double* __restrict__ id = a.idem4 + 4 * t;
+        part[3 * t + 0] = mirror ? 0.0 : (tr[0] + tr[1]) + (tr[2] + tr[3]);
+        part[3 * t + 1] = (mirror ? 2.0 : 1.0) * ((f[0] + f[1]) + (f[2] + f[3]));
+        part[3 * t + 2] = (id[0] + id[1]) + (id[2] + id[3]);
+        tzn[t] = bits == 0 ? 1 : 0;
+        if (bits == 0) continue;
+        kept += (mirror ? 2 : 1) * __popc(bits);
+        // kept column sub-blocks of panel bi, row sub-blocks of panel bj
+        const int cols = (bits | bits >> 4 | bits >> 8 | bits >> 12) & 15;
+        int rows = 0;
+        for (int r = 0; r < 4; ++r) rows |= ((bits >> (4 * r) & 15) != 0 ? 1 : 0) << r;
+        atomicMin(&env[2 * bi], 4 * bj + __ffs(cols) - 1);
+        atomicMax(&env[2 * bi + 1], 4 * bj + 31 - __clz(cols));
+        atomicMin(&env[2 * bj], 4 * bi + __ffs(rows) - 1);
+        atomicMax(&env[2 * bj + 1], 4 * bi + 31 - __clz(rows));
+        atomicOr(&mk[(size_t)bi * W + ((4 * bj) >> 6)], (unsigned long long)cols << ((4 * bj) & 63));
+        if (mirror) atomicOr(&mk[(size_t)bj * W + ((4 * bi) >> 6)], (unsigned long long)rows << ((4 * bi) & 63));
+    }
+    for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o, 64);
+    if (threadIdx.x == 0 && kept) atomicAdd(&st->kept, (unsigned long long)kept);
 }
 
 // Epilogue of the split tiles: workgroup p takes the summed chunks of the
@@ -1472,8 +1597,14 @@ static hipError_t launch_list_kernel(SplitScratch& s, double* buf0, double* buf1
                        s.tile_group, part, list, ctr);
     if (s.list64) {
         const int grid = std::max(2 * device_cus() / kXcds, 1) * kXcds;
+        // 20 doubles per tile and 4 per diagonal one, where the dense kernel keeps its K chunks
+        double* a0 = reinterpret_cast<double*>(s.tail_acc);
+        if (((size_t)20 * T + 4 * nt) * sizeof(double) > s.tail_bytes) return hipErrorInvalidValue;
+        const List64 a = {s.tau, s.elem, a0, a0 + (size_t)4 * T, a0 + (size_t)20 * T};
         hipLaunchKernelGGL((k_gemm_int8x_list64<S, NL>), dim3(grid), dim3(256), sizeof(I8Smem64<S>), stream, buf0,
-                           buf1, ld, st, s.digits, s.scale, part, env, s.tz, list, ctr);
+                           buf1, ld, st, s.digits, s.scale, a, env, s.tz, list, ctr);
+        hipLaunchKernelGGL(k_tile_finish, dim3(std::min((T + 63) / 64, device_cus())), dim3(64), 0, stream, st, nt, a,
+                           part, s.env_next, s.tz, list, ctr);
     } else {
         const int grid = std::min(T, device_cus());
         hipLaunchKernelGGL((k_gemm_int8x_list<S, NL>), dim3(grid), dim3(512), sizeof(I8Smem<S>), stream, buf0, buf1,

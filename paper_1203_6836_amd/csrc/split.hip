@@ -39,8 +39,7 @@ __device__ __forceinline__ void tri_coords_t(int t, int nt, int& bi, int& bj) {
 template <bool FROM_H>
 __device__ void threshold_tile(double* __restrict__ X, int ld, int N, double tau, int elem, State* __restrict__ st,
                                double* __restrict__ part, int init, int* __restrict__ env, int* __restrict__ tz,
-                               int xb, int T, int t, int bi, int bj, const double* __restrict__ H,
-                               const double* __restrict__ idem4 = nullptr) {
+                               int xb, int T, int t, int bi, int bj, const double* __restrict__ H) {
     const bool mirror = bi != bj;
     const double emax = FROM_H ? st->eps_max : 0.0;
     const double inv = FROM_H ? 1.0 / (st->eps_max - st->eps_min) : 0.0;
@@ -185,7 +184,6 @@ __device__ void threshold_tile(double* __restrict__ X, int ld, int N, double tau
         part[3 * t + 0] = (s_tr[0] + s_tr[1]) + (s_tr[2] + s_tr[3]);
         part[3 * t + 1] = wgt * ((s_fr[0] + s_fr[1]) + (s_fr[2] + s_fr[3]));
         if (init) part[3 * t + 2] = 0.0;
-        if (idem4) part[3 * t + 2] = (idem4[4 * t] + idem4[4 * t + 1]) + (idem4[4 * t + 2] + idem4[4 * t + 3]);
         const int k = s_k[0] + s_k[1] + s_k[2] + s_k[3];
         atomicAdd(&st->kept, (unsigned long long)(mirror ? 2 * k : k));
         if (tz) tz[(size_t)xb * T + t] = k == 0 ? 1 : 0;
@@ -270,8 +268,7 @@ __global__ __launch_bounds__(256) void k_block_threshold_list(double* __restrict
                                                               State* __restrict__ st, double* __restrict__ part,
                                                               int* __restrict__ env, int* __restrict__ tz,
                                                               const int* __restrict__ list,
-                                                              const int* __restrict__ list_ctr,
-                                                              const double* __restrict__ idem4) {
+                                                              const int* __restrict__ list_ctr) {
     if (st->done || st->full_fill) return;
     const int xb = st->cur ? 0 : 1;
     double* X = xb == 0 ? buf0 : buf1;
@@ -280,8 +277,7 @@ __global__ __launch_bounds__(256) void k_block_threshold_list(double* __restrict
     for (int k = blockIdx.x; k < n; k += gridDim.x) {
         const int it = list[k];
         const int bi = it >> 15, bj = it & 0x7fff;
-        threshold_tile<false>(X, ld, N, tau, elem, st, part, 0, env, tz, xb, T, tri_index(bi, bj, nt), bi, bj, nullptr,
-                              idem4);
+        threshold_tile<false>(X, ld, N, tau, elem, st, part, 0, env, tz, xb, T, tri_index(bi, bj, nt), bi, bj, nullptr);
         __syncthreads();   // the tile's shared sums are reused by the next entry
     }
 }
@@ -300,7 +296,7 @@ __global__ void k_env_reset(int* __restrict__ env, int npanel, int nwords, const
 hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, double tau, int elem, State* st,
                                   double* part, int* nslots, int init, hipStream_t stream, int* env, int* tz,
                                   const int* list, bool dense_switch, const double* H, const unsigned* hz,
-                                  bool list64) {
+                                  bool thresholded) {
     const int nt = ld / 128;
     const int T = nt * (nt + 1) / 2;
     *nslots = T;
@@ -309,8 +305,9 @@ hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, dou
         hipLaunchKernelGGL(k_env_reset, dim3((nt * W + 255) / 256), dim3(256), 0, stream, env, nt, W, st);
     }
     if (list && tz && env && !init) {
-        hipLaunchKernelGGL(k_block_threshold_list, dim3(std::min(T, 2048)), dim3(256), 0, stream, buf0, buf1, ld, N,
-                           tau, elem, st, part, env, tz, list, list + T, list64 ? part + 3 * T : nullptr);
+        if (!thresholded)
+            hipLaunchKernelGGL(k_block_threshold_list, dim3(std::min(T, 2048)), dim3(256), 0, stream, buf0, buf1, ld, N,
+                               tau, elem, st, part, env, tz, list, list + T);
         if (dense_switch)
             hipLaunchKernelGGL(k_block_threshold, dim3(T), dim3(256), 0, stream, buf0, buf1, ld, N, tau, elem, st,
                                part, 0, env, tz, 1);

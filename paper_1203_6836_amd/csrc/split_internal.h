@@ -40,7 +40,10 @@ struct SplitScratch {
     // dense tile kernel, which runs (and the work-list kernels return at
     // once) while State::full_fill is set
     bool dense_switch = false;
-    bool list64 = false;        // the work-list product runs 64 x 64 tiles (set per product)
+    bool list64 = false;        // the work-list product runs 64 x 64 tiles (set per product) and applies
+                                // the threshold itself:
+    double tau = 0.0;
+    int elem = 0;
 };
 
 int split_reserve(SplitScratch& s, int ld, int slices, bool bf16);
@@ -75,13 +78,12 @@ hipError_t launch_split_gemm(SplitScratch& s, double* buf0, double* buf1, int ld
 // set (the product then ran the dense tile kernel and built no list).  With
 // init and H (N x N) non-null, the X_0 pass forms X_0 from H itself (no
 // launch_init before it); hz (may be null, needs tz): the block flags of H.
-// list64: the product ran 64 x 64 tiles, whose idempotency partials (part +
-// 3 T, four per tile) are added up here.
+// thresholded: the list product was one that applies the threshold itself.
 hipError_t launch_block_threshold(double* buf0, double* buf1, int ld, int N, double tau, int elem, State* st,
                                   double* part, int* nslots, int init, hipStream_t stream, int* env = nullptr,
                                   int* tz = nullptr, const int* list = nullptr, bool dense_switch = false,
                                   const double* H = nullptr, const unsigned* hz = nullptr,
-                                  bool list64 = false);
+                                  bool thresholded = false);
 
 // int8 digit-plane product (int8x.hip)
 hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double* buf1, int ld, State* st,
