@@ -352,9 +352,10 @@ def test_int8_mfma_rate_probe(ctx):
                                             (384, {"slices": 5}), (560, {"slices": 4, "levels": 5}),
                                             (768, {"slices": 4, "levels": 5})])
 def test_int8x_small_output_tile_equals_the_large_one(ctx, n_atoms, recipe):
-    """Direct solves of these sizes run 64 x 64 output tiles, the server's
-    128 x 128: the digit sums are exact and the update's arithmetic the same,
-    so D is the same bit for bit.  N = 108 (one padded tile), 132 and 720
+    """Direct solves of these sizes run 64 x 64 output tiles in one launch per
+    product, the server's in grouped launches of runs per XCD: the digit sums
+    are exact and the update's arithmetic the same, so D is the same bit for
+    bit (and that of 128 x 128 tiles, which N = 3500 is checked against).  N = 108 (one padded tile), 132 and 720
     (ragged), 1536, 2240 (17.5 padded tiles) and 3072 (several tiles per CU).
     Two planes resolve no gap at N = 720: both ways end with the same status."""
     import paper_1203_6836_amd as p
