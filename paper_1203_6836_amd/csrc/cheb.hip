@@ -49,13 +49,15 @@ __global__ __launch_bounds__(256) void k_cheb_traces(const double* __restrict__ 
 // one read of the S - 1 matrices.  HBM (or last-level cache) bound:
 // (S - 1 + NG) N^2 / 2 doubles read.  S is a template argument: with a run-time
 // bound on j the loads waited for one another (S = 32, N = 500: 46 us for one
-// multiple, 24 for two now; N = 2048: 204, and 122 for two, 4.7 TB/s).
-template <int S, int NG>
+// multiple, 24 for two now; N = 2048: 204, and 122 for two, 4.7 TB/s).  ROWS: row
+// y of the grid takes the sums j = y S .. y S + S - 1 of s = gridDim.y S.
+template <int S, int NG, bool ROWS>
 __global__ __launch_bounds__(256) void k_cheb_dots(const double* __restrict__ G0, const double* __restrict__ G1,
                                                    const double* __restrict__ T, int N, double* __restrict__ part) {
     const int nt = (N + CT - 1) / CT, ntiles = nt * (nt + 1) / 2;
     const size_t n2 = (size_t)N * N;
     const int c = threadIdx.x & 31, r0 = threadIdx.x >> 5;
+    const int j0 = ROWS ? blockIdx.y * S : 0, s = ROWS ? gridDim.y * S : S;
     double acc[NG][S];
 #pragma unroll
     for (int g = 0; g < NG; ++g)
@@ -72,12 +74,14 @@ __global__ __launch_bounds__(256) void k_cheb_dots(const double* __restrict__ G0
             const size_t e = (size_t)gi * N + gj;
             double v[S], g[NG];
 #pragma unroll
-            for (int j = 1; j < S; ++j) v[j] = T[(size_t)(j - 1) * n2 + e];
+            for (int j = ROWS ? 0 : 1; j < S; ++j)
+                if (j > 0 || j0 > 0) v[j] = T[(size_t)(j0 + j - 1) * n2 + e];
             g[0] = wgt * G0[e];
             if (NG > 1) g[NG - 1] = wgt * G1[e];
 #pragma unroll
             for (int k = 0; k < NG; ++k) {
-                if (gi == gj) acc[k][0] += g[k];
+                if (ROWS && j0 > 0) acc[k][0] += g[k] * v[0];
+                else if (gi == gj) acc[k][0] += g[k];
 #pragma unroll
                 for (int j = 1; j < S; ++j) acc[k][j] += g[k] * v[j];
             }
@@ -94,7 +98,7 @@ __global__ __launch_bounds__(256) void k_cheb_dots(const double* __restrict__ G0
         }
     __syncthreads();
     if (threadIdx.x < NG * S)
-        part[(size_t)threadIdx.x * gridDim.x + blockIdx.x] =
+        part[(size_t)(ROWS ? threadIdx.x / S * s + j0 + threadIdx.x % S : threadIdx.x) * gridDim.x + blockIdx.x] =
             (sw[0][threadIdx.x] + sw[1][threadIdx.x]) + (sw[2][threadIdx.x] + sw[3][threadIdx.x]);
 }
 
@@ -264,11 +268,21 @@ int cheb_round(int s) { return s <= 1 ? 1 : s <= 3 ? 2 : s <= 7 ? 4 : std::min(s
 
 hipError_t launch_cheb_dots(const double* G0, const double* G1, const double* T, int N, int s, double* part,
                             hipStream_t st) {
-    const dim3 grid(cheb_dot_blocks(N));
+    // Few tiles (up to N = 992) leave CUs idle, and a workgroup's time is the
+    // chain of its NG s wave sums: the sums are dealt over rows of the grid, four
+    // each.  s = 32, two multiples, N = 500: 24 -> 13 us; N = 1020 level.
+    const int nblk = cheb_dot_blocks(N);
+    if (nblk < 2 * device_cus() && s % 4 == 0 && s > 4) {
+        const dim3 grid(nblk, s / 4);
+        if (G1) hipLaunchKernelGGL((k_cheb_dots<4, 2, true>), grid, dim3(256), 0, st, G0, G1, T, N, part);
+        else hipLaunchKernelGGL((k_cheb_dots<4, 1, true>), grid, dim3(256), 0, st, G0, G1, T, N, part);
+        return hipGetLastError();
+    }
+    const dim3 grid(nblk);
     return with_stored(s, [&](auto sc) {
         constexpr int S = decltype(sc)::value;
-        if (G1) hipLaunchKernelGGL((k_cheb_dots<S, 2>), grid, dim3(256), 0, st, G0, G1, T, N, part);
-        else hipLaunchKernelGGL((k_cheb_dots<S, 1>), grid, dim3(256), 0, st, G0, G1, T, N, part);
+        if (G1) hipLaunchKernelGGL((k_cheb_dots<S, 2, false>), grid, dim3(256), 0, st, G0, G1, T, N, part);
+        else hipLaunchKernelGGL((k_cheb_dots<S, 1, false>), grid, dim3(256), 0, st, G0, G1, T, N, part);
         return hipGetLastError();
     });
 }
