@@ -488,6 +488,7 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     c->split.tz = tz;
     c->split.tau = o.tau;
     c->split.elem = o.threshold;
+    c->split.nb = (N + 31) / 32;
     unsigned* hz = tz ? reinterpret_cast<unsigned*>(tz) + (size_t)3 * tri_tiles(nt) + 2 : nullptr;
     // the work-list path alternates two env buffers: product g reads the g-th
     // (mod 2) and clears the other for the threshold pass behind it
@@ -506,9 +507,11 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     HIPCHK(c, launch_check_h(H, N, c->chk, &nchk, st, hz));
     HIPCHK(c, launch_gershgorin(H, N, part, &ns, st, hz));
     HIPCHK(c, launch_bounds(part, ns, c->chk, nchk, c->st, st));
-    if (o.tau > 0.0)   // X_0 formed and thresholded in one pass over H
+    // X_0 formed and thresholded in one pass over H, zero blocks left out
+    // unless the block rule keeps them (tau^2 rounds to zero)
+    if (o.tau > 0.0)
         HIPCHK(c, launch_block_threshold(buf0, buf1, ld, N, o.tau, o.threshold, c->st, part, &ns, 1, st, env, tz,
-                                         nullptr, false, H, hz));
+                                         nullptr, false, H, o.threshold || o.tau * o.tau > 0.0 ? hz : nullptr));
     else
         HIPCHK(c, launch_init(H, N, ld, buf0, c->st, part, &ns, st, upper ? c->split.rmax : nullptr));
     HIPCHK(c, launch_ctrl_init(part, ns, c->st, a, st));

@@ -1365,10 +1365,10 @@ __global__ __launch_bounds__(256, 2) void k_gemm_int8x_list64(double* __restrict
 
 // What the threshold pass leaves behind beside X, from the block sums of the
 // 64 x 64 tiles: the tile's partials and flag, its panels' ranges and masks,
-// and the kept count.  One thread per listed tile; the same sums in the same
-// order as threshold_tile.
-__global__ __launch_bounds__(64) void k_tile_finish(State* __restrict__ st, int nt, List64 a, double* __restrict__ part,
-                                                    int* __restrict__ env, int* __restrict__ tz,
+// and the kept count (of the nb x nb blocks without the padding).  One thread
+// per listed tile; the same sums in the same order as threshold_tile.
+__global__ __launch_bounds__(64) void k_tile_finish(State* __restrict__ st, int nt, int nb, List64 a,
+                                                    double* __restrict__ part, int* __restrict__ env, int* __restrict__ tz,
                                                     const int* __restrict__ list, const int* __restrict__ list_ctr) {
     if (st->done || st->phase != 1 || st->full_fill) return;
     const int T = nt * (nt + 1) / 2, n = list_ctr[0];
@@ -1400,7 +1400,10 @@ __global__ __launch_bounds__(64) void k_tile_finish(State* __restrict__ st, int 
         part[3 * t + 2] = (id[0] + id[1]) + (id[2] + id[3]);
         tzn[t] = bits == 0 ? 1 : 0;
         if (bits == 0) continue;
-        kept += (mirror ? 2 : 1) * __popc(bits);
+        // of the padding's blocks, zero and below tau, none counts (nor is one
+        // kept, unless tau^2 rounds to zero)
+        const int in_r = (1 << 4 * min(4, nb - 4 * bi)) - 1, in_c = 0x1111 * ((1 << min(4, nb - 4 * bj)) - 1);
+        kept += (mirror ? 2 : 1) * __popc(bits & in_r & in_c);
         // kept column sub-blocks of panel bi, row sub-blocks of panel bj
         const int cols = (bits | bits >> 4 | bits >> 8 | bits >> 12) & 15;
         int rows = 0;
@@ -1603,8 +1606,8 @@ static hipError_t launch_list_kernel(SplitScratch& s, double* buf0, double* buf1
         const List64 a = {s.tau, s.elem, a0, a0 + (size_t)4 * T, a0 + (size_t)20 * T};
         hipLaunchKernelGGL((k_gemm_int8x_list64<S, NL>), dim3(grid), dim3(256), sizeof(I8Smem64<S>), stream, buf0,
                            buf1, ld, st, s.digits, s.scale, a, env, s.tz, list, ctr);
-        hipLaunchKernelGGL(k_tile_finish, dim3(std::min((T + 63) / 64, device_cus())), dim3(64), 0, stream, st, nt, a,
-                           part, s.env_next, s.tz, list, ctr);
+        hipLaunchKernelGGL(k_tile_finish, dim3(std::min((T + 63) / 64, device_cus())), dim3(64), 0, stream, st, nt,
+                           s.nb, a, part, s.env_next, s.tz, list, ctr);
     } else {
         const int grid = std::min(T, device_cus());
         hipLaunchKernelGGL((k_gemm_int8x_list<S, NL>), dim3(grid), dim3(512), sizeof(I8Smem<S>), stream, buf0, buf1,

@@ -44,6 +44,7 @@ struct SplitScratch {
                                 // the threshold itself:
     double tau = 0.0;
     int elem = 0;
+    int nb = 0;                 // 32-column blocks of the unpadded N
 };
 
 int split_reserve(SplitScratch& s, int ld, int slices, bool bf16);

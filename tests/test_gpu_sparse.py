@@ -415,3 +415,25 @@ def test_unwritten_zero_tiles(ctx, N, rule):
     for D, st in out[1:]:
         assert np.array_equal(D, D0)
         assert st["branches"] == s0["branches"] and st["fill_hist"] == s0["fill_hist"]
+
+
+@pytest.mark.parametrize("N", [16, 64, 130, 160, 1001])
+def test_int8x_tiny_tau_equals_dense(ctx, N):
+    """A tau whose square rounds to zero drops no 32 x 32 block, zero ones
+    included: the int8 solve of a banded H under the block rule takes the
+    dense one's products and branches to the same D, every block inside N
+    counts as kept and none of the padding's does (N = 16 to 160 are padded
+    to twice their blocks and more)."""
+    import paper_1203_6836_amd as p
+    rng = np.random.default_rng(N)
+    d = np.abs(np.subtract.outer(np.arange(N), np.arange(N)))
+    H = np.triu(np.where(d <= 8, rng.uniform(-0.2, 0.2, (N, N)), 0.0), 1)
+    H = H + H.T + np.diag(np.where(np.arange(N) % 2 == 0, -2.0, 2.0))
+    n_occ = (N + 1) // 2
+    say(f"case int8x tau=1e-300 N={N}")
+    D0, s0 = ctx.sp2_density_matrix(to_dev(H), n_occ, p.options("int8x"))
+    D1, s1 = ctx.sp2_density_matrix(to_dev(H), n_occ, p.options("int8x", tau=1e-300))
+    say(f"  products {s0['iterations']} / {s1['iterations']}, fill {s1['fill_min']}..{s1['fill_max']}")
+    assert s0["iterations"] == s1["iterations"] and s0["branches"] == s1["branches"]
+    assert np.array_equal(D0.cpu().numpy(), D1.cpu().numpy())
+    assert s1["fill_min"] == 1.0 and s1["fill_max"] == 1.0
