@@ -92,24 +92,31 @@ struct Arena {
     }
 };
 
-// Device footprint of one request and its layout inside its arena block.
+// Device footprint of one request and its layout inside its arena block.  The
+// partials and the row maxima are last used by the last product's encode and
+// control step, and D is formed behind them on the same stream: they lie in
+// D's memory.  Where D is too small for that (N < 19) the row maxima take the
+// place of the H check's partials, last read before X_0 sets the maxima.
 struct Layout {
     size_t H, X, digits, scale, part, chk, rmax, D, q, total;
 };
 Layout layout_for(int N, int slices) {
     const size_t ld = align_up((size_t)N, kTile);
     const size_t nt = ld / kGroupTile;
+    const size_t D_bytes = (size_t)N * N * 8, rmax_bytes = 2 * ld * 8;
+    const size_t part_bytes = align_up(std::max<size_t>(nt * (nt + 1) / 2, ld / 4) * 3 * 8, 256);
+    const bool in_D = part_bytes + rmax_bytes <= D_bytes;
     Layout L;
     size_t o = 0;
     L.H = o;      o = align_up(o + (size_t)N * N * 8, 256);
     L.X = o;      o = align_up(o + 2 * ld * ld * 8, 256);
     L.digits = o; o = align_up(o + (size_t)slices * ld * ld, 256);
     L.scale = o;  o = align_up(o + ld * 8, 256);
-    L.part = o;   o = align_up(o + std::max<size_t>(nt * (nt + 1) / 2, ld / 4) * 3 * 8, 256);
+    L.part = o;   o += in_D ? 0 : part_bytes;
     L.chk = o;    o = align_up(o + 2 * (size_t)kCheckGrid * 8, 256);
-    // the row maxima are last used by the last product, D is formed after it
-    L.D = L.rmax = o;
-    o = align_up(o + std::max((size_t)N * N * 8, 2 * ld * 8), 256);
+    L.D = o;      o = align_up(o + D_bytes, 256);
+    if (in_D) L.part = L.D;
+    L.rmax = in_D ? L.D + part_bytes : L.chk;
     L.q = o;      o = align_up(o + (size_t)(N / 4 + 1) * 8, 256);
     L.total = o;
     return L;

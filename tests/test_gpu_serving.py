@@ -207,3 +207,35 @@ def test_tiles_left_over_in_the_last_round(ctx, n_atoms, recipe):
     Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(H).cuda(), 2 * n_atoms, p.options("int8x", **recipe))
     assert st["branches"] == sd["branches"]
     assert np.array_equal(D, Dd.cpu().numpy())
+
+
+@pytest.mark.parametrize("n_atoms,recipe", [(4, {"slices": 2}), (512, {}), (1053, {"slices": 4, "levels": 5})])
+def test_request_of_exactly_its_footprint(ctx, n_atoms, recipe):
+    """A request is accepted by a server whose budget is just the arrays that a
+    solve needs side by side (H, two padded X, the digit planes, row scales,
+    partial sums of 128 x 128 tiles, the H check's partials, D and charges, each
+    rounded up to 256 bytes), and equals the direct solve bit for bit: N = 16
+    (smaller than the smallest budget, 1 MiB), 2048 and 4212."""
+    import torch
+    import paper_1203_6836_amd as p
+    H = request_H(n_atoms, 61)
+    N = H.shape[0]
+    ld = (N + 127) // 128 * 128
+    nt = ld // 128
+    arrays = (8 * N * N, 16 * ld * ld, recipe.get("slices", 5) * ld * ld, 8 * ld, 24 * max(nt * (nt + 1) // 2, ld // 4),
+              2 * 2048 * 8, 8 * N * N, 8 * (N // 4 + 1))
+    need = sum((a + 255) // 256 * 256 for a in arrays)
+    say(f"case footprint N={N}: {need} bytes")
+    srv = p.Server(ctx, hbm_budget_bytes=max(need, 1 << 20), max_slots=1, **recipe)
+    opts = p.options("int8x", **recipe)
+    try:
+        D, _, st = srv.sp2_server_wait(srv.sp2_server_submit(H, 2 * n_atoms), N)
+    except p.Sp2Error as e:
+        status, _ = ctx.sp2_density_matrix_status(torch.from_numpy(H).cuda(), 2 * n_atoms, opts)
+        assert status == e.status != p.SP2_EBUDGET
+        return
+    finally:
+        srv.close()
+    Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(H).cuda(), 2 * n_atoms, opts)
+    assert st["branches"] == sd["branches"]
+    assert np.array_equal(D, Dd.cpu().numpy())
