@@ -10,7 +10,7 @@ namespace sp2 {
 constexpr int kChebMaxS = 32;       // most stored polynomials T_1 .. T_s
 constexpr int kChebBlocks = 1024;   // most workgroups (and partials per sum) of the dot kernel
 
-// T1 = (H - c I) * inv_w.
+// T1 = ((H + H^T) / 2 - c I) * inv_w, exactly symmetric.
 hipError_t launch_cheb_scale(const double* H, int N, double c, double inv_w, double* T1, hipStream_t s);
 // out[j - 1] = Tr T_j of the s matrices T (T_j at T + (j - 1) N^2).
 hipError_t launch_cheb_traces(const double* T, int N, int s, double* out, hipStream_t st);

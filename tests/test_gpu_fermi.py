@@ -390,3 +390,23 @@ def test_expansion_is_the_recursions_function(ctx, n, kT, steps, max_newton):
     assert passes * 2 * steps <= ctx.last_fermi_products <= passes * 10 * steps
     if max_newton:
         assert abs(np.trace(D) - n_occ) < 1.01 * tol
+
+
+@pytest.mark.parametrize("N,kT,mu", [(45, 1e7, None), (45, 0.5, -19.0), (500, 1e7, None), (500, 0.5, None)])
+def test_density_is_exactly_symmetric(ctx, N, kT, mu):
+    """H symmetric only to 5e-13 of its largest element (the check's bound is
+    1e-12) still gives an exactly symmetric D: where two polynomials carry the
+    Fermi function (kT = 1e7), at a fixed mu far below the spectrum, and where
+    products of the stored polynomials carry it."""
+    rng = np.random.default_rng(N)
+    H = rng.uniform(-1.0, 1.0, (N, N)) / np.sqrt(N)
+    H = (H + H.T) / 2 + np.diag(np.where(np.arange(N) % 2 == 0, -2.0, 2.0))
+    lower = np.tril(rng.uniform(-5e-13, 5e-13, (N, N)) * np.abs(H).max(), -1)
+    say(f"case symmetric D N={N} kT={kT}")
+    kw = {"max_newton": 0, "mu": mu} if mu is not None else {"tol": 1e-8}
+    D, m, _ = ctx.sp2_fermi_density_matrix(to_dev(H + lower), N / 2.0, kT, 16, **kw)
+    D = D.cpu().numpy()
+    Dd = fermi.fermi_density(H, N / 2.0, kT, solver="lapack")[0] if mu is None else None
+    assert np.array_equal(D, D.T)
+    if Dd is not None:
+        assert np.abs(D - Dd).max() < 1e-8
