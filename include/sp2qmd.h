@@ -600,7 +600,8 @@ void sp2_server_options_default(sp2_server_options *opt);
 /* Start a server on the context's device with its own stream and scheduler
  * thread.  Requests are admitted in arrival order whenever a slot is free and
  * their device footprint (about 37 N^2 bytes for 5 planes) fits in the arena;
- * they start in that order while the running ones leave room on the chip;
+ * they start in that order while the running ones leave room on the chip
+ * (N <= 640 at once, N = 641-3968 and N > 3968 each among themselves);
  * every tick advances all started systems by one product in grouped,
  * graph-replayed launches, and finished systems are retired and replaced
  * between ticks.  Each result is independent of the other requests in flight. */

@@ -6,8 +6,9 @@
 // hbm_budget_bytes made at creation, carved by a first-fit allocator), runs
 // H is uploaded on a copy stream; once it has landed, the per-system start
 // kernels (H check, bounds, X_0, first branch) run on the compute stream and
-// the system joins the group, in order of arrival while the group has room
-// (kGroupFill); the group advances every started system by
+// the system joins the group, at once if it is small, else in order of arrival
+// while the group has room for its class of size (kGroupFill); the group
+// advances every started system by
 // iters_per_tick SP2 products per tick with grouped launches (encode,
 // product, control) that cover all tiles of all systems in the group.  The
 // launches are captured once in a hipGraph and replayed every tick; only the
@@ -223,7 +224,15 @@ struct sp2_server {
 // the chip busy, and with fewer systems side by side the first ones finish,
 // and their results leave for the host, while the others compute (24 requests
 // of N = 128-2048: 47 ms without a limit, 42 at 1024-2048, 45 at 3072, 47 at 600).
+// Each class has the room for itself: a larger system fills the chip whatever
+// runs beside it, so these run one after another (two of N = 8192: 505 ms, 538
+// side by side), and if all the others counted with it, they would wait for its
+// whole solve (eight of N = 128 behind one of N = 8192: mean latency 256 ms, 214
+// beside it).  Small ones add a few percent to a full group's product and never
+// wait (one of N = 128 behind 28 of N = 2048: 117 ms, 13 beside the first).
 constexpr int kGroupFill = 2048;
+constexpr int kGroupFast = 55;   // N <= 640
+static int group_class(int tiles) { return tiles <= kGroupFast ? 0 : tiles <= kGroupFill ? 1 : 2; }
 
 static int group_tiles(int N) { return tri_tiles((int)(align_up((size_t)N, kTile) / kGroupTile)); }
 
@@ -481,13 +490,19 @@ void sp2_server::loop() {
             uploading.push_back(r);
             if (rc == SP2_OK) rc = begin_upload(r);
         }
-        // systems whose H has landed start and join the group, in order of
-        // arrival while the group has room
-        int tiles = 0;
+        // systems whose H has landed start and join the group, each class in
+        // order of arrival while it has room
+        int tiles[3] = {};
+        bool full[3] = {};
         for (Request* r : slots)
-            if (r && r->started) tiles += group_tiles(r->N);
+            if (r && r->started) tiles[group_class(group_tiles(r->N))] += group_tiles(r->N);
         for (auto it = uploading.begin(); rc == SP2_OK && it != uploading.end();) {
-            if (tiles > 0 && tiles + group_tiles((*it)->N) > kGroupFill) break;
+            const int t = group_tiles((*it)->N), cl = group_class(t);
+            full[cl] = full[cl] || (cl > 0 && tiles[cl] > 0 && tiles[cl] + t > kGroupFill);
+            if (full[cl]) {
+                ++it;
+                continue;
+            }
             const hipError_t e = hipEventQuery((*it)->ev_up);
             if (e == hipErrorNotReady) {
                 ++it;
@@ -498,7 +513,7 @@ void sp2_server::loop() {
                 break;
             }
             (*it)->started = true;
-            tiles += group_tiles((*it)->N);
+            tiles[cl] += t;
             group_dirty = true;
             it = uploading.erase(it);
         }

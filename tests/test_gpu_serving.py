@@ -239,3 +239,36 @@ def test_request_of_exactly_its_footprint(ctx, n_atoms, recipe):
     Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(H).cuda(), 2 * n_atoms, opts)
     assert st["branches"] == sd["branches"]
     assert np.array_equal(D, Dd.cpu().numpy())
+
+
+@pytest.mark.parametrize("first", [[1152], [992, 160]])
+def test_requests_that_do_not_wait_for_room(ctx, first):
+    """A request of N = 640 that needs a few products starts at once and ends
+    first, beside one larger than the group's room (N = 4608, about 60
+    products) and where a large and a middle one (N = 3968 and 640) fill it."""
+    import paper_1203_6836_amd as p
+    say(f"case serving beside {[4 * n for n in first]}")
+    Hs = [request_H(n, 71) for n in first]
+    rng = np.random.default_rng(7)
+    quick = np.triu(rng.uniform(-1e-3, 1e-3, (640, 640)), 1)
+    quick = quick + quick.T + np.diag(np.where(np.arange(640) % 2 == 0, -1.0, 1.0))
+    srv = p.Server(ctx, max_slots=4)
+    for h in Hs + [quick]:   # every buffer of the requests below exists
+        srv.sp2_server_wait(srv.sp2_server_submit(h, h.shape[0] // 2), h.shape[0], want_D=False)
+    tk = [srv.sp2_server_submit(h, h.shape[0] // 2) for h in Hs]
+    tq = srv.sp2_server_submit(quick, 320)
+    _, _, st = srv.sp2_server_wait(tq, 640, want_D=False)
+    running = []
+    for t, h in zip(tk, Hs):
+        try:
+            srv.sp2_server_wait(t, h.shape[0], timeout_s=0.0, want_D=False)
+            running.append(False)
+        except p.Sp2Error as e:
+            assert e.status == p.SP2_ETIMEOUT
+            running.append(True)
+    for t, h, r in zip(tk, Hs, running):
+        if r:
+            srv.sp2_server_wait(t, h.shape[0], want_D=False)
+    srv.close()
+    say(f"  quick one: {st['iterations']} products, {st['ms']:.1f} ms; others still running {running}")
+    assert st["iterations"] < 16 and all(running)
