@@ -328,7 +328,8 @@ sp2_status sp2_mulliken_overlap(sp2_ctx *ctx, int n_atoms, const double *D, cons
  * polynomials in H, formed as a symmetric FP64 MFMA product of upper tiles,
  * so each X is exactly symmetric; the inverse by Newton-Schulz), or, where
  * that takes fewer products, by the Chebyshev expansion of the same function
- * of H (mu then comes from moments, at most 32 GiB of work matrices).  Its
+ * of H (mu then comes from moments; at most 32 GiB of work matrices and half
+ * of the device's free memory, what exceeds 2 GiB given back at the end).  Its
  * exponent carries a relative error of about (beta |e - mu| / 2^n_steps)^2
  * / 12 per eigenvalue e; FP64 rounding sets a floor near 1e-11 for
  * n_steps >= 16.

@@ -87,6 +87,7 @@ struct sp2_ctx {
     // Y / H_perp, T / D_perp, W) plus reduction slots
     double* nobuf = nullptr;
     size_t nocap = 0;
+    bool noback = false;   // more than kNobufKeep: given back when the call ends
     // non-orthogonal finite-temperature solves: Z, H_perp, D_perp kept
     // across the Fermi-operator and entropy calls (which use nobuf)
     double* ftbuf = nullptr;
@@ -128,7 +129,8 @@ static sp2_status fail(sp2_ctx* c, sp2_status s, const std::string& msg) {
 // One call at a time per context: the first call of a thread takes the
 // context, nested calls of the same thread pass, a call of another thread
 // meanwhile returns SP2_EBUSY (without touching the error string, which the
-// owner may be writing).
+// owner may be writing).  The call that owns the context gives nobuf back at its
+// end where it asked for that.
 static unsigned long long thread_token() {
     static std::atomic<unsigned long long> next{1};
     thread_local unsigned long long t = next.fetch_add(1);
@@ -145,7 +147,14 @@ struct CtxGuard {
         else ok = expected == me;
     }
     ~CtxGuard() {
-        if (owner) c->owner.store(0);
+        if (!owner) return;
+        if (c->noback) {
+            (void)hipFree(c->nobuf);
+            c->nobuf = nullptr;
+            c->nocap = 0;
+            c->noback = false;
+        }
+        c->owner.store(0);
     }
     CtxGuard(const CtxGuard&) = delete;
     CtxGuard& operator=(const CtxGuard&) = delete;
@@ -1165,8 +1174,11 @@ extern "C" sp2_status sp2_density_matrix_nonorth(sp2_ctx* c, int N, const double
 // Tr T_(qs+j) = 2 <T_qs, T_j> - Tr T_|qs-j|.  s is about sqrt(m), which makes
 // the products fewest while the elements read for the dots stay m N^2 / 2.
 // The matrices (s + 2 of N x N) lie in nobuf: at most 32 GiB of them, but
-// always the five of the recursion; an allocation that fails is tried again
-// with fewer.
+// always the five of the recursion; an allocation that fails, or would leave
+// other allocators on the device less than it takes itself, is tried again
+// with fewer.  Beyond kNobufKeep (N = 2800 with 32 stored) the buffer is given
+// back at the end of the call: 0.6 ms of calls that take 80 and more.
+constexpr size_t kNobufKeep = (size_t)2 << 30;
 struct ChebBasis {
     int s = 0;            // stored polynomials, T_j at T + (j - 1) N^2
     double* T = nullptr;
@@ -1188,10 +1200,16 @@ static sp2_status cheb_moments(sp2_ctx* c, int N, const double* H, double ctr, d
     sp2_status s = SP2_ENOMEM;
     for (b->s = cheb_stored(N, m); b->s >= min_s; b->s = b->s == 1 ? 0 : cheb_round(b->s / 2)) {
         const size_t slots = (size_t)cheb_multiples(m, b->s) * b->s;
-        size_t nb = c->nocap;
-        s = grow(c, (void**)&c->nobuf, &nb,
-                 ((b->s + 2) * n2 + slots * (nblk + 1) + kChebMaxS) * sizeof(double));
+        const size_t need = ((b->s + 2) * n2 + slots * (nblk + 1) + kChebMaxS) * sizeof(double);
+        size_t nb = c->nocap, free_b = 0, total_b = 0;
+        const bool more = need > nb;
+        if (more && b->s > 1 && hipMemGetInfo(&free_b, &total_b) == hipSuccess && need > (free_b + nb) / 2) {
+            s = fail(c, SP2_ENOMEM, "no room for the Chebyshev expansion's matrices");
+            continue;
+        }
+        s = grow(c, (void**)&c->nobuf, &nb, need);
         c->nocap = nb;
+        if (s == SP2_OK && more && nb > std::max(kNobufKeep, 5 * n2 * sizeof(double))) c->noback = true;
         if (s != SP2_ENOMEM) break;
     }
     if (s != SP2_OK) return s;

@@ -410,3 +410,29 @@ def test_density_is_exactly_symmetric(ctx, N, kT, mu):
     assert np.array_equal(D, D.T)
     if Dd is not None:
         assert np.abs(D - Dd).max() < 1e-8
+
+
+def test_expansion_gives_its_matrices_back(ctx):
+    """N = 3400: the stored polynomials of the expansion take 3.1 GB during a
+    call; after it the context keeps at most 2 GiB (the recursion's five
+    matrices would be 0.46 GB), and a second call gives the same D."""
+    import torch
+    import paper_1203_6836_amd as p
+    N = 3400
+    say(f"case fermi work matrices N={N}")
+    rng = np.random.default_rng(N)
+    H = rng.uniform(-1.0, 1.0, (N, N)) / np.sqrt(N)
+    Hd = to_dev((H + H.T) / 2 + np.diag(np.where(np.arange(N) % 2 == 0, -2.0, 2.0)))
+    out = [torch.empty_like(Hd) for _ in range(2)]
+    c = p.Context(0)
+    torch.cuda.synchronize()
+    free0 = torch.cuda.mem_get_info()[0]
+    kept = []
+    for D in out:
+        c.sp2_fermi_density_matrix(Hd, N / 2.0, 0.3, 16, tol=1e-7, D_out=D)
+        c.sp2_fermi_entropy(Hd, 0.0, 0.3)
+        kept.append(free0 - torch.cuda.mem_get_info()[0])
+    say(f"  kept {kept}")
+    c.close()
+    assert max(kept) <= (2 << 30) + (64 << 20)
+    assert torch.equal(out[0], out[1])
