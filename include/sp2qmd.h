@@ -234,7 +234,9 @@ sp2_status sp2_density_matrix_noalloc(sp2_ctx *ctx, int N, const double *H, int 
  * G in {0 (row-major), 4, 8, 16, 32}) and, for INT8X, the K-stage
  * configuration of the LDS staging ring (stage_cfg 0: 64-byte K stages two
  * deep (32-byte three deep at six planes), 1: 32-byte stages three deep, 2:
- * 32-byte stages four deep, up to five planes), for FP64 the most chunks of a
+ * 32-byte stages four deep, up to five planes), all on 128 x 128 tiles (dense
+ * solves without an FP64 head run 64 x 64 tiles up to a padded N of 2304 and at
+ * 2944-3328, which take the tile order only), for FP64 the most chunks of a
  * tile split along K (8 or 16) and, up to a padded N of 3968, the output tile
  * shape (128 x 128 tiles of 4 waves, or 32 x 32 tiles whose waves split K,
  * no tile order; without an entry pure FP64 solves take the 32 x 32 tile

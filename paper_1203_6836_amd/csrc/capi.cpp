@@ -459,6 +459,7 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     // their upper tiles only and the encode reads the upper triangle
     const bool upper = int8x && o.tau == 0.0 && o.fp64_head == 0;
     c->split.upper = upper;
+    c->split.tile64 = true;
     const TuneChoice tc = tuned_choice(c, ld, o.precision, int8x ? o.slices : 0, int8_levels(o));
     const int tile_group = o.tile_group >= 0 ? o.tile_group : tc.tile_group;
     c->split.tile_group = tile_group;
@@ -846,6 +847,10 @@ extern "C" sp2_status sp2_autotune(sp2_ctx* c, int N, int precision, int slices,
         if (split_reserve(c->split, ld, int8x ? slices : 0, bf16x || fp32) != 0)
             return fail(c, SP2_ENOMEM, "device allocation for split operands failed");
         c->split.upper = int8x;
+        // also where dense solves run 64 x 64 tiles, which have no stage
+        // layouts: the entry is what solves with an FP64 head read there, and is
+        // lent to sizes up to twice this one
+        c->split.tile64 = false;
         c->split.levels = nl;
         c->split.env = nullptr;
         c->split.tz = nullptr;

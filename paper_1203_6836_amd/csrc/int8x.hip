@@ -1667,7 +1667,7 @@ static hipError_t run_int8x(SplitScratch& s, double* buf0, double* buf1, int ld,
         return e;
     }
     if (env) return launch_tile_kernel<S, NL, true, false>(s, buf0, buf1, ld, st, part, stream, env);
-    if (s.upper && use_tile64(ld)) return launch_t64<S, NL>(s, buf0, buf1, ld, st, part, stream);
+    if (s.upper && s.tile64 && use_tile64(ld)) return launch_t64<S, NL>(s, buf0, buf1, ld, st, part, stream);
     // dense products: the stage configuration chosen by the autotuner
     if constexpr (i8_cfg_ok(S, 2)) {
         if (s.stage_cfg == 2)
@@ -1849,7 +1849,7 @@ hipError_t launch_int8x_encode(SplitScratch& s, const double* buf0, const double
 
 hipError_t launch_int8x_gemm(SplitScratch& s, double* buf0, double* buf1, int ld, State* st, double* part,
                              int* nslots, hipStream_t stream, const int* env) {
-    const bool small = s.upper && !env && use_tile64(ld);
+    const bool small = s.upper && s.tile64 && !env && use_tile64(ld);
     *nslots = tri_tiles(ld / (small ? QT : QB)) + (s.upper && !env && !small && left_in_pieces(ld) ? 3 * left_tiles(s, ld) : 0);
     const bool next = s.levels == s.slices + 1;
     if (!next && s.levels != s.slices) return hipErrorInvalidValue;

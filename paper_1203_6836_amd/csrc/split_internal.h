@@ -34,6 +34,7 @@ struct SplitScratch {
     // products from the first product on only; null otherwise), followed by
     // room for the product's work list (T entries) and 2 counters
     const int* env = nullptr;
+    bool tile64 = true;         // dense upper-only products may run 64 x 64 tiles (the autotuner times the others)
     int* env_next = nullptr;    // with tz: the buffer the threshold pass behind the next product records into
     int* tz = nullptr;
     // thresholded int8 products: besides the work-list product, launch the

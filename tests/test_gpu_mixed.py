@@ -378,3 +378,23 @@ def test_int8x_small_output_tile_equals_the_large_one(ctx, n_atoms, recipe):
     say(f"  N={H.shape[0]} iterations {st['iterations']} / {st_srv['iterations']}")
     assert st["branches"] == st_srv["branches"]
     assert np.array_equal(D.cpu().numpy(), D_srv)
+
+
+def test_autotuner_times_the_large_output_tile(ctx):
+    """N = 720: dense solves run 64 x 64 tiles, which have no stage layouts.  The
+    candidates are the 128 x 128 kernel's, whose entry solves with an FP64 head
+    and larger sizes take, and which needs about twice a solve's time per
+    product (its control step and start included) at this size."""
+    import torch
+    import paper_1203_6836_amd as p
+    pos = synth.lattice_positions((6, 6, 5), seed=12)
+    H = ctx.tb_hamiltonian(synth.STATIC_MODEL, torch.from_numpy(pos).cuda())
+    c = p.Context(0)
+    r = c.sp2_autotune(H.shape[0], "int8x")
+    best = min(c.sp2_density_matrix(H, 2 * len(pos), p.options("int8x"))[1]["ms"] for _ in range(5))
+    _, st = c.sp2_density_matrix(H, 2 * len(pos), p.options("int8x"))
+    c.close()
+    per = best / st["iterations"]
+    fastest = min(r["ms_per_product"].values())
+    say(f"case autotuner N=720: fastest candidate {fastest * 1e3:.1f} us, solve {per * 1e3:.1f} us a product")
+    assert fastest > 1.3 * per
