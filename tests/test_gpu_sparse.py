@@ -95,6 +95,8 @@ def test_int8x_threshold_full_size(ctx):
     assert abs(float(torch.trace(Ds)) - w.n_occ) < 1e-3
 
 
+# Up to a padded N of 4096 dense_fill changes nothing (the first three cases);
+# test_dense_switch_above_padded_4096 has both rules where the switch is made.
 @pytest.mark.parametrize("case,rule", [("8x8x8", 0), ("6x6x5", 0), ("6x6x5", 1), ("sparse", 0)])
 def test_dense_switch_is_exact(ctx, case, rule):
     """Thresholded int8 solves give bitwise the same D, products, branches and
@@ -437,3 +439,30 @@ def test_int8x_tiny_tau_equals_dense(ctx, N):
     assert s0["iterations"] == s1["iterations"] and s0["branches"] == s1["branches"]
     assert np.array_equal(D0.cpu().numpy(), D1.cpu().numpy())
     assert s1["fill_min"] == 1.0 and s1["fill_max"] == 1.0
+
+
+@pytest.mark.parametrize("rule,tau,recipe", [(0, 1e-5, {}), (1, 1e-5, {}), (1, 1e-6, {"slices": 4, "levels": 5})])
+def test_dense_switch_above_padded_4096(ctx, rule, tau, recipe):
+    """Below a padded N of 4352 the dense tile kernel never runs; here (N = 4300,
+    ragged, a 3-D lattice that fills up) it takes over from the work list at the
+    kept fraction 0.95, at 0.5, or runs from the first product on (dense_fill 0):
+    the same D, branches and fill per update as the work list alone, bit for
+    bit, under both threshold rules, and within their tolerance of the dense
+    solve."""
+    import torch
+    import paper_1203_6836_amd as p
+    pos = synth.lattice_positions(synth.cube_dims_for(1075), seed=9, n_atoms=1075)
+    H = ctx.tb_hamiltonian(synth.STATIC_MODEL, to_dev(pos))
+    n_occ = 2 * len(pos)
+    say(f"case dense switch N={H.shape[0]} rule={rule} tau={tau}")
+    D2, s2 = ctx.sp2_density_matrix(H, n_occ, p.options("int8x", tau=tau, threshold=rule, dense_fill=2.0, **recipe))
+    fills = s2["fill_hist"][:s2["iterations"] - 1]
+    say("  fill per update: " + " ".join(f"{f:.3f}" for f in fills))
+    assert fills[0] < 0.5 and max(fills) >= 0.95   # the switches below do happen
+    for f in (0.95, 0.5, 0.0):
+        D, st = ctx.sp2_density_matrix(H, n_occ, p.options("int8x", tau=tau, threshold=rule, dense_fill=f, **recipe))
+        assert st["iterations"] == s2["iterations"] and st["branches"] == s2["branches"]
+        assert st["fill_hist"] == s2["fill_hist"]
+        assert torch.equal(D, D2)
+    D0, _ = ctx.sp2_density_matrix(H, n_occ, p.options("int8x", **recipe))
+    assert float(torch.linalg.norm(D2 - D0)) / H.shape[0] ** 0.5 < 1e-2
