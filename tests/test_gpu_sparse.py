@@ -380,6 +380,8 @@ def test_blocksparse_scattered_n16384_fp64_against_oracle(ctx):
     del D, H
     torch.cuda.empty_cache()
 
+# (N = 4225 keeps too few blocks for the 128 x 128 list tiles: these are in
+# test_large_list_tiles_with_unwritten_zero_tiles.)
 @pytest.mark.parametrize("N,rule", [(129, 0), (770, 1), (1001, 0), (1536, 1), (4225, 0)])
 def test_unwritten_zero_tiles(ctx, N, rule):
     """The work-list products leave tiles of X that are all zero unwritten, and
@@ -466,3 +468,45 @@ def test_dense_switch_above_padded_4096(ctx, rule, tau, recipe):
         assert torch.equal(D, D2)
     D0, _ = ctx.sp2_density_matrix(H, n_occ, p.options("int8x", **recipe))
     assert float(torch.linalg.norm(D2 - D0)) / H.shape[0] ** 0.5 < 1e-2
+
+
+@pytest.mark.parametrize("N,rule", [(4301, 0), (4301, 1), (4736, 1)])
+def test_large_list_tiles_with_unwritten_zero_tiles(ctx, N, rule):
+    """Above a padded N of 4096 and an average K range of 2048 columns the work
+    list runs 128 x 128 tiles, which store zeros into a flagged X_n tile before
+    they read it.  A dense gapped block of 3/4 of the rows with a banded rest
+    behind it keeps the kept fraction above 0.5, while the band's tiles fill in
+    from their neighbours over the products; in buffers that hold an earlier
+    solve's X, D, branches and fill equal those of a fresh context and of the
+    dense tile kernel bit for bit, and D the oracle's within 1e-6 per sqrt(N)."""
+    import paper_1203_6836_amd as p
+    rng = np.random.default_rng(N + rule)
+    m = 3 * N // 4
+    ld = (N + 127) // 128 * 128
+    d = np.abs(np.subtract.outer(np.arange(N), np.arange(N)))
+    H = np.where(d <= 20, rng.uniform(-0.08, 0.08, (N, N)), 0.0)
+    H[:m, :m] = rng.uniform(-0.5, 0.5, (m, m)) / np.sqrt(m)
+    H = np.triu(H, 1)
+    H = H + H.T + np.diag(np.where(np.arange(N) % 2 == 0, -2.0, 2.0))
+    n_occ = (N + 1) // 2
+    tau = 1e-7
+    say(f"case large list tiles N={N} rule={rule}")
+    G = rng.uniform(-1.0, 1.0, (N, N))
+    ctx.sp2_density_matrix(to_dev((G + G.T) / 2 + np.diag(np.where(np.arange(N) % 2 == 0, -4.0 * N, 4.0 * N))), n_occ,
+                           p.options("int8x"))   # a full X in the buffers
+    out = []
+    fresh = p.Context(0)
+    for c, fill in ((ctx, 2.0), (fresh, 2.0), (ctx, 0.0)):
+        D, st = c.sp2_density_matrix(to_dev(H), n_occ, p.options("int8x", tau=tau, threshold=rule, dense_fill=fill))
+        out.append((D.cpu().numpy(), st))
+    fresh.close()
+    D0, s0 = out[0]
+    fills = s0["fill_hist"][:s0["iterations"] - 1]
+    say("  fill per update: " + " ".join(f"{f:.4f}" for f in fills))
+    assert min(fills) * ld > 2100 and max(fills) < 0.95      # 128 x 128 list tiles once the host has seen a product
+    assert max(fills[5:]) > fills[4]                         # tiles still fill in then
+    for D, st in out[1:]:
+        assert np.array_equal(D, D0)
+        assert st["branches"] == s0["branches"] and st["fill_hist"] == s0["fill_hist"]
+    ref = osp2.sp2(H, n_occ, tau=tau, threshold=("block", "element")[rule])
+    assert np.linalg.norm(D0 - ref.D) / np.sqrt(N) <= TOL_D
