@@ -211,6 +211,9 @@ def test_bf16x2_configured_recipe_reported(ctx, dims, seed):
     assert err < 1e-2
 
 
+# Dense int8 solves of N = 2048 run 64 x 64 tiles here and in the next test: the
+# stage layouts and orders of the 128 x 128 tiles are in
+# test_stage_layouts_of_the_large_output_tile.
 def test_autotune_and_tile_order_invariance(ctx):
     """The autotuner times every candidate launch configuration (tile order;
     int8: K-stage configuration; FP64: split cap and output tile) and keeps
@@ -398,3 +401,30 @@ def test_autotuner_times_the_large_output_tile(ctx):
     fastest = min(r["ms_per_product"].values())
     say(f"case autotuner N=720: fastest candidate {fastest * 1e3:.1f} us, solve {per * 1e3:.1f} us a product")
     assert fastest > 1.3 * per
+
+
+@pytest.mark.parametrize("n_atoms,head", [(640, 0), (180, 3), (512, 3)])
+def test_stage_layouts_of_the_large_output_tile(ctx, tmp_path, n_atoms, head):
+    """Every K-stage layout that a table entry selects gives bitwise the same D
+    where 128 x 128 tiles run: N = 2560 (padded the same), and behind an FP64
+    head N = 720 (ragged) and 2048; and every tile order."""
+    import torch
+    import paper_1203_6836_amd as p
+    pos = synth.lattice_positions(synth.cube_dims_for(n_atoms), seed=8, n_atoms=n_atoms)
+    H = ctx.tb_hamiltonian(synth.STATIC_MODEL, torch.from_numpy(pos).cuda())
+    N = H.shape[0]
+    ld = (N + 127) // 128 * 128
+    say(f"case stage layouts N={N} head={head}")
+    ctx.sp2_autotune(256, "int8x")
+    ctx.sp2_tune_save(str(tmp_path / "probe.txt"))
+    arch, cus = [l for l in (tmp_path / "probe.txt").read_text().splitlines() if not l.startswith("#")][0].split()[:2]
+    ref = None
+    for cfg in (0, 1, 2):
+        (tmp_path / "t.txt").write_text(f"{arch} {cus} {ld} 1 5 5 8 {cfg} 16 128 1.0\n")
+        cc = p.Context(0)
+        cc.sp2_tune_load(str(tmp_path / "t.txt"))
+        for g in (-1, 0, 4) if cfg else (-1, 0, 4, 8, 16):
+            D, st = cc.sp2_density_matrix(H, 2 * n_atoms, p.options("int8x", fp64_head=head, tile_group=g))
+            ref = D if ref is None else ref
+            assert torch.equal(D, ref), (cfg, g)
+        cc.close()
