@@ -325,6 +325,8 @@ def test_fp64_output_tile_from_table(ctx, tmp_path):
     cc.close()
 
 
+# N = 1024 and 4096 run 64 x 64 tiles and pieces: the K chunks are in
+# test_k_chunks_of_the_last_round_are_exact.
 @pytest.mark.parametrize("dims", [(4, 4, 16), (8, 8, 16)])
 def test_tail_split_is_exact(ctx, dims):
     """Splitting the K loops of the last wave's tiles (all 36 tiles at N = 1024,
@@ -428,3 +430,21 @@ def test_stage_layouts_of_the_large_output_tile(ctx, tmp_path, n_atoms, head):
             ref = D if ref is None else ref
             assert torch.equal(D, ref), (cfg, g)
         cc.close()
+
+
+@pytest.mark.parametrize("recipe", [{}, {"slices": 4, "levels": 5}, {"slices": 6}])
+def test_k_chunks_of_the_last_round_are_exact(ctx, recipe):
+    """From four rounds of 128 x 128 tiles over the CUs on, the tiles left for a
+    nearly empty last round are split along K and their int32 chunks summed: N =
+    5720 (ragged, 45 padded tiles a side: 11 of 1035 tiles left on 256 CUs)
+    gives the same D with and without, bit for bit."""
+    import torch
+    import paper_1203_6836_amd as p
+    say(f"case K chunks N=5720 {recipe}")
+    pos = synth.lattice_positions(synth.cube_dims_for(1430), seed=5, n_atoms=1430)
+    H = ctx.tb_hamiltonian(synth.STATIC_MODEL, torch.from_numpy(pos).cuda())
+    D0, s0 = ctx.sp2_density_matrix(H, 2860, p.options("int8x", tail_split=0, **recipe))
+    D1, s1 = ctx.sp2_density_matrix(H, 2860, p.options("int8x", **recipe))
+    say(f"  iters {s0['iterations']} / {s1['iterations']}  ms {s0['ms']:.1f} / {s1['ms']:.1f}")
+    assert s0["branches"] == s1["branches"]
+    assert torch.equal(D0, D1)
