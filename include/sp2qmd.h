@@ -357,11 +357,16 @@ sp2_status sp2_mulliken_overlap(sp2_ctx *ctx, int n_atoms, const double *D, cons
  * recursion over all passes (2 per step plus 2 per Newton-Schulz update; the
  * updates per inverse follow from a bound on X's spectrum, fewer in the first
  * steps, where X is near I/2); the expansion forms fewer for the same
- * result.  N <= 32768 (five N x N FP64 work matrices at least).  Blocks
+ * result (sp2_fermi_products_formed).  N <= 32768 (five N x N FP64 work matrices at least).  Blocks
  * the host until D_out is written. */
 sp2_status sp2_fermi_density_matrix(sp2_ctx *ctx, int N, const double *H, double n_occ, double kT,
                                     int n_steps, int max_newton, double tol, double *mu,
                                     double *D_out, int *newton_iterations, long long *products);
+/* N x N FP64 matrix products that this context's last finite-temperature call
+ * (sp2_fermi_density_matrix, _nonorth with its transforms, or
+ * sp2_fermi_entropy) launched, read before any other call: the expansion's or
+ * the recursion's, whichever ran (the latter's are *products above). */
+sp2_status sp2_fermi_products_formed(const sp2_ctx *ctx, long long *products);
 
 /* Electronic entropy (Eq. Entropy) in units of k_B:
  * S = -2 sum_i [f_i ln f_i + (1 - f_i) ln(1 - f_i)], f_i = (exp((e_i - mu)

@@ -129,6 +129,7 @@ _SIGS = {
     "sp2_fermi_entropy": (_I, [_P, _I, _P, _D, _D, ctypes.POINTER(_D), ctypes.POINTER(_I)]),
     "sp2_fermi_density_matrix": (_I, [_P, _I, _P, _D, _D, _I, _I, _D, ctypes.POINTER(_D), _P,
                                       ctypes.POINTER(_I), ctypes.POINTER(ctypes.c_longlong)]),
+    "sp2_fermi_products_formed": (_I, [_P, ctypes.POINTER(ctypes.c_longlong)]),
     "sp2_fermi_density_matrix_nonorth": (_I, [_P, _I, _P, _P, _D, _D, _I, _I, _D, ctypes.POINTER(_D), _P, _P,
                                               ctypes.POINTER(_D), ctypes.POINTER(_I)]),
     "tb_overlap": (_I, [_P, ctypes.POINTER(TBParams), ctypes.c_double, ctypes.c_double, _I, _P, _P]),
@@ -338,8 +339,8 @@ class Context:
 
         max_newton == 0 keeps mu fixed (it must be given); otherwise mu is the
         canonical chemical potential, Newton from mu (None: the middle of the
-        Gershgorin interval).  The N x N products the call made are left in
-        ``self.last_fermi_products``.
+        Gershgorin interval).  The N x N products of the recursion are left in
+        ``self.last_fermi_products`` (``sp2_fermi_products_formed``: those made).
         """
         import torch
         N = H.shape[0]
@@ -356,6 +357,12 @@ class Context:
         self.last_fermi_products = prods.value
         self._check(st, "sp2_fermi_density_matrix")
         return D_out, m.value, its.value
+
+    def sp2_fermi_products_formed(self) -> int:
+        """N x N products launched by the last finite-temperature call."""
+        n = ctypes.c_longlong(0)
+        self._check(lib().sp2_fermi_products_formed(self._h, ctypes.byref(n)), "sp2_fermi_products_formed")
+        return n.value
 
     def sp2_fermi_density_matrix_nonorth(self, H, S, n_occ: float, kT: float, n_steps: int, mu=None,
                                          max_newton: int = 50, tol: float = 1e-10, D_out=None, W_out=None):

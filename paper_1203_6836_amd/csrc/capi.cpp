@@ -88,6 +88,7 @@ struct sp2_ctx {
     double* nobuf = nullptr;
     size_t nocap = 0;
     bool noback = false;   // more than kNobufKeep: given back when the call ends
+    long long formed = 0;  // matrix products launched by the last finite-temperature call
     // non-orthogonal finite-temperature solves: Z, H_perp, D_perp kept
     // across the Fermi-operator and entropy calls (which use nobuf)
     double* ftbuf = nullptr;
@@ -1054,6 +1055,7 @@ static sp2_status prod(sp2_ctx* c, int N, const double* A, const double* B, doub
     sp2_status s = f64_tail_buffer(c, 0, -1, &chunk, &chunk_bytes);
     if (s != SP2_OK) return s;
     GemmTN g{A, B, Cin, C, N, alpha, beta, gamma, keep_split};
+    c->formed += 1;
     HIPCHK(c, launch_gemm_tn(g, sym, 8, chunk, chunk_bytes, c->stream));
     return SP2_OK;
 }
@@ -1580,7 +1582,14 @@ extern "C" sp2_status sp2_fermi_density_matrix(sp2_ctx* c, int N, const double* 
                                                 double* D_out, int* newton_iterations, long long* products) {
     CTX_ENTER(c);
     if (!c) return SP2_EINVAL;
+    if (_ctx_guard.owner) c->formed = 0;
     return fermi_solve(c, N, H, n_occ, kT, n_steps, max_newton, tol, mu, D_out, newton_iterations, products, nullptr);
+}
+
+extern "C" sp2_status sp2_fermi_products_formed(const sp2_ctx* c, long long* products) {
+    if (!c || !products) return SP2_EINVAL;
+    *products = c->formed;
+    return SP2_OK;
 }
 
 // Electronic entropy S / k_B = -2 sum_i [f_i ln f_i + (1 - f_i) ln(1 - f_i)]
@@ -1597,6 +1606,7 @@ extern "C" sp2_status sp2_fermi_entropy(sp2_ctx* c, int N, const double* H, doub
                                          int* moments) {
     CTX_ENTER(c);
     if (!c) return SP2_EINVAL;
+    if (_ctx_guard.owner) c->formed = 0;
     if (moments) *moments = 0;
     if (N < 1 || N > 32768 || !H || !S_out) return fail(c, SP2_EINVAL, "bad entropy arguments");
     if (!(kT > 0.0) || !std::isfinite(kT) || !std::isfinite(mu)) return fail(c, SP2_EINVAL, "need finite mu and kT > 0");
@@ -1643,6 +1653,7 @@ extern "C" sp2_status sp2_fermi_density_matrix_nonorth(sp2_ctx* c, int N, const 
                                                         double* entropy_out, int* newton_iterations) {
     CTX_ENTER(c);
     if (!c) return SP2_EINVAL;
+    if (_ctx_guard.owner) c->formed = 0;
     if (newton_iterations) *newton_iterations = 0;
     if (N < 1 || N > 32768 || !H || !S || !D_out || !mu)
         return fail(c, SP2_EINVAL, "bad non-orthogonal Fermi-operator arguments");

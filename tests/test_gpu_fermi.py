@@ -436,3 +436,30 @@ def test_expansion_gives_its_matrices_back(ctx):
     c.close()
     assert max(kept) <= (2 << 30) + (64 << 20)
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("kT,steps,kw,recursion", [(0.5, 16, {"tol": 1e-8}, False),
+                                                   (0.25, 16, {"max_newton": 0, "mu": -5.0}, True),
+                                                   (0.5, 8, {"tol": 4e-11}, True)])
+def test_products_formed_tell_the_path(ctx, kT, steps, kw, recursion):
+    """N = 108: the recursion launches exactly the products of its count (a
+    fixed mu at kT = 0.25 eV, where one pass is cheaper than the expansion, and
+    a tol below 4e-13 N), the expansion less than half of them; both give the
+    function that the recursion defines, 1 / (1 + exp(2^(n + 1) atanh t)) with
+    t = (e - mu) / (kT 2^(n + 1))."""
+    w, H = lattice((3, 3, 3), 7)
+    Hd = to_dev(H)
+    say(f"case products formed kT={kT} {kw}")
+    D, mu, passes = ctx.sp2_fermi_density_matrix(Hd, w.n_occ, kT, steps, **kw)
+    formed, counted = ctx.sp2_fermi_products_formed(), ctx.last_fermi_products
+    say(f"  formed {formed}, the recursion's {counted} in {passes} passes")
+    e, v = np.linalg.eigh(H)
+    t = (e - mu) / kT / 2.0 ** (steps + 1)
+    f = 1.0 / (1.0 + np.exp(2.0 ** (steps + 1) * np.arctanh(t)))
+    assert np.abs(D.cpu().numpy() - (v * f) @ v.T).max() < 1e-9
+    if recursion:
+        assert formed == counted
+    else:
+        assert 0 < formed < counted / 2
+    ctx.sp2_fermi_entropy(Hd, mu, kT)
+    assert 0 < ctx.sp2_fermi_products_formed() < counted / 2 or recursion
