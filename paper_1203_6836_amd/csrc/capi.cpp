@@ -1110,8 +1110,11 @@ static sp2_status loewdin_factor(sp2_ctx* c, int N, const double* S, double** Zo
         // R_(k+1) = 3/4 R_k^2 + 1/4 R_k^3 for the residual matrix: once that is
         // surely below tol, Z_(k+1) is the factor (and the next iteration the
         // last), and neither Y_(k+1) nor its residual is needed.  Within 10
-        // iterations S / c has no eigenvalue below 0.01, so the residual's
-        // rounding floor lies far under tol (else it has to be looked at)
+        // iterations S / c has no eigenvalue below 0.0059 (the smallest one
+        // that t (3 - t)^2 / 4 brings that close to 1 in so many steps: 0.0089
+        // at N = 128, 0.0072 at 4096, 0.0059 at 65536, as tol grows with N), so
+        // the residual's rounding floor lies far under tol (else it has to
+        // be looked at)
         const bool last = it < 10 && 0.75 * r * r + 0.25 * r * r * r < 0.5 * tol;
         if (!last) {
             if ((s = prod_keep(c, N, Y, T, W, true)) != SP2_OK) return s;     // Y_{k+1} = Y_k T_k
@@ -1192,12 +1195,6 @@ struct ChebBasis {
     double* buf[2] = {nullptr, nullptr};   // two more N x N matrices
     std::vector<double> mom;               // Tr T_k, k < m
 };
-
-static int cheb_stored(int N, int m) {
-    const double cap = std::max(5.0, std::floor(32.0 * 1073741824.0 / (8.0 * N * N)));
-    return cheb_round(std::min((int)std::ceil(std::sqrt((double)m)), (int)cap - 2));
-}
-static int cheb_multiples(int m, int s) { return std::max((m + s - 1) / s - 1, 0); }
 
 // min_s: fewest stored polynomials to try; moments: whether b->mom is formed.
 static sp2_status cheb_moments(sp2_ctx* c, int N, const double* H, double ctr, double w, int m, int min_s, bool moments,

@@ -277,7 +277,6 @@ static hipError_t with_stored(int s, F f) {
         default: return hipErrorInvalidValue;
     }
 }
-int cheb_round(int s) { return s <= 1 ? 1 : s <= 3 ? 2 : s <= 7 ? 4 : std::min(s / 4 * 4, kChebMaxS); }
 
 hipError_t launch_cheb_dots(const double* G0, const double* G1, const double* T, int N, int s, double* part,
                             hipStream_t st) {

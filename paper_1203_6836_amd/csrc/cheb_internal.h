@@ -5,18 +5,16 @@
 
 #include <vector>
 
+#include "cheb_plan.h"
+
 namespace sp2 {
 
-constexpr int kChebMaxS = 32;       // most stored polynomials T_1 .. T_s
 constexpr int kChebBlocks = 1024;   // most workgroups (and partials per sum) of the dot kernel
 
 // T1 = ((H + H^T) / 2 - c I) * inv_w, exactly symmetric.
 hipError_t launch_cheb_scale(const double* H, int N, double c, double inv_w, double* T1, hipStream_t s);
 // out[j - 1] = Tr T_j of the s matrices T (T_j at T + (j - 1) N^2).
 hipError_t launch_cheb_traces(const double* T, int N, int s, double* out, hipStream_t st);
-// The number of stored polynomials the kernels are built for, at most s: 1, 2,
-// 4, 8, 12, .. 32.
-int cheb_round(int s);
 // Partials of Tr G and of <G, T_j> = sum_e G_e T_j,e, j = 1 .. s - 1, for the
 // symmetric matrices G = G0 and, if not null, G1: part[(g s + j) * nblk + b],
 // nblk = cheb_dot_blocks(N) (j = 0 the trace).
