@@ -538,21 +538,28 @@ static sp2_status sp2_solve_in(sp2_ctx* c, int N, const double* H, int n_occ, co
     *progress = 0;
     int seen = 0;   // the last progress word read
     // Product g has been launched: wait until the device is at most `ahead`
-    // products behind (the stream running empty or failing ends the wait as well).
+    // products behind (the stream running empty or failing ends the wait as
+    // well).  The stream is asked only after 100 ms without an answer: each
+    // question puts a marker into it, a gap of 5 us on the device.
     auto follow = [&](int g, int ahead) -> hipError_t {
+        using namespace std::chrono;
+        auto since = steady_clock::now();
         for (unsigned spin = 1;; ++spin) {
             seen = *progress;
             if (progress_done(seen) || g - progress_products(seen) <= ahead) return hipSuccess;
-            if (spin % 65536 == 0) {
-                const hipError_t q = hipStreamQuery(st);
-                if (q == hipSuccess) {
-                    seen = *progress;
-                    return hipSuccess;
-                }
-                if (q != hipErrorNotReady) return q;
-                (void)hipGetLastError();   // not an error of the next launch
-                std::this_thread::sleep_for(std::chrono::microseconds(20));
+            if (spin % 1024) continue;
+            const auto waited = steady_clock::now() - since;
+            if (waited < milliseconds(1)) continue;
+            std::this_thread::sleep_for(microseconds(50));
+            if (waited < milliseconds(100)) continue;
+            const hipError_t q = hipStreamQuery(st);
+            if (q == hipSuccess) {
+                seen = *progress;
+                return hipSuccess;
             }
+            if (q != hipErrorNotReady) return q;
+            (void)hipGetLastError();   // not an error of the next launch
+            since = steady_clock::now();
         }
     };
 

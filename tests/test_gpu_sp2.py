@@ -357,3 +357,25 @@ def test_control_folded_into_the_next_product(ctx, n_atoms, precision, kw):
     assert code == p.SP2_EINVAL
     code, _ = both(deg, 2 * n_atoms + 1)
     assert code == p.SP2_EGAP
+
+
+@pytest.mark.parametrize("opts", [{}, {"tau": 1e-5}])
+def test_solve_behind_other_work_on_its_stream(ctx, opts):
+    """The host waits for the device's progress while about half a second of
+    other work is in front of the solve on the same stream, past the point
+    where it asks the stream itself: the same D as without (control folded into
+    the products, and control kernels)."""
+    import torch
+    import paper_1203_6836_amd as p
+    say(f"case solve behind other work {opts}")
+    pos = synth.lattice_positions((4, 4, 4), seed=0)
+    H = ctx.tb_hamiltonian(synth.STATIC_MODEL, to_dev(pos))
+    D0, s0 = ctx.sp2_density_matrix(H, 128, p.options("fp64", **opts))
+    A = torch.rand((8192, 8192), dtype=torch.float64, device="cuda")
+    A @ A
+    torch.cuda.synchronize()
+    for _ in range(30):
+        A @ A
+    assert not torch.cuda.current_stream().query()
+    D1, s1 = ctx.sp2_density_matrix(H, 128, p.options("fp64", **opts))
+    assert s0["branches"] == s1["branches"] and torch.equal(D0, D1)
