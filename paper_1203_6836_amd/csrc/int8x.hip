@@ -1622,7 +1622,13 @@ static hipError_t launch_list_kernel(SplitScratch& s, double* buf0, double* buf1
 // the 64 x 64 tiles share CUs and follow their number, 10 + 4.8e-5 T K (174 us
 // measured at N = 3072, 170 modelled; 113 against 101 at 2560, which stays on
 // 128).  From ld = 4096 on the 128 x 128 kernel splits its last round and is
-// never behind (N = 5600: 832 against 935 us).
+// never behind (N = 5600: 832 against 935 us).  The model is of four planes and
+// five levels and holds the sizes for every recipe: whole solves per product,
+// 128 x 128 tiles throughout against this rule, N = 720 / 2048 / 2304 / 3072 /
+// 3328: three planes, four levels 42 -> 21, 74 -> 67, 81 -> 76, 182 -> 138, 198
+// -> 178 us; five planes 54 -> 26, 104 -> 102, 116 -> 115, 282 -> 223, 305 ->
+// 278; six 81 -> 31, 169 -> 130, 191 -> 146, 467 -> 297, 503 -> 372.  Sizes
+// between these would gain too with six planes or six levels, not with fewer.
 static bool use_tile64(int ld) {
     if (ld >= 4096) return false;
     const int n128 = ld / QB, n64 = ld / QT, cus = device_cus();
