@@ -272,3 +272,27 @@ def test_requests_that_do_not_wait_for_room(ctx, first):
     srv.close()
     say(f"  quick one: {st['iterations']} products, {st['ms']:.1f} ms; others still running {running}")
     assert st["iterations"] < 16 and all(running)
+
+
+@pytest.mark.parametrize("N", [2, 18, 19, 129])
+def test_smallest_requests_equal_the_direct_solve(ctx, N):
+    """Below N = 19 a request's row maxima take the place of its H check's
+    partials, from there on they lie in D's memory with the partial sums: both
+    ways two requests side by side equal the direct solve bit for bit."""
+    import torch
+    import paper_1203_6836_amd as p
+    say(f"case served N={N}")
+    rng = np.random.default_rng(N)
+    Hs = []
+    for _ in range(2):
+        H = np.triu(rng.uniform(-0.3, 0.3, (N, N)) / np.sqrt(N), 1)
+        Hs.append(H + H.T + np.diag(np.where(np.arange(N) % 2 == 0, -1.0, 1.0)))
+    n_occ = (N + 1) // 2
+    srv = p.Server(ctx, max_slots=2)
+    tk = [srv.sp2_server_submit(H, n_occ) for H in Hs]
+    out = [srv.sp2_server_wait(t, N) for t in tk]
+    srv.close()
+    for H, (D, _, st) in zip(Hs, out):
+        Dd, sd = ctx.sp2_density_matrix(torch.from_numpy(H).cuda(), n_occ, p.options("int8x"))
+        assert st["branches"] == sd["branches"]
+        assert np.array_equal(D, Dd.cpu().numpy())
